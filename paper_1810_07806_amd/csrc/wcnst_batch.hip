@@ -1,15 +1,15 @@
 // Batched solve of many independent 1D Euler problems.
 //
 // Each instance is advanced with exactly the arithmetic of the single-solve
-// path (the same stage kernel body, CFL rule and stopping rule), so it gives
+// path (the same step kernel body, CFL rule and stopping rule), so it gives
 // the same bits batched as alone.  The batch advances in ticks: one tick is
-// `steps` SSP-RK3 steps, i.e. 3 x steps stage launches, each covering the
-// strips of every instance still running (one ReqGrid row, control block,
-// dt and step parity per instance); the launches of a tick are captured in a
-// HIP graph and replayed while the set of running instances is unchanged.
-// Between ticks the host reads the control blocks back, drops the instances
-// that reached t_final or failed, and compacts the table.  Kernel boundaries
-// order the stages: no wave ever waits for another.
+// `steps` SSP-RK3 steps, one launch each, covering the tiles of every
+// instance still running (one ReqGrid row, control block, dt and step parity
+// per instance); the launches of a tick are captured in a HIP graph and
+// replayed while the set of running instances is unchanged.  Between ticks
+// the host reads the control blocks back, drops the instances that reached
+// t_final or failed, and compacts the table.  Kernel boundaries order the
+// steps: no workgroup ever waits for another.
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -43,7 +43,7 @@ struct wcnst_batch {
     bool general = false;       // some instance has reflecting / fixed sides
     // device (caller's workspace)
     ReqGrid* d_req = nullptr;
-    int* d_map = nullptr;  // table row of every block of a stage launch
+    int* d_map = nullptr;  // table row of every block of a step launch
     uint8_t* d_ctrl = nullptr;
     size_t ctrl_bytes = 0;
     double* U1 = nullptr;
@@ -59,7 +59,7 @@ struct wcnst_batch {
     // persistent finish: once the running instances hold at most
     // persist_strips strips, one persistent launch (persist_waves waves per
     // workgroup, persist_group instances each) runs them to their final
-    // times; 0 keeps stage launches to the end
+    // times; 0 keeps step launches to the end
     int persist_strips = 0, persist_waves = 8, persist_group = 1;
     int persist_instances = 0;  // instances the last solve finished in the persistent launch
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
@@ -139,7 +139,7 @@ static wcnst_status batch_check(const wcnst_desc* descs, int32_t n, long long* t
             return wcnst_fail(WCNST_E_INVALID_ARG, "descriptor %d: scheme parameters differ from descriptor 0", i);
         if (offs) (*offs)[i] = off;
         off += ((long long)NV * d.nx + 63) / 64 * 64;  // 512-byte aligned instances
-        nstr += (d.nx + TX - 1) / TX;
+        nstr += wcnst_line_tiles(d.diff, d.nx);
     }
     if (offs) (*offs)[n] = off;
     if (total) *total = off;
@@ -267,9 +267,7 @@ static wcnst_status run_tick(wcnst_batch* b, int nreq, int blocks, int steps, bo
 {
     if (steps != b->steps_per_tick) {
         for (int s = 0; s < steps; ++s)
-            for (int stage = 0; stage < 3; ++stage)
-                WCNST_HIP_TRY(wcnst_launch_multi(&b->d0, 1, b->d_req, b->d_map, nreq, blocks, stage, s & 1, 0, b->general,
-                                                 b->stream));
+            WCNST_HIP_TRY(wcnst_launch_line_multi(&b->d0, b->d_req, b->d_map, nreq, blocks, s & 1, b->stream));
         return WCNST_OK;
     }
     if (!b->exec || table_changed) {
@@ -281,9 +279,7 @@ static wcnst_status run_tick(wcnst_batch* b, int nreq, int blocks, int steps, bo
         WCNST_HIP_TRY(hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal));
         hipError_t le = hipSuccess;
         for (int s = 0; s < steps && le == hipSuccess; ++s)
-            for (int stage = 0; stage < 3 && le == hipSuccess; ++stage)
-                le = wcnst_launch_multi(&b->d0, 1, b->d_req, b->d_map, nreq, blocks, stage, s & 1, 0, b->general,
-                                        b->cap);
+            le = wcnst_launch_line_multi(&b->d0, b->d_req, b->d_map, nreq, blocks, s & 1, b->cap);
         hipError_t ce = hipStreamEndCapture(b->cap, &g);
         if (le != hipSuccess || ce != hipSuccess)
             return wcnst_fail(WCNST_E_HIP, "graph capture failed: %s / %s", hipGetErrorString(le),
@@ -327,8 +323,9 @@ extern "C" wcnst_status wcnst_batch_solve(wcnst_batch* b, double* U, const doubl
         wcnst_make_params(&d, &q.P);
         q.t_final = t_final[i];
         q.cfl = cfl;
-        q.nstrips = (d.nx + TX - 1) / TX;
+        q.nstrips = wcnst_line_tiles(d.diff, d.nx);
         q.parity0 = 0;
+        q.home = 0;
     }
     b->ticks = 0;
     b->graphs = 0;
@@ -365,7 +362,7 @@ extern "C" wcnst_status wcnst_batch_solve(wcnst_batch* b, double* U, const doubl
     uint8_t* snaps[2] = {b->h_ctrl, b->h_ctrl2};
     int uploads = 1;  // the initial table came from tabs[0]
     long long launched = 0;
-    bool changed = true;
+    bool changed = true, persist = false;
     int k = 0;
     while (!active.empty() && launched < (long long)max_steps) {
         const int steps = (int)std::min<long long>(b->steps_per_tick, (long long)max_steps - launched);
@@ -410,36 +407,43 @@ extern "C" wcnst_status wcnst_batch_solve(wcnst_batch* b, double* U, const doubl
             still.reserve(active.size());
             for (int i : active) {
                 const Ctrl& c = *(const Ctrl*)(snap + b->ctrl_bytes * (size_t)i);
-                const bool done = c.status != 0 || c.done != 0 ||
+                const bool done = c.status != 0 || c.bad_key != ~0ull || c.done != 0 ||
                                   (std::isfinite(t_final[i]) && reached(t_final[i], newest(c).t));
                 if (!done) still.push_back(i);
             }
             changed = still.size() != active.size();
             active.swap(still);
             long long strips = 0;
-            for (int i : active) strips += rows[(size_t)i].nstrips;
+            for (int i : active) strips += (b->descs[(size_t)i].nx + TX - 1) / TX;
             if (b->persist_strips > 0 && !active.empty() && strips <= b->persist_strips &&
                 launched < (long long)max_steps) {
-                // the rest in one persistent launch, after the ticks queued
-                // so far (same stream), from the table of the running ones
-                ReqGrid* tab = tabs[uploads & 1];
-                for (size_t j = 0; j < active.size(); ++j) {
-                    const int i = active[j];
-                    tab[j] = rows[(size_t)i];
-                    tab[j].blk0 = 0;
-                    tab[j].parity0 = parity[(size_t)i];
-                }
-                WCNST_HIP_TRY(hipMemcpyAsync(b->d_req, tab, sizeof(ReqGrid) * active.size(), hipMemcpyHostToDevice,
-                                             b->stream));
-                uploads += 1;
-                WCNST_HIP_TRY(wcnst_launch_persist(&b->d0, b->d_req, (int)active.size(), b->persist_group,
-                                                   b->persist_waves, (long long)max_steps - launched, b->general,
-                                                   b->stream));
-                b->persist_instances = (int)active.size();
+                persist = true;
                 break;
             }
         }
         k += 1;
+    }
+    // every instance's newest state into the packed buffer
+    {
+        ReqGrid* tab = tabs[uploads & 1];
+        for (int i = 0; i < n; ++i) tab[i] = rows[(size_t)i];
+        WCNST_HIP_TRY(hipMemcpyAsync(b->d_req, tab, sizeof(ReqGrid) * (size_t)n, hipMemcpyHostToDevice, b->stream));
+        WCNST_HIP_TRY(wcnst_launch_line_settle_multi(b->d_req, n, b->stream));
+        uploads += 1;
+    }
+    if (persist) {
+        // the rest in one persistent launch, from the table of the running
+        // ones (both staging tables may be in flight)
+        WCNST_HIP_TRY(hipStreamSynchronize(b->stream));
+        ReqGrid* tab = tabs[uploads & 1];
+        for (size_t j = 0; j < active.size(); ++j) {
+            tab[j] = rows[(size_t)active[j]];
+            tab[j].nstrips = (tab[j].P.nx + TX - 1) / TX;
+        }
+        WCNST_HIP_TRY(hipMemcpyAsync(b->d_req, tab, sizeof(ReqGrid) * active.size(), hipMemcpyHostToDevice, b->stream));
+        WCNST_HIP_TRY(wcnst_launch_persist(&b->d0, b->d_req, (int)active.size(), b->persist_group, b->persist_waves,
+                                           (long long)max_steps - launched, b->general, b->stream));
+        b->persist_instances = (int)active.size();
     }
     WCNST_HIP_TRY(hipEventRecord(b->ev1, b->stream));
     WCNST_HIP_TRY(hipMemcpyAsync(b->h_ctrl, b->d_ctrl, b->ctrl_bytes * (size_t)n, hipMemcpyDeviceToHost, b->stream));

@@ -163,6 +163,66 @@ struct Strip1D {
     WCNST_HD int nfaces() const { return jmax + G + 1; }
 };
 
+// One tile of a 1D line whose three Runge-Kutta stages run in one launch:
+// the cells [c0, c1) that the tile writes, and for each stage s the cells
+// [A(s), B(s)) whose stage output it forms.  A cell's right-hand side reaches
+// REACH cells to either side (MND: midpoints 3/2 away, each with nodes up to
+// 5/2 away: 4; MD 5; HWCNS 3), so stage s covers REACH (2 - s) more cells at
+// each end.  With ghosts (every side but a periodic one that another tile
+// continues) the line ends there: cells are clipped to [0, nx) and the
+// REACH ghosts beyond each end are formed with the cells, by the same
+// operations on their source cell.  Without, positions beyond the ends are
+// the wrapped cells, formed like any other.
+//
+// Positions (cells and ghosts) are numbered from base(); stage s leaves
+// [out_lo(s), out_hi(s)), which holds what stage s + 1 reads.
+template <int DIFF>
+struct Tile1D {
+    static constexpr int G = DIFF == DIFF_MD ? 3 : (DIFF == DIFF_HW ? 1 : 2);  // midpoints on either side of a cell
+    static constexpr int REACH = DIFF == DIFF_MD ? 5 : (DIFF == DIFF_HW ? 3 : 4);
+    int c0, c1, nx;
+    bool ghosts;
+    // tile t of nt equal tiles of a line of nx cells
+    WCNST_HD Tile1D(int t, int nt, int nx_, int bc) : nx(nx_)
+    {
+        c0 = (int)((long long)t * nx / nt);
+        c1 = (int)((long long)(t + 1) * nx / nt);
+        ghosts = bc != BC_PERIODIC || nt == 1;
+    }
+    WCNST_HD int A(int s) const
+    {
+        const int a = c0 - REACH * (2 - s);
+        return ghosts && a < 0 ? 0 : a;
+    }
+    WCNST_HD int B(int s) const
+    {
+        const int b = c1 + REACH * (2 - s);
+        return ghosts && b > nx ? nx : b;
+    }
+    WCNST_HD int base() const { return A(0) - REACH; }
+    WCNST_HD int positions() const { return B(0) + REACH - base(); }
+    // midpoints A(s) - G + i, i < faces(s): those the cells [A(s), B(s)) need
+    WCNST_HD int faces(int s) const { return B(s) - A(s) + 2 * G - 1; }
+    WCNST_HD int out_lo(int s) const { return ghosts && A(s) == 0 ? -REACH : A(s); }
+    WCNST_HD int out_hi(int s) const { return ghosts && B(s) == nx ? nx + REACH : B(s); }
+    // the cell whose stage output position p takes
+    WCNST_HD int source(int p, int bc) const;
+};
+
+// Threads of a tile, and the tiles of a line of nx cells: as few as let every
+// midpoint and position of the widest stage have a thread of its own.
+constexpr int TILE_THREADS = 256;
+constexpr int LINE_CAP = TILE_THREADS + 8;  // positions of a tile, at most TILE_THREADS + 2 REACH - 2 G + 1
+template <int DIFF>
+WCNST_HD int line_tiles(int nx)
+{
+    using T = Tile1D<DIFF>;
+    // one tile: nx + 2 REACH positions; else W + 4 REACH cells in stage 0
+    if (nx + 2 * T::REACH <= TILE_THREADS) return 1;
+    constexpr int W = TILE_THREADS - 4 * T::REACH - 2 * T::G + 1;
+    return (nx + W - 1) / W;
+}
+
 struct Params {
     double CT, C, eps_teno, eps_js;
     double gamma;
@@ -197,13 +257,16 @@ struct Ctrl {
     long long call_step0;        // step counter at the start of the current solve call
     int status;                  // sticky WCNST_E_NONPHYSICAL
     int done;                    // sticky: t_final reached in the current call
-    int pad[2];
+    // max CFL speed (bit pattern) of the state after step n in speed[n % 3]:
+    // a launch that runs a whole step reads one, accumulates the next, and
+    // clears the one after
+    unsigned long long speed[3];
 };
 
 // One grid (1D or 2D) of a multi-grid stage launch: its buffers (U holds
 // the state at t^n, U1 / U2 the stage states), control block, parameters,
-// and its first block in the launch (blocks blk0 .. blk0 + nstrips*nseg - 1,
-// nseg = 1 in 1D).
+// and its first block in the launch (blocks blk0 .. blk0 + nstrips*nseg - 1;
+// in 1D nstrips counts the line's tiles, nseg = 1).
 struct ReqGrid {
     double* U;
     double* U1;
@@ -213,10 +276,28 @@ struct ReqGrid {
     double t_final, cfl;
     int nstrips, blk0;
     int parity0;  // step parity at tick step 0
-    int pad;
+    int home;     // 1D: step parity at which the state is in U (else in U1)
+};
+
+// One step of a 1D line: dt = fixed_dt when > 0, else cfl / CFL speed,
+// clipped to t_final; the current record is rec[parity].
+struct LineStep {
+    double t_final, cfl, fixed_dt;
+    int parity;
 };
 
 // ------------------------------------------------------------ helpers
+
+// Whether a rare condition holds on any lane of the wavefront: one scalar
+// branch, laid out so that the common path runs straight through.
+WCNST_HD bool any_lane(bool rare)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_expect(__builtin_amdgcn_ballot_w64(rare) != 0ull, 0);
+#else
+    return rare;
+#endif
+}
 
 // A copy of a table entry.  Tables reach device memory by copies ordered
 // before the launch on its stream, so plain loads see them.
@@ -256,6 +337,12 @@ WCNST_HD int ghost_map_any(int g, int n, int bc)
     }
     g = g < 0 ? 0 : g;
     return g >= n ? n - 1 : g;
+}
+
+template <int DIFF>
+WCNST_HD int Tile1D<DIFF>::source(int p, int bc) const
+{
+    return ghosts ? ghost_map(p, nx, bc) : p;
 }
 
 // What a ghost holds besides its source cell's value: GH_COPY (interior
@@ -458,41 +545,45 @@ WCNST_HD double interp_side(double c, double D10, double D11, double D12, double
             w1 = a1 / s;
             w2 = a2 / s;
         } else {
-            // Eq. (16); Eqs. (17)-(18) as gamma_k < C_T * sum(gamma)
-            const double tau = fabs(b0 - b2);
-            const double e0 = b0 + P.eps_teno, e1 = b1 + P.eps_teno, e2 = b2 + P.eps_teno;
             // Smooth data keep every candidate without the measure: with
-            // tau <= t e_min each C + tau/e_k lies in [C, C + t], so
-            // chi_k >= C^q / (3 (C + t)^q), which P.teno_smooth (t) keeps
-            // above C_T by a margin far beyond rounding.
-            mask = 7u;
-            if (!(tau <= P.teno_smooth * fmin(fmin(e0, e1), e2))) {
-                const int q = SCHEME == SCH_TENO ? 6 : P.q;
-                double x0 = fma(tau, approx_rcp(e0), P.C);
-                double x1 = fma(tau, approx_rcp(e1), P.C);
-                double x2 = fma(tau, approx_rcp(e2), P.C);
-                if constexpr (SCHEME == SCH_TENO_Q) {
-                    // the test is unchanged when every C + tau/e_k is scaled
-                    // by one power of two; scaled by that of the largest, the
-                    // powers and their sum stay finite where they would
-                    // overflow (q = 8 with eps = 1e-40: tau near 0.03), and
-                    // every comparison is decided as unscaled where they
-                    // would not.  With q = 6 the powers stay finite while
-                    // C + tau/e_k <= 8e50, and the scaling (1.6 % of the 2D
-                    // stage) is left out.
-                    int ex;
-                    (void)frexp(fmax(fmax(x0, x1), x2), &ex);
-                    x0 = ldexp(x0, -ex);
-                    x1 = ldexp(x1, -ex);
-                    x2 = ldexp(x2, -ex);
-                }
-                const double g0 = pow_q(x0, q);
-                const double g1 = pow_q(x1, q);
-                const double g2 = pow_q(x2, q);
-                const double thr = P.CT * (g0 + g1 + g2);
-                const bool k0 = !(g0 < thr), k1 = !(g1 < thr), k2 = !(g2 < thr);
-                mask = (unsigned)k0 | ((unsigned)k1 << 1) | ((unsigned)k2 << 2);
+            // tau <= t beta_k for all k, each C + tau/(beta_k + eps) lies in
+            // [C, C + t], so chi_k >= C^q / (3 (C + t)^q), which
+            // P.teno_smooth (t) keeps above C_T by a margin far beyond
+            // rounding.  Where every lane's data are smooth the weights are
+            // constants, else every lane takes the measure, which keeps the
+            // smooth ones' candidates too (no table reads on smooth data;
+            // 163 -> 145 registers in the 1D step).
+            const double tau = fabs(b0 - b2);
+            if (!any_lane(!(tau <= P.teno_smooth * fmin(fmin(b0, b1), b2)))) {
+                mask = 7u;
+                return fma(5.0 / 16.0, q2, fma(10.0 / 16.0, q1, (1.0 / 16.0) * q0));
             }
+            // Eq. (16); Eqs. (17)-(18) as gamma_k < C_T * sum(gamma)
+            const double e0 = b0 + P.eps_teno, e1 = b1 + P.eps_teno, e2 = b2 + P.eps_teno;
+            const int q = SCHEME == SCH_TENO ? 6 : P.q;
+            double x0 = fma(tau, approx_rcp(e0), P.C);
+            double x1 = fma(tau, approx_rcp(e1), P.C);
+            double x2 = fma(tau, approx_rcp(e2), P.C);
+            if constexpr (SCHEME == SCH_TENO_Q) {
+                // the test is unchanged when every C + tau/e_k is scaled by
+                // one power of two; scaled by that of the largest, the powers
+                // and their sum stay finite where they would overflow (q = 8
+                // with eps = 1e-40: tau near 0.03), and every comparison is
+                // decided as unscaled where they would not.  With q = 6 the
+                // powers stay finite while C + tau/e_k <= 8e50, and the
+                // scaling (1.6 % of the 2D stage) is left out.
+                int ex;
+                (void)frexp(fmax(fmax(x0, x1), x2), &ex);
+                x0 = ldexp(x0, -ex);
+                x1 = ldexp(x1, -ex);
+                x2 = ldexp(x2, -ex);
+            }
+            const double g0 = pow_q(x0, q);
+            const double g1 = pow_q(x1, q);
+            const double g2 = pow_q(x2, q);
+            const double thr = P.CT * (g0 + g1 + g2);
+            const bool k0 = !(g0 < thr), k1 = !(g1 < thr), k2 = !(g2 < thr);
+            mask = (unsigned)k0 | ((unsigned)k1 << 1) | ((unsigned)k2 << 2);
             // Eq. (19): d_k delta_k / sum_m d_m delta_m, the exact quotient
             // for each of the seven patterns
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -612,31 +703,80 @@ struct Eigen {
     WCNST_HD double lam(int k) const { return k == 0 ? u - c : (k == NV - 1 ? u + c : u); }
 };
 
-// With RANGED the result is exact (equal to the IEEE one) where the return
-// value is true: the densities and c^2 lie in [2^-767, 2^1022), and with
-// them every other argument of a reciprocal or root.
-template <int NV, bool RANGED = false>
-WCNST_HD bool roe_eigen(const double* A, const double* B, double gamma, Eigen<NV>& E)
+// What the Roe average, the node flux and the stage checks take from one
+// state: velocities, pressure, total enthalpy, sqrt(rho) and 1/rho.
+template <int NV>
+struct Node {
+    double u, v, p, H, s, ir;
+};
+
+template <int NV, bool RANGED>
+WCNST_HD void node_quantities(const double* U, double gamma, Node<NV>& N)
 {
-    const double rA = A[0], rB = B[0];
-    const double irA = recip<RANGED>(rA), irB = recip<RANGED>(rB);
-    const double uA = A[1] * irA, uB = B[1] * irB;
-    const double vA = NV == 4 ? A[2] * irA : 0.0, vB = NV == 4 ? B[2] * irB : 0.0;
-    const double HA = (A[NV - 1] + pressure<NV>(A, gamma, irA)) * irA;
-    const double HB = (B[NV - 1] + pressure<NV>(B, gamma, irB)) * irB;
-    const double sA = root<RANGED>(rA), sB = root<RANGED>(rB);
-    const double is = recip<RANGED>(sA + sB);
-    E.u = (sA * uA + sB * uB) * is;
-    E.v = (sA * vA + sB * vB) * is;
-    E.H = (sA * HA + sB * HB) * is;
-    E.q2 = E.u * E.u + E.v * E.v;
+    N.ir = recip<RANGED>(U[0]);
+    N.u = U[1] * N.ir;
+    if constexpr (NV == 4) N.v = U[2] * N.ir;
+    N.p = pressure<NV>(U, gamma, N.ir);
+    N.H = (U[NV - 1] + N.p) * N.ir;
+    N.s = root<RANGED>(U[0]);
+}
+
+// The same by the ranged sequences, and by the IEEE operations where rho
+// leaves their range.
+template <int NV>
+WCNST_HD void node_quantities(const double* U, double gamma, Node<NV>& N)
+{
+    node_quantities<NV, true>(U, gamma, N);
+    const bool ok = in_ieee_range(U[0]);
+    if (any_lane(!ok)) {
+        if (!ok) node_quantities<NV, false>(U, gamma, N);
+    }
+}
+
+// Roe average of two nodes and its eigen-system.  With RANGED it is exact
+// (equal to the IEEE one) where the return value is true: sqrt(rho_A) +
+// sqrt(rho_B) and c^2 lie in [2^-767, 2^1022), and with them every argument
+// of a reciprocal or root here.
+template <int NV, bool RANGED>
+WCNST_HD bool roe_average(const Node<NV>& A, const Node<NV>& B, double gamma, Eigen<NV>& E)
+{
+    const double ss = A.s + B.s;
+    const double is = recip<RANGED>(ss);
+    E.u = (A.s * A.u + B.s * B.u) * is;
+    E.H = (A.s * A.H + B.s * B.H) * is;
+    E.q2 = E.u * E.u;
+    if constexpr (NV == 4) {
+        E.v = (A.s * A.v + B.s * B.v) * is;
+        E.q2 = E.q2 + E.v * E.v;
+    }
     const double c2 = (gamma - 1.0) * (E.H - 0.5 * E.q2);
     E.c = root<RANGED>(c2);
     E.ic = recip<RANGED>(E.c);
     E.b1 = (gamma - 1.0) * (E.ic * E.ic);
     E.b2 = 0.5 * E.q2 * E.b1;
     E.uc = E.u * E.ic;
-    return !RANGED || (in_ieee_range(rA) && in_ieee_range(rB) && in_ieee_range(c2));
+    return !RANGED || (in_ieee_range(ss) && in_ieee_range(c2));
+}
+
+template <int NV>
+WCNST_HD void roe_average(const Node<NV>& A, const Node<NV>& B, double gamma, Eigen<NV>& E)
+{
+    const bool ok = roe_average<NV, true>(A, B, gamma, E);
+    if (any_lane(!ok)) {
+        if (!ok) roe_average<NV, false>(A, B, gamma, E);
+    }
+}
+
+// Roe average of two states.  With RANGED the result is exact where the
+// return value is true: the densities lie in that range too.
+template <int NV, bool RANGED = false>
+WCNST_HD bool roe_eigen(const double* A, const double* B, double gamma, Eigen<NV>& E)
+{
+    Node<NV> NA, NB;
+    node_quantities<NV, RANGED>(A, gamma, NA);
+    node_quantities<NV, RANGED>(B, gamma, NB);
+    const bool ok = roe_average<NV, RANGED>(NA, NB, gamma, E);
+    return !RANGED || (ok && in_ieee_range(A[0]) && in_ieee_range(B[0]));
 }
 
 // van Leer's split normal flux (the flux named for the results of Sec. 3;
@@ -708,10 +848,13 @@ WCNST_HD void euler_num_flux(const double* UL, const double* UR, double gamma, d
     } else {
         Eigen<NV> E;
         // (the test covers rho_L and rho_R, the reciprocals' arguments)
-        if (!roe_eigen<NV, RG>(UL, UR, gamma, E)) {
-            euler_flux<NV>(UL, gamma, FL);
-            euler_flux<NV>(UR, gamma, FR);
-            roe_eigen<NV>(UL, UR, gamma, E);
+        const bool ok = roe_eigen<NV, RG>(UL, UR, gamma, E);
+        if (any_lane(!ok)) {
+            if (!ok) {
+                euler_flux<NV>(UL, gamma, FL);
+                euler_flux<NV>(UR, gamma, FR);
+                roe_eigen<NV>(UL, UR, gamma, E);
+            }
         }
         double alpha[NV];
 #pragma unroll
@@ -763,7 +906,10 @@ WCNST_HD void midpoint_eigen(ST& st, const Params& P, Eigen<NV>& E)
         A[v] = st(2, v);
         B[v] = st(3, v);
     }
-    if (!roe_eigen<NV, true>(A, B, P.gamma, E)) roe_eigen<NV>(A, B, P.gamma, E);
+    const bool ok = roe_eigen<NV, true>(A, B, P.gamma, E);
+    if (any_lane(!ok)) {
+        if (!ok) roe_eigen<NV>(A, B, P.gamma, E);
+    }
 }
 
 // Characteristic field k of the six stencil nodes, w_m = l_k . U_m (sums
@@ -804,17 +950,18 @@ WCNST_HD void back_project_field(const Eigen<NV>& E, int k, double wl, double wr
     }
 }
 
-// s: nodes j-2 .. j+3 around x_{j+1/2}.  F: flux at x_{j+1/2}.
-// fb: 6 flag bits per field (left mask | right mask << 3).
-template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, class ST>
-WCNST_HD void face_flux(ST& st, const Params& P, double (&F)[NV], unsigned& fb)
+// s: nodes j-2 .. j+3 around x_{j+1/2}.  basis(E): the characteristic basis
+// there.  F: flux at x_{j+1/2}.  fb: 6 flag bits per field (left mask |
+// right mask << 3).
+template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, class ST, class BASIS>
+WCNST_HD void face_flux(ST& st, const Params& P, double (&F)[NV], unsigned& fb, const BASIS& basis)
 {
     fb = 0u;
     if constexpr (SYS == SYS_EULER) {
         double UL[NV], UR[NV];
         if constexpr (CHAR) {
             Eigen<NV> E;
-            midpoint_eigen<NV>(st, P, E);
+            basis(E);
             // one characteristic field at a time: project, interpolate both
             // sides, and add its share of the back-projection
 #pragma unroll
@@ -855,6 +1002,23 @@ WCNST_HD void face_flux(ST& st, const Params& P, double (&F)[NV], unsigned& fb)
     }
 }
 
+// The same with the basis formed from the states of nodes j and j+1.
+template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, class ST>
+WCNST_HD void face_flux(ST& st, const Params& P, double (&F)[NV], unsigned& fb)
+{
+    face_flux<SYS, NV, FLUX, SCHEME, CHAR>(st, P, F, fb, [&](auto& E) { midpoint_eigen<NV>(st, P, E); });
+}
+
+// Normal flux of a node from its quantities (the operations of euler_flux).
+template <int NV>
+WCNST_HD void node_flux(const double* U, const Node<NV>& N, double* F)
+{
+    F[0] = U[1];
+    F[1] = U[1] * N.u + N.p;
+    if constexpr (NV == 4) F[2] = U[2] * N.u;
+    F[NV - 1] = N.u * (U[NV - 1] + N.p);
+}
+
 template <int SYS, int NV>
 WCNST_HD void node_flux(const double* U, const Params& P, double* F)
 {
@@ -863,7 +1027,10 @@ WCNST_HD void node_flux(const double* U, const Params& P, double* F)
             // 1D: 1/rho by the ranged sequence, the IEEE division where rho
             // leaves its range
             euler_flux<NV, true>(U, P.gamma, F);
-            if (!in_ieee_range(U[0])) euler_flux<NV>(U, P.gamma, F);
+            const bool ok = in_ieee_range(U[0]);
+            if (any_lane(!ok)) {
+                if (!ok) euler_flux<NV>(U, P.gamma, F);
+            }
         } else {
             euler_flux<NV>(U, P.gamma, F);
         }
@@ -897,17 +1064,39 @@ WCNST_HD bool cell_bad(const double* U, const Params& P)
     return bad;
 }
 
+// cell_speed and cell_bad from the quantities of the state (the same
+// operations).
+template <int NV>
+WCNST_HD double node_speed(const Node<NV>& N, const Params& P)
+{
+    const double a = sqrt(P.gamma * N.p * N.ir);
+    double s = (fabs(N.u) + a) / P.dx;
+    if constexpr (NV == 4) s = s + (fabs(N.v) + a) / P.dy;
+    return s;
+}
+
+template <int NV>
+WCNST_HD bool node_bad(const double* U, const Node<NV>& N)
+{
+    bool bad = false;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) bad |= !isfinite(U[v]);
+    return bad | !(U[0] > 0.0) | !(N.p > 0.0);
+}
+
 // Stage update in the Shu-Osher form of SSP-RK3.
 template <int NV>
 WCNST_HD void rk_combine(int stage, double dt, const double* Uk, const double* Un, const double* R,
                          double* o)
 {
+    if (stage == 0) {
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        if (stage == 0) o[v] = Uk[v] + dt * R[v];
-        else if (stage == 1) o[v] = 0.75 * Un[v] + 0.25 * (Uk[v] + dt * R[v]);
-        else o[v] = (1.0 / 3.0) * Un[v] + (2.0 / 3.0) * (Uk[v] + dt * R[v]);
+        for (int v = 0; v < NV; ++v) o[v] = Uk[v] + dt * R[v];
+        return;
     }
+    const double a = stage == 1 ? 0.75 : 1.0 / 3.0, b = stage == 1 ? 0.25 : 2.0 / 3.0;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) o[v] = a * Un[v] + b * (Uk[v] + dt * R[v]);
 }
 
 // MD difference, Eq. (3): -(a1 (F_{i+1/2} - F_{i-1/2}) + a2 (F_{i+3/2} - F_{i-3/2})

@@ -18,22 +18,44 @@ size_t wcnst_align256(size_t b);
 
 namespace wcnst {
 struct Params;
+struct Ctrl;
+struct LineStep;
 }
 // Solver parameters of a validated descriptor (spacing, Eq. (5) coefficients).
 void wcnst_make_params(const wcnst_desc* d, wcnst::Params* out);
 
-// Multi-grid stage launches: bytes of one control block; reset it to t = 0
-// and accumulate the CFL speed of U (1D or 2D Euler grid d) into its record
-// 0; one stage of every grid of a ReqGrid table of one dimension (nblocks =
-// total strips in 1D, total segments of ty rows in 2D).
+// Multi-grid launches: bytes of one control block; reset it to t = 0 and
+// accumulate the CFL speed of U (1D or 2D Euler grid d) for step 0; one
+// stage of every 2D grid of a ReqGrid table (nblocks = total segments of ty
+// rows).
 size_t wcnst_ctrl_bytes();
 hipError_t wcnst_launch_init_grid(const wcnst_desc* d, const double* U, void* ctrl, hipStream_t st);
 // general: some grid of the table has reflecting / fixed sides or gravity
 // (the tables then take the stage kernels that handle them).
 // map (nullable): the table row of every block (wcnst_launch_block_map);
 // without one each block searches the table.
-hipError_t wcnst_launch_multi(const wcnst_desc* d, int ndim, const void* reqs, const int* map, int nreq, int nblocks,
-                              int stage, int tick_step, int ty, bool general, hipStream_t st);
+hipError_t wcnst_launch_multi(const wcnst_desc* d, const void* reqs, const int* map, int nreq, int nblocks, int stage,
+                              int tick_step, int ty, bool general, hipStream_t st);
+// 1D lines.  Tiles (workgroups) of a line; one whole SSP-RK3 step of one
+// line, in -> out, or of every 1D Euler line of a ReqGrid table (nblocks =
+// total tiles), whose state alternates between U and U1 with the step
+// parity; and the end of a run of steps: the newest state into U (from U1
+// where the newest record's parity is not the line's home parity), the
+// status of a failure in the last step, the CFL speed into the newest record.
+int wcnst_line_tiles(int diff, int nx);
+hipError_t wcnst_launch_line_step(const wcnst_desc* d, const wcnst::Params& P, wcnst::Ctrl* ctrl, const double* in,
+                                  double* out, const wcnst::LineStep& A, hipStream_t st);
+hipError_t wcnst_launch_line_multi(const wcnst_desc* d, const void* reqs, const int* map, int nreq, int nblocks,
+                                   int tick_step, hipStream_t st);
+// Whether one workgroup runs the whole line, and up to `steps` steps of it in
+// one launch, in place (open: the start of a solve or step call; nothing
+// else has to be launched before it).
+bool wcnst_line_solo(const wcnst_desc* d);
+hipError_t wcnst_launch_line_solo(const wcnst_desc* d, const wcnst::Params& P, wcnst::Ctrl* ctrl, double* U,
+                                  const wcnst::LineStep& A, int steps, bool open, hipStream_t st);
+hipError_t wcnst_launch_line_settle(wcnst::Ctrl* ctrl, double* U, const double* U1, long long n, int home,
+                                    hipStream_t st);
+hipError_t wcnst_launch_line_settle_multi(const void* reqs, int nreq, hipStream_t st);
 // One persistent launch that runs the nreq 1D grids of a table to their
 // final times (or max_steps more steps): per_group grids per workgroup of
 // `waves` wavefronts (at most 8 each).

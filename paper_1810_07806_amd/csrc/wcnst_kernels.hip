@@ -147,25 +147,18 @@ __device__ __forceinline__ void write_flags(uint8_t* fl, int nlines, int nfaces,
 
 // ------------------------------------------------------------------ 1D
 
-// Strip bx of one 1D grid (geometry in Strip1D).  Thread 0 of strip 0
-// opens the next step record.
-// GB: general boundaries (reflecting walls, fixed ends); without it only
-// index-remap sides (periodic, zero gradient).
-template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, int MODE, int DIFF = DIFF_MND, bool GB = true>
-__device__ __forceinline__ void sweep1d_block(const double* __restrict__ U, const double* __restrict__ Un,
-                                              double* __restrict__ out, uint8_t* __restrict__ flags,
-                                              Ctrl* __restrict__ ctrl, const Params& P, const StageArgs& A, int bx)
+// Right-hand side of strip bx of one 1D grid (geometry in Strip1D).
+template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, int DIFF>
+__global__ void __launch_bounds__(WAVE)
+sweep1d(const double* __restrict__ U, double* __restrict__ out, uint8_t* __restrict__ flags, Params P)
 {
     constexpr int G = Strip1D<DIFF>::G;
     const int nx = P.nx;
-    const int lane = threadIdx.x;
+    const int bx = (int)blockIdx.x, lane = (int)threadIdx.x;
     const Strip1D<DIFF> S(bx, lane, nx);
     const int c = S.c, jx = S.jx, jxl = S.jxl;
-    const bool cell_ok = S.cell_ok;
 
-    // the stencil (and U^n of this lane's cell) load while the control
-    // record is read
-    double s[6][NV], un[NV];
+    double s[6][NV];
 #pragma unroll
     for (int m = 0; m < 6; ++m) {
         // HWCNS lanes reach up to 5 cells past the line: any-distance map
@@ -173,7 +166,7 @@ __device__ __forceinline__ void sweep1d_block(const double* __restrict__ U, cons
 #pragma unroll
         for (int v = 0; v < NV; ++v) s[m][v] = U[(size_t)v * nx + col];
     }
-    if (GB && P.bc_x >= BC_REFLECT) {
+    if (P.bc_x >= BC_REFLECT) {
         // reflecting walls reverse the momentum of their ghosts; fixed ends
         // supply their own states
 #pragma unroll
@@ -183,14 +176,6 @@ __device__ __forceinline__ void sweep1d_block(const double* __restrict__ U, cons
             for (int v = 0; v < NV; ++v) s[m][v] = ghost_value(kind, v, 1, s[m][v], P.fixed_x);
         }
     }
-#pragma unroll
-    for (int v = 0; v < NV; ++v) un[v] = MODE == MODE_STAGE && A.stage && cell_ok ? Un[(size_t)v * nx + c] : 0.0;
-    double dt = 0.0;
-    long long step = 0;
-    unsigned long long seen = 0ull;
-    if constexpr (MODE == MODE_STAGE) {
-        if (!stage_prologue(ctrl, A, dt, step, bx == 0 && threadIdx.x == 0, seen)) return;
-    }
     __shared__ double sF[NV][WAVE];
     __shared__ double sN[NV][WAVE];
     init_weight_table();
@@ -198,7 +183,7 @@ __device__ __forceinline__ void sweep1d_block(const double* __restrict__ U, cons
     unsigned fb;
     RegStencil<NV> st{s};
     face_flux<SYS, NV, FLUX, SCHEME, CHAR>(st, P, F, fb);
-    if (MODE == MODE_RHS && flags && S.owns_face(bx, nx)) write_flags<NV>(flags, 1, S.nfaces(), 0, jx + G, fb);
+    if (flags && S.owns_face(bx, nx)) write_flags<NV>(flags, 1, S.nfaces(), 0, jx + G, fb);
     // node flux: MND at node jx+1 (stencil node 3), HWCNS at node jx-1 (1)
     if constexpr (DIFF == DIFF_MND) node_flux<SYS, NV>(s[3], P, fn);
     if constexpr (DIFF == DIFF_HW) node_flux<SYS, NV>(s[1], P, fn);
@@ -208,177 +193,21 @@ __device__ __forceinline__ void sweep1d_block(const double* __restrict__ U, cons
         if constexpr (DIFF != DIFF_MD) sN[v][lane] = fn[v];
     }
     __syncthreads();
-    unsigned long long sm = 0ull;
-    if (cell_ok) {
-        double R[NV];
+    if (!S.cell_ok) return;
 #pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            if constexpr (DIFF == DIFF_MD)
-                R[v] = md(P.c1x, P.c2x, P.c3x, sF[v][lane], sF[v][lane + 1], sF[v][lane + 2], sF[v][lane + 3],
-                          sF[v][lane + 4], sF[v][lane + 5]);
-            else if constexpr (DIFF == DIFF_HW)
-                R[v] = hwcns(P.c1x, P.c2x, P.c3x, sF[v][lane], sF[v][lane + 1], sN[v][lane], sN[v][lane + 1],
-                             sN[v][lane + 3], sN[v][lane + 4]);
-            else
-                R[v] = mnd(P.c1x, P.c2x, P.c3x, sF[v][lane], sF[v][lane + 1], sF[v][lane + 2], sF[v][lane + 3],
-                           sN[v][lane], sN[v][lane + 2]);
-        }
-        if constexpr (MODE == MODE_RHS) {
-#pragma unroll
-            for (int v = 0; v < NV; ++v) out[(size_t)v * nx + c] = R[v];
-        } else {
-            double o[NV];
-            rk_combine<NV>(A.stage, dt, s[G + 2], un, R, o);
-#pragma unroll
-            for (int v = 0; v < NV; ++v) out[(size_t)v * nx + c] = o[v];
-            stage_epilogue<SYS, NV>(ctrl, P, A.stage, step, c, o, sm);
-        }
+    for (int v = 0; v < NV; ++v) {
+        double r;
+        if constexpr (DIFF == DIFF_MD)
+            r = md(P.c1x, P.c2x, P.c3x, sF[v][lane], sF[v][lane + 1], sF[v][lane + 2], sF[v][lane + 3],
+                   sF[v][lane + 4], sF[v][lane + 5]);
+        else if constexpr (DIFF == DIFF_HW)
+            r = hwcns(P.c1x, P.c2x, P.c3x, sF[v][lane], sF[v][lane + 1], sN[v][lane], sN[v][lane + 1],
+                      sN[v][lane + 3], sN[v][lane + 4]);
+        else
+            r = mnd(P.c1x, P.c2x, P.c3x, sF[v][lane], sF[v][lane + 1], sF[v][lane + 2], sF[v][lane + 3],
+                    sN[v][lane], sN[v][lane + 2]);
+        out[(size_t)v * nx + c] = r;
     }
-    if constexpr (MODE == MODE_STAGE) {
-        if (A.stage == 2) flush_speed(ctrl, A.parity, sm, seen);
-    }
-}
-
-template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, int MODE, int DIFF>
-__global__ void __launch_bounds__(WAVE)
-sweep1d(const double* __restrict__ U, const double* __restrict__ Un, double* __restrict__ out,
-        uint8_t* __restrict__ flags, Ctrl* __restrict__ ctrl, Params P, StageArgs A)
-{
-    sweep1d_block<SYS, NV, FLUX, SCHEME, CHAR, MODE, DIFF>(U, Un, out, flags, ctrl, P, A, (int)blockIdx.x);
-}
-
-// ------------------------------------------------------ 1D latency mode
-
-// A stage over a few strips cannot fill the chip, and each launch then
-// lasts about one wavefront's dependent chain.  In the latency mode a strip
-// of a 1D Euler grid gets a workgroup of three wavefronts: wavefront k
-// interpolates characteristic field k (conserved component k when not
-// characteristic-wise) at the strip's 64 midpoints; the interpolated values
-// meet in LDS; wavefront 0 forms the back-projection and the midpoint flux
-// while wavefront 1 forms the node flux; wavefront 0 finishes the MND
-// difference, the stage update, the non-physical check and the CFL speed.
-// Each value is formed by the operations of the one-wavefront kernel in the
-// same order, so the results are the same bits.
-constexpr int SPLIT_WAVES = 3;
-// Strips up to which single 1D Euler solves use it (three wavefronts per
-// strip on the 1024 SIMDs of the chip).
-constexpr int SPLIT_STRIPS = 256;
-
-template <int FLUX, int SCHEME, bool CHAR, bool GB>
-__device__ __forceinline__ void strip1d_split(const double* __restrict__ U, const double* __restrict__ Un,
-                                              double* __restrict__ out, Ctrl* __restrict__ ctrl, const Params& P,
-                                              const StageArgs& A, int bx)
-{
-    constexpr int NV = 3;
-    const int wave = (int)threadIdx.x / WAVE;
-    const int lane = (int)threadIdx.x & (WAVE - 1);
-    const int nx = P.nx;
-    const Strip1D<DIFF_MND> S(bx, lane, nx);
-    __shared__ double sW[NV][2][WAVE];
-    __shared__ double sF[NV][WAVE];
-    __shared__ double sN[NV][WAVE];
-    __shared__ double s_dt;
-    __shared__ long long s_step;
-    __shared__ unsigned long long s_seen;
-    __shared__ int s_go;
-
-    double s[6][NV], un[NV];
-#pragma unroll
-    for (int m = 0; m < 6; ++m) {
-        const int col = ghost_map(S.jxl - 2 + m, nx, P.bc_x);
-#pragma unroll
-        for (int v = 0; v < NV; ++v) s[m][v] = U[(size_t)v * nx + col];
-    }
-    if (GB && P.bc_x >= BC_REFLECT) {
-#pragma unroll
-        for (int m = 0; m < 6; ++m) {
-            const int kind = ghost_kind(S.jxl - 2 + m, nx, P.bc_x);
-#pragma unroll
-            for (int v = 0; v < NV; ++v) s[m][v] = ghost_value(kind, v, 1, s[m][v], P.fixed_x);
-        }
-    }
-#pragma unroll
-    for (int v = 0; v < NV; ++v) un[v] = wave == 0 && A.stage && S.cell_ok ? Un[(size_t)v * nx + S.c] : 0.0;
-    // the step record, read once for the workgroup
-    if (threadIdx.x == 0) {
-        double dt = 0.0;
-        long long step = 0;
-        unsigned long long seen = 0ull;
-        s_go = stage_prologue(ctrl, A, dt, step, bx == 0, seen) ? 1 : 0;
-        s_dt = dt;
-        s_step = step;
-        s_seen = seen;
-    }
-    init_weight_table();  // (its barrier also publishes the record)
-    if (!s_go) return;    // one value for the whole workgroup
-
-    RegStencil<NV> st{s};
-    Eigen<NV> E;
-    {
-        double wl, wr;
-        unsigned mL, mR;
-        if constexpr (CHAR) {
-            midpoint_eigen<NV>(st, P, E);
-            double w[6];
-            if (wave == 0) project_field<NV>(st, E, 0, w);
-            else if (wave == 1) project_field<NV>(st, E, 1, w);
-            else project_field<NV>(st, E, 2, w);
-            interp_pair<SCHEME>(w[0], w[1], w[2], w[3], w[4], w[5], P, wl, wr, mL, mR);
-        } else if (wave == 0) {
-            interp_pair<SCHEME>(s[0][0], s[1][0], s[2][0], s[3][0], s[4][0], s[5][0], P, wl, wr, mL, mR);
-        } else if (wave == 1) {
-            interp_pair<SCHEME>(s[0][1], s[1][1], s[2][1], s[3][1], s[4][1], s[5][1], P, wl, wr, mL, mR);
-        } else {
-            interp_pair<SCHEME>(s[0][2], s[1][2], s[2][2], s[3][2], s[4][2], s[5][2], P, wl, wr, mL, mR);
-        }
-        sW[wave][0][lane] = wl;
-        sW[wave][1][lane] = wr;
-    }
-    __syncthreads();
-    if (wave == 0) {
-        double UL[NV], UR[NV], F[NV];
-        if constexpr (CHAR) {
-#pragma unroll
-            for (int k = 0; k < NV; ++k) back_project_field<NV>(E, k, sW[k][0][lane], sW[k][1][lane], UL, UR);
-        } else {
-#pragma unroll
-            for (int v = 0; v < NV; ++v) {
-                UL[v] = sW[v][0][lane];
-                UR[v] = sW[v][1][lane];
-            }
-        }
-        euler_num_flux<NV, FLUX>(UL, UR, P.gamma, F);
-#pragma unroll
-        for (int v = 0; v < NV; ++v) sF[v][lane] = F[v];
-    } else if (wave == 1) {
-        double fn[NV];
-        node_flux<SYS_EULER, NV>(s[3], P, fn);
-#pragma unroll
-        for (int v = 0; v < NV; ++v) sN[v][lane] = fn[v];
-    }
-    __syncthreads();
-    if (wave != 0) return;
-    unsigned long long sm = 0ull;
-    if (S.cell_ok) {
-        double R[NV], o[NV];
-#pragma unroll
-        for (int v = 0; v < NV; ++v)
-            R[v] = mnd(P.c1x, P.c2x, P.c3x, sF[v][lane], sF[v][lane + 1], sF[v][lane + 2], sF[v][lane + 3],
-                       sN[v][lane], sN[v][lane + 2]);
-        rk_combine<NV>(A.stage, s_dt, s[4], un, R, o);
-#pragma unroll
-        for (int v = 0; v < NV; ++v) out[(size_t)v * nx + S.c] = o[v];
-        stage_epilogue<SYS_EULER, NV>(ctrl, P, A.stage, s_step, S.c, o, sm);
-    }
-    if (A.stage == 2) flush_speed(ctrl, A.parity, sm, s_seen);
-}
-
-template <int FLUX, int SCHEME, bool CHAR, bool GB>
-__global__ void __launch_bounds__(WAVE * SPLIT_WAVES)
-sweep1d_split(const double* __restrict__ U, const double* __restrict__ Un, double* __restrict__ out,
-              Ctrl* __restrict__ ctrl, Params P, StageArgs A)
-{
-    strip1d_split<FLUX, SCHEME, CHAR, GB>(U, Un, out, ctrl, P, A, (int)blockIdx.x);
 }
 
 // The table row of block b: the grid r with blk0[r] <= b < blk0[r+1],
@@ -417,25 +246,6 @@ __device__ __forceinline__ StageArgs request_stage(const ReqGrid& R, int stage, 
     A.stage = stage;
     A.parity = (R.parity0 + tick_step) & 1;
     return A;
-}
-
-// One stage of many independent 1D Euler grids in one launch (one strip per
-// block), each with its own parameters, buffers, control block and parity.
-template <int FLUX, int SCHEME, bool CHAR, bool GB>
-__global__ void __launch_bounds__(WAVE)
-sweep1d_multi(const ReqGrid* __restrict__ reqs, const int* __restrict__ map, int nreq, int stage, int tick_step)
-{
-    // the strips of one XCD are one contiguous run of the table's strips
-    const int b = xcd_order((int)blockIdx.x, 0, (int)gridDim.x);
-    ReqGrid R = load_request(reqs, map, nreq, b);
-    // every field the strip geometry and the stencil loads need, loaded in
-    // one round trip before any of them is used
-    asm volatile("" : "+s"(R.U), "+s"(R.U1), "+s"(R.U2), "+s"(R.ctrl), "+s"(R.P.nx), "+s"(R.P.bc_x), "+s"(R.blk0));
-    const StageArgs A = request_stage(R, stage, tick_step);
-    const double* in = stage == 0 ? R.U : (stage == 1 ? R.U1 : R.U2);
-    double* out = stage == 0 ? R.U1 : (stage == 1 ? R.U2 : R.U);
-    sweep1d_block<SYS_EULER, 3, FLUX, SCHEME, CHAR, MODE_STAGE, DIFF_MND, GB>(in, R.U, out, nullptr, R.ctrl, R.P, A,
-                                                                         b - R.blk0);
 }
 
 // ------------------------------------------- persistent batched 1D solves
@@ -1094,6 +904,7 @@ __global__ void __launch_bounds__(256) multi_init(const ReqGrid* __restrict__ re
             ctrl->rec[k].smax_bits = k == 0 ? m : 0ull;
             ctrl->rec[k].step = 0;
         }
+        for (int k = 0; k < 3; ++k) ctrl->speed[k] = k == 0 ? m : 0ull;
         ctrl->bad_key = ~0ull;
         ctrl->call_step0 = 0;
         ctrl->status = 0;
@@ -1110,18 +921,20 @@ __global__ void ctrl_init(Ctrl* ctrl, double t, long long step)
         ctrl->rec[k].smax_bits = 0ull;
         ctrl->rec[k].step = step;
     }
+    for (int k = 0; k < 3; ++k) ctrl->speed[k] = 0ull;
     ctrl->bad_key = ~0ull;
     ctrl->call_step0 = step;
     ctrl->status = 0;
     ctrl->done = 0;
 }
 
-// Opens a solve / step call: clears the done flag and the speed accumulator
-// of the current record and remembers the step counter.
+// Opens a solve / step call: clears the done flag and the speed
+// accumulators of the current record and remembers the step counter.
 __global__ void ctrl_open(Ctrl* ctrl, int parity)
 {
     if (threadIdx.x != 0) return;
     ctrl->rec[parity].smax_bits = 0ull;
+    for (int k = 0; k < 3; ++k) ctrl->speed[k] = 0ull;
     ctrl->done = 0;
     ctrl->call_step0 = ctrl->rec[parity].step;
     // a launch that stopped part of its wavefronts early (a non-physical
@@ -1130,6 +943,10 @@ __global__ void ctrl_open(Ctrl* ctrl, int parity)
     if (seg->on) *seg->ctr = 0u;
 }
 
+// Max CFL speed of a state, one atomic per block: where a 1D line's next
+// step reads it (speed of that step), and for 2D grids into the current
+// record.  8192 atomics of the waves of 2048 blocks on the one address took
+// 98 us on a line of 1e6 cells and 110 us on 2048^2.
 template <int SYS, int NV>
 __global__ void __launch_bounds__(256) wavespeed(const double* __restrict__ U, Ctrl* ctrl, Params P,
                                                   int parity)
@@ -1145,7 +962,13 @@ __global__ void __launch_bounds__(256) wavespeed(const double* __restrict__ U, C
         m = b > m ? b : m;
     }
     m = wave_max_bits(m);
-    if ((threadIdx.x & (WAVE - 1)) == 0) atomicMax(&ctrl->rec[parity].smax_bits, m);
+    __shared__ unsigned long long red[256 / WAVE];
+    if ((threadIdx.x & (WAVE - 1)) == 0) red[threadIdx.x / WAVE] = m;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int i = 1; i < 256 / WAVE; ++i) m = red[i] > m ? red[i] : m;
+    unsigned long long* dst = NV == 4 ? &ctrl->rec[parity].smax_bits : &ctrl->speed[ctrl->rec[parity].step % 3];
+    if (__hip_atomic_load(dst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < m) atomicMax(dst, m);
 }
 
 }  // namespace wcnst
@@ -1189,7 +1012,7 @@ struct wcnst_solver {
     int parity;
     int ty;  // rows per 2D segment
     bool ty_user;  // set by wcnst_set_tuning (else chosen at creation)
-    int split_strips;  // 1D Euler stages over at most this many strips run in the latency mode
+    int home;      // 1D: step parity at which the state is in U (else in U1)
     int slots;     // wavefront slots of the device
     // adaptive first-height segment rows of balanced 2D stage launches (in
     // the workspace; off where the shape does not take them)
@@ -1202,6 +1025,7 @@ struct wcnst_solver {
     bool prof;
     std::vector<hipEvent_t> ev_pool;
     size_t ev_used;
+    int64_t prof_stages;  // stages of the bracketed launches
 };
 
 size_t wcnst_align256(size_t b) { return (b + 255) & ~(size_t)255; }
@@ -1430,13 +1254,14 @@ extern "C" wcnst_status wcnst_create(const wcnst_desc* d, void* hip_stream, void
     s->parity = 0;
     s->slots = wcnst_wave_slots();
     s->ty_user = false;
-    s->split_strips = SPLIT_STRIPS;
     {
         const int strips = (d->nx + TX - 1) / TX, rows = d->ny;
         s->ty = d->ndim == 2 ? wcnst_auto_rows(&strips, &rows, 1, s->slots) : 35;
     }
+    s->home = 0;
     s->prof = false;
     s->ev_used = 0;
+    s->prof_stages = 0;
 
     wcnst_make_params(d, &s->P);
 
@@ -1554,29 +1379,16 @@ static void launch_sweep_t(const wcnst_solver* s, const double* U, const double*
                                s->stream, U, Un, out, flags, s->ctrl, s->P, A, m.ty, m.ty2, m.nseg1, seg_par);
     } else if (s->d.diff == WCNST_MD) {
         constexpr int W = strip_cells<DIFF_MD>();
-        hipLaunchKernelGGL((sweep1d<SYS, NV, FLUX, SCHEME, CHAR, MODE, DIFF_MD>), dim3((s->d.nx + W - 1) / W),
-                           dim3(WAVE), 0, s->stream, U, Un, out, flags, s->ctrl, s->P, A);
+        hipLaunchKernelGGL((sweep1d<SYS, NV, FLUX, SCHEME, CHAR, DIFF_MD>), dim3((s->d.nx + W - 1) / W), dim3(WAVE), 0,
+                           s->stream, U, out, flags, s->P);
     } else if (s->d.diff == WCNST_HWCNS) {
         constexpr int W = strip_cells<DIFF_HW>();
-        hipLaunchKernelGGL((sweep1d<SYS, NV, FLUX, SCHEME, CHAR, MODE, DIFF_HW>), dim3((s->d.nx + W - 1) / W),
-                           dim3(WAVE), 0, s->stream, U, Un, out, flags, s->ctrl, s->P, A);
+        hipLaunchKernelGGL((sweep1d<SYS, NV, FLUX, SCHEME, CHAR, DIFF_HW>), dim3((s->d.nx + W - 1) / W), dim3(WAVE), 0,
+                           s->stream, U, out, flags, s->P);
     } else {
         constexpr int W = strip_cells<DIFF_MND>();
-        const int nstrips = (s->d.nx + W - 1) / W;
-        if constexpr (MODE == MODE_STAGE && SYS == SYS_EULER && NV == 3) {
-            // few strips: the latency mode (three wavefronts per strip)
-            if (nstrips <= s->split_strips) {
-                if (wcnst_general_bc(&s->d))
-                    hipLaunchKernelGGL((sweep1d_split<FLUX, SCHEME, CHAR, true>), dim3(nstrips),
-                                       dim3(WAVE * SPLIT_WAVES), 0, s->stream, U, Un, out, s->ctrl, s->P, A);
-                else
-                    hipLaunchKernelGGL((sweep1d_split<FLUX, SCHEME, CHAR, false>), dim3(nstrips),
-                                       dim3(WAVE * SPLIT_WAVES), 0, s->stream, U, Un, out, s->ctrl, s->P, A);
-                return;
-            }
-        }
-        hipLaunchKernelGGL((sweep1d<SYS, NV, FLUX, SCHEME, CHAR, MODE, DIFF_MND>), dim3(nstrips), dim3(WAVE), 0,
-                           s->stream, U, Un, out, flags, s->ctrl, s->P, A);
+        hipLaunchKernelGGL((sweep1d<SYS, NV, FLUX, SCHEME, CHAR, DIFF_MND>), dim3((s->d.nx + W - 1) / W), dim3(WAVE),
+                           0, s->stream, U, out, flags, s->P);
     }
 }
 
@@ -1603,34 +1415,36 @@ static void launch_char(const wcnst_solver* s, const double* U, const double* Un
     else launch_scheme<SYS, NV, FLUX, false, MODE>(s, U, Un, out, flags, A);
 }
 
+// A right-hand side (any grid) or a stage (2D grids).
 template <int MODE>
 static void launch_sweep(const wcnst_solver* s, const double* U, const double* Un, double* out,
                          uint8_t* flags, const StageArgs& A)
 {
     const bool lf = s->d.flux == WCNST_LF, vl = s->d.flux == WCNST_VANLEER;
-    switch (s->kind) {
-    case K_ADV1: launch_scheme<SYS_ADV, 1, FLUX_ROE, false, MODE>(s, U, Un, out, flags, A); break;
-    case K_BURG1:
-        if (lf) launch_scheme<SYS_BURG, 1, FLUX_LF, false, MODE>(s, U, Un, out, flags, A);
-        else launch_scheme<SYS_BURG, 1, FLUX_ROE, false, MODE>(s, U, Un, out, flags, A);
-        break;
-    case K_EUL1:
-        if (lf) launch_char<SYS_EULER, 3, FLUX_LF, MODE>(s, U, Un, out, flags, A);
-        else if (vl) launch_char<SYS_EULER, 3, FLUX_VL, MODE>(s, U, Un, out, flags, A);
-        else launch_char<SYS_EULER, 3, FLUX_ROE, MODE>(s, U, Un, out, flags, A);
-        break;
-    case K_EUL2:
+    if (s->kind == K_EUL2) {
         if (lf) launch_char<SYS_EULER, 4, FLUX_LF, MODE>(s, U, Un, out, flags, A);
         else if (vl) launch_char<SYS_EULER, 4, FLUX_VL, MODE>(s, U, Un, out, flags, A);
         else launch_char<SYS_EULER, 4, FLUX_ROE, MODE>(s, U, Un, out, flags, A);
-        break;
+        return;
+    }
+    if constexpr (MODE == MODE_RHS) {
+        if (s->kind == K_ADV1) {
+            launch_scheme<SYS_ADV, 1, FLUX_ROE, false, MODE>(s, U, Un, out, flags, A);
+        } else if (s->kind == K_BURG1) {
+            if (lf) launch_scheme<SYS_BURG, 1, FLUX_LF, false, MODE>(s, U, Un, out, flags, A);
+            else launch_scheme<SYS_BURG, 1, FLUX_ROE, false, MODE>(s, U, Un, out, flags, A);
+        } else {
+            if (lf) launch_char<SYS_EULER, 3, FLUX_LF, MODE>(s, U, Un, out, flags, A);
+            else if (vl) launch_char<SYS_EULER, 3, FLUX_VL, MODE>(s, U, Un, out, flags, A);
+            else launch_char<SYS_EULER, 3, FLUX_ROE, MODE>(s, U, Un, out, flags, A);
+        }
     }
 }
 
 static void launch_wavespeed(const wcnst_solver* s, const double* U)
 {
     const size_t cells = (size_t)s->d.nx * s->d.ny;
-    int blocks = (int)std::min<size_t>((cells + 255) / 256, 2048);
+    int blocks = (int)std::min<size_t>((cells + 255) / 256, 1024);
     switch (s->kind) {
     case K_ADV1: hipLaunchKernelGGL((wavespeed<SYS_ADV, 1>), dim3(blocks), dim3(256), 0, s->stream, U, s->ctrl, s->P, s->parity); break;
     case K_BURG1: hipLaunchKernelGGL((wavespeed<SYS_BURG, 1>), dim3(blocks), dim3(256), 0, s->stream, U, s->ctrl, s->P, s->parity); break;
@@ -1649,9 +1463,39 @@ static hipEvent_t pool_event(wcnst_solver* s)
     return s->ev_pool[s->ev_used++];
 }
 
-// One SSP-RK3 step: three fused stage kernels.
+// Opens / closes a profiled launch (events on the solver's stream).
+static hipEvent_t prof_begin(wcnst_solver* s, hipEvent_t* end)
+{
+    *end = nullptr;
+    if (!s->prof) return nullptr;
+    hipEvent_t e0 = pool_event(s);
+    *end = pool_event(s);
+    if (e0) (void)hipEventRecord(e0, s->stream);
+    return e0;
+}
+
+static void prof_end(wcnst_solver* s, hipEvent_t end, int stages)
+{
+    if (!s->prof || !end) return;
+    (void)hipEventRecord(end, s->stream);
+    s->prof_stages += stages;
+}
+
+// One SSP-RK3 step: one launch on a 1D line (the state is in U when the
+// step parity is the home parity, else in U1), three fused stage kernels in
+// 2D.
 static void launch_step(wcnst_solver* s, double* U, double t_final, double cfl, double fixed_dt)
 {
+    hipEvent_t end;
+    if (s->kind != K_EUL2) {
+        const bool at_home = s->parity == s->home;
+        const LineStep A{t_final, cfl, fixed_dt, s->parity};
+        (void)prof_begin(s, &end);
+        (void)wcnst_launch_line_step(&s->d, s->P, s->ctrl, at_home ? U : s->U1, at_home ? s->U1 : U, A, s->stream);
+        prof_end(s, end, 3);
+        s->parity ^= 1;
+        return;
+    }
     const double* in[3] = {U, s->U1, s->U2};
     double* outp[3] = {s->U1, s->U2, U};
     for (int st = 0; st < 3; ++st) {
@@ -1661,16 +1505,78 @@ static void launch_step(wcnst_solver* s, double* U, double t_final, double cfl, 
         A.fixed_dt = fixed_dt;
         A.stage = st;
         A.parity = s->parity;
-        hipEvent_t e0 = nullptr, e1 = nullptr;
-        if (s->prof) {
-            e0 = pool_event(s);
-            e1 = pool_event(s);
-            if (e0) (void)hipEventRecord(e0, s->stream);
-        }
+        (void)prof_begin(s, &end);
         launch_sweep<MODE_STAGE>(s, in[st], U, outp[st], nullptr, A);
-        if (s->prof && e1) (void)hipEventRecord(e1, s->stream);
+        prof_end(s, end, 1);
     }
     s->parity ^= 1;
+}
+
+static wcnst_status read_ctrl(wcnst_solver* s, Ctrl* c)
+{
+    HIP_TRY(hipMemcpyAsync(c, s->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s->stream));
+    HIP_TRY(hipStreamSynchronize(s->stream));
+    return WCNST_OK;
+}
+
+// The record holding the newest completed state.
+static const StepRec& newest(const Ctrl& c)
+{
+    return c.rec[0].step >= c.rec[1].step ? c.rec[0] : c.rec[1];
+}
+
+// Steps of a short line in one launch of one workgroup.
+constexpr int SOLO_STEPS = 2048;
+
+// Runs the short line of a solver up to t_final or for max_steps steps,
+// opening the call, in launches of at most SOLO_STEPS steps; a timed run is
+// looked at after each.  *c receives the control block at the end.
+static wcnst_status solve_short_line(wcnst_solver* s, double* U, double t_final, double cfl, int64_t max_steps, Ctrl* c)
+{
+    int64_t launched = 0;
+    bool open = true;
+    do {
+        const int k = (int)std::min<int64_t>(SOLO_STEPS, max_steps - launched);
+        const LineStep A{t_final, cfl, 0.0, s->parity};
+        hipEvent_t end;
+        (void)prof_begin(s, &end);
+        HIP_TRY(wcnst_launch_line_solo(&s->d, s->P, s->ctrl, U, A, k, open, s->stream));
+        prof_end(s, end, 3 * k);
+        open = false;
+        launched += k;
+        if (!std::isfinite(t_final) && launched < max_steps) {
+            s->parity ^= k & 1;
+            continue;
+        }
+        const wcnst_status st = read_ctrl(s, c);
+        if (st) return st;
+        s->parity = &newest(*c) == &c->rec[0] ? 0 : 1;
+        if (c->status != 0 || c->done) break;
+    } while (launched < max_steps);
+    return WCNST_OK;
+}
+
+// Outcome of a solve from its control block.
+static wcnst_status solve_outcome(const Ctrl& c, double t_final, int64_t max_steps, double* t_out, int64_t* steps_out)
+{
+    const StepRec& r = newest(c);
+    if (t_out) *t_out = r.t;
+    if (steps_out) *steps_out = r.step - c.call_step0;
+    if (c.status != 0) {
+        const long long stg = c.bad_key == ~0ull ? -1 : (long long)(c.bad_key >> 36);
+        const long long cell = c.bad_key == ~0ull ? -1 : (long long)(c.bad_key & ((1ull << 36) - 1));
+        return fail(WCNST_E_NONPHYSICAL, "non-physical state at global stage %lld, cell %lld", stg, cell);
+    }
+    if (std::isfinite(t_final) && !(t_final - r.t <= 1e-12 * t_final))
+        return fail(WCNST_E_MAX_STEPS, "t_final not reached in %lld steps (t = %.17g)", (long long)max_steps, r.t);
+    return WCNST_OK;
+}
+
+// After a run of steps: a 1D line's newest state into U.
+static hipError_t launch_settle(wcnst_solver* s, double* U)
+{
+    if (s->kind == K_EUL2) return hipSuccess;
+    return wcnst_launch_line_settle(s->ctrl, U, s->U1, (long long)s->nv * s->d.nx, s->home, s->stream);
 }
 
 extern "C" wcnst_status wcnst_rhs(wcnst_solver* s, const double* U, double* R, uint8_t* flags)
@@ -1687,24 +1593,22 @@ extern "C" wcnst_status wcnst_step(wcnst_solver* s, double* U, double dt, double
 {
     if (!s || !U) return fail(WCNST_E_INVALID_ARG, "null argument");
     if (!(dt > 0.0) && !(cfl > 0.0)) return fail(WCNST_E_INVALID_ARG, "need dt > 0 or cfl > 0");
+    if (wcnst_line_solo(&s->d)) {
+        const LineStep A{INFINITY, cfl, dt > 0.0 ? dt : 0.0, s->parity};
+        hipEvent_t end;
+        (void)prof_begin(s, &end);
+        HIP_TRY(wcnst_launch_line_solo(&s->d, s->P, s->ctrl, U, A, 1, true, s->stream));
+        prof_end(s, end, 3);
+        s->parity ^= 1;
+        return WCNST_OK;
+    }
     hipLaunchKernelGGL(ctrl_open, dim3(1), dim3(64), 0, s->stream, s->ctrl, s->parity);
     if (!(dt > 0.0)) launch_wavespeed(s, U);
+    s->home = s->parity;
     launch_step(s, U, INFINITY, cfl, dt > 0.0 ? dt : 0.0);
+    HIP_TRY(launch_settle(s, U));
     HIP_TRY(hipGetLastError());
     return WCNST_OK;
-}
-
-static wcnst_status read_ctrl(wcnst_solver* s, Ctrl* c)
-{
-    HIP_TRY(hipMemcpyAsync(c, s->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s->stream));
-    HIP_TRY(hipStreamSynchronize(s->stream));
-    return WCNST_OK;
-}
-
-// The record holding the newest completed state.
-static const StepRec& newest(const Ctrl& c)
-{
-    return c.rec[0].step >= c.rec[1].step ? c.rec[0] : c.rec[1];
 }
 
 extern "C" wcnst_status wcnst_solve(wcnst_solver* s, double* U, double t_final, double cfl,
@@ -1715,10 +1619,16 @@ extern "C" wcnst_status wcnst_solve(wcnst_solver* s, double* U, double t_final, 
     if (max_steps < 0) return fail(WCNST_E_INVALID_ARG, "max_steps must be >= 0");
     if (std::isnan(t_final)) return fail(WCNST_E_INVALID_ARG, "t_final is NaN");
     const bool timed = std::isfinite(t_final);
+    if (wcnst_line_solo(&s->d) && max_steps > 0) {
+        Ctrl c;
+        const wcnst_status st = solve_short_line(s, U, t_final, cfl, max_steps, &c);
+        return st ? st : solve_outcome(c, t_final, max_steps, t_out, steps_out);
+    }
 
     hipLaunchKernelGGL(ctrl_open, dim3(1), dim3(64), 0, s->stream, s->ctrl, s->parity);
     launch_wavespeed(s, U);
     HIP_TRY(hipGetLastError());
+    s->home = s->parity;
 
     int64_t launched = 0;
     int64_t chunk = 4;
@@ -1744,7 +1654,7 @@ extern "C" wcnst_status wcnst_solve(wcnst_solver* s, double* U, double t_final, 
         HIP_TRY(hipEventSynchronize(s->snap_ev[prev]));
         const Ctrl& c = *s->host_ctrl[prev];
         const StepRec& r = newest(c);
-        if (c.status != 0 || c.done) break;
+        if (c.status != 0 || c.bad_key != ~0ull || c.done) break;
         // estimate the steps still needed beyond what is already queued
         const int64_t done_steps = r.step - c.call_step0;
         const double dt = c.rec[0].step >= c.rec[1].step ? c.rec[1].dt : c.rec[0].dt;
@@ -1755,21 +1665,12 @@ extern "C" wcnst_status wcnst_solve(wcnst_solver* s, double* U, double t_final, 
         prev_launched = launched;
         chunk = std::max<int64_t>(1, std::min<int64_t>(est - queued, 512));
     }
+    HIP_TRY(launch_settle(s, U));
     Ctrl c;
     wcnst_status st = read_ctrl(s, &c);
     if (st) return st;
-    const StepRec& r = newest(c);
-    if (t_out) *t_out = r.t;
-    if (steps_out) *steps_out = r.step - c.call_step0;
-    if (c.status != 0) {
-        const long long stg = c.bad_key == ~0ull ? -1 : (long long)(c.bad_key >> 36);
-        const long long cell = c.bad_key == ~0ull ? -1 : (long long)(c.bad_key & ((1ull << 36) - 1));
-        return fail(WCNST_E_NONPHYSICAL, "non-physical state at global stage %lld, cell %lld", stg, cell);
-    }
-    if (timed && !(t_final - r.t <= 1e-12 * t_final))
-        return fail(WCNST_E_MAX_STEPS, "t_final not reached in %lld steps (t = %.17g)",
-                    (long long)max_steps, r.t);
-    return WCNST_OK;
+    if (s->kind != K_EUL2) s->parity = &newest(c) == &c.rec[0] ? 0 : 1;
+    return solve_outcome(c, t_final, max_steps, t_out, steps_out);
 }
 
 // ------------------------------------------------ allocation-free solve
@@ -1844,17 +1745,20 @@ extern "C" wcnst_status wcnst_solve_noalloc(const wcnst_desc* d, void* hip_strea
         const int strips = (d->nx + TX - 1) / TX, rows = d->ny;
         s.ty = d->ndim == 2 ? wcnst_auto_rows(&strips, &rows, 1, s.slots) : 35;
     }
-    s.split_strips = SPLIT_STRIPS;
     wcnst_make_params(d, &s.P);
     const bool timed = std::isfinite(t_final);
 
     // a fresh solve from t = 0: the control block is reset by a kernel
     hipLaunchKernelGGL(ctrl_init, dim3(1), dim3(64), 0, s.stream, s.ctrl, 0.0, 0LL);
+    Ctrl c;
+    if (wcnst_line_solo(d) && max_steps > 0) {
+        st = solve_short_line(&s, U, t_final, cfl, max_steps, &c);
+        return st ? st : solve_outcome(c, t_final, max_steps, t_out, steps_out);
+    }
     hipLaunchKernelGGL(ctrl_open, dim3(1), dim3(64), 0, s.stream, s.ctrl, s.parity);
     launch_wavespeed(&s, U);
     HIP_TRY(hipGetLastError());
     int64_t launched = 0, chunk = 4;
-    Ctrl c;
     while (launched < max_steps) {
         const int64_t k = std::min(chunk, max_steps - launched);
         for (int64_t i = 0; i < k; ++i) launch_step(&s, U, t_final, cfl, 0.0);
@@ -1863,26 +1767,17 @@ extern "C" wcnst_status wcnst_solve_noalloc(const wcnst_desc* d, void* hip_strea
         if (!timed) continue;
         st = read_ctrl(&s, &c);
         if (st) return st;
-        if (c.status != 0 || c.done) break;
+        if (c.status != 0 || c.bad_key != ~0ull || c.done) break;
         const StepRec& r = newest(c);
         const double dt = c.rec[0].step >= c.rec[1].step ? c.rec[1].dt : c.rec[0].dt;
         int64_t est = 8;
         if (dt > 0.0 && std::isfinite(dt)) est = (int64_t)std::ceil((t_final - r.t) / dt) + 1;
         chunk = std::max<int64_t>(1, std::min<int64_t>(est, 512));
     }
+    HIP_TRY(launch_settle(&s, U));
     st = read_ctrl(&s, &c);
     if (st) return st;
-    const StepRec& r = newest(c);
-    if (t_out) *t_out = r.t;
-    if (steps_out) *steps_out = r.step;
-    if (c.status != 0) {
-        const long long stg = c.bad_key == ~0ull ? -1 : (long long)(c.bad_key >> 36);
-        const long long cell = c.bad_key == ~0ull ? -1 : (long long)(c.bad_key & ((1ull << 36) - 1));
-        return fail(WCNST_E_NONPHYSICAL, "non-physical state at global stage %lld, cell %lld", stg, cell);
-    }
-    if (timed && !(t_final - r.t <= 1e-12 * t_final))
-        return fail(WCNST_E_MAX_STEPS, "t_final not reached in %lld steps (t = %.17g)", (long long)max_steps, r.t);
-    return WCNST_OK;
+    return solve_outcome(c, t_final, max_steps, t_out, steps_out);
 }
 
 extern "C" wcnst_status wcnst_status_sync(wcnst_solver* s, double* t, int64_t* steps, int32_t* status,
@@ -2002,6 +1897,7 @@ extern "C" wcnst_status wcnst_profile_enable(wcnst_solver* s, int enable)
     HIP_TRY(hipStreamSynchronize(s->stream));
     s->prof = enable != 0;
     s->ev_used = 0;
+    s->prof_stages = 0;
     return WCNST_OK;
 }
 
@@ -2016,8 +1912,9 @@ extern "C" wcnst_status wcnst_profile_read(wcnst_solver* s, double* stage_ms, in
         total += ms;
     }
     if (stage_ms) *stage_ms = total;
-    if (stage_launches) *stage_launches = (int64_t)(s->ev_used / 2);
+    if (stage_launches) *stage_launches = s->prof_stages;
     s->ev_used = 0;
+    s->prof_stages = 0;
     return WCNST_OK;
 }
 
@@ -2049,71 +1946,57 @@ hipError_t wcnst_launch_multi_init(int ndim, const void* reqs, int nreq, hipStre
     return hipGetLastError();
 }
 
-template <int NDIM, int FLUX, int SCHEME, bool CHAR>
+template <int FLUX, int SCHEME, bool CHAR>
 static void launch_multi_t(const ReqGrid* reqs, const int* map, int nreq, int nblocks, int stage, int tick_step,
                            int ty, bool general, hipStream_t st)
 {
-    if constexpr (NDIM == 2) {
-        if (general)
-            hipLaunchKernelGGL((sweep2d_multi<4, FLUX, SCHEME, CHAR, true>), dim3(nblocks), dim3(WAVE), 0, st, reqs,
-                               map, nreq, stage, tick_step, ty);
-        else
-            hipLaunchKernelGGL((sweep2d_multi<4, FLUX, SCHEME, CHAR, false>), dim3(nblocks), dim3(WAVE), 0, st, reqs,
-                               map, nreq, stage, tick_step, ty);
-    } else if (general) {
-        hipLaunchKernelGGL((sweep1d_multi<FLUX, SCHEME, CHAR, true>), dim3(nblocks), dim3(WAVE), 0, st, reqs, map,
-                           nreq, stage, tick_step);
-    } else {
-        hipLaunchKernelGGL((sweep1d_multi<FLUX, SCHEME, CHAR, false>), dim3(nblocks), dim3(WAVE), 0, st, reqs, map,
-                           nreq, stage, tick_step);
-    }
+    if (general)
+        hipLaunchKernelGGL((sweep2d_multi<4, FLUX, SCHEME, CHAR, true>), dim3(nblocks), dim3(WAVE), 0, st, reqs, map,
+                           nreq, stage, tick_step, ty);
+    else
+        hipLaunchKernelGGL((sweep2d_multi<4, FLUX, SCHEME, CHAR, false>), dim3(nblocks), dim3(WAVE), 0, st, reqs, map,
+                           nreq, stage, tick_step, ty);
 }
 
-template <int NDIM, int FLUX, bool CHAR>
+template <int FLUX, bool CHAR>
 static void launch_multi_s(const wcnst_desc* d, const ReqGrid* reqs, const int* map, int nreq, int nblocks, int stage,
                            int tick_step, int ty, bool general, hipStream_t st)
 {
     switch (d->scheme) {
     case WCNST_LINEAR:
-        launch_multi_t<NDIM, FLUX, SCH_LINEAR, CHAR>(reqs, map, nreq, nblocks, stage, tick_step, ty, general, st);
+        launch_multi_t<FLUX, SCH_LINEAR, CHAR>(reqs, map, nreq, nblocks, stage, tick_step, ty, general, st);
         break;
     case WCNST_JS:
-        launch_multi_t<NDIM, FLUX, SCH_JS, CHAR>(reqs, map, nreq, nblocks, stage, tick_step, ty, general, st);
+        launch_multi_t<FLUX, SCH_JS, CHAR>(reqs, map, nreq, nblocks, stage, tick_step, ty, general, st);
         break;
     case WCNST_Z:
-        launch_multi_t<NDIM, FLUX, SCH_Z, CHAR>(reqs, map, nreq, nblocks, stage, tick_step, ty, general, st);
+        launch_multi_t<FLUX, SCH_Z, CHAR>(reqs, map, nreq, nblocks, stage, tick_step, ty, general, st);
         break;
     default:
         if (d->q == 6)
-            launch_multi_t<NDIM, FLUX, SCH_TENO, CHAR>(reqs, map, nreq, nblocks, stage, tick_step, ty, general, st);
+            launch_multi_t<FLUX, SCH_TENO, CHAR>(reqs, map, nreq, nblocks, stage, tick_step, ty, general, st);
         else
-            launch_multi_t<NDIM, FLUX, SCH_TENO_Q, CHAR>(reqs, map, nreq, nblocks, stage, tick_step, ty, general, st);
+            launch_multi_t<FLUX, SCH_TENO_Q, CHAR>(reqs, map, nreq, nblocks, stage, tick_step, ty, general, st);
         break;
     }
 }
 
-template <int NDIM>
-static void launch_multi_d(const wcnst_desc* d, const ReqGrid* r, const int* map, int nreq, int nblocks, int stage,
+template <int FLUX>
+static void launch_multi_f(const wcnst_desc* d, const ReqGrid* r, const int* map, int nreq, int nblocks, int stage,
                            int tick_step, int ty, bool general, hipStream_t st)
 {
-    if (d->flux == WCNST_LF) {
-        if (d->charwise) launch_multi_s<NDIM, FLUX_LF, true>(d, r, map, nreq, nblocks, stage, tick_step, ty, general, st);
-        else launch_multi_s<NDIM, FLUX_LF, false>(d, r, map, nreq, nblocks, stage, tick_step, ty, general, st);
-    } else if (d->flux == WCNST_VANLEER) {
-        if (d->charwise) launch_multi_s<NDIM, FLUX_VL, true>(d, r, map, nreq, nblocks, stage, tick_step, ty, general, st);
-        else launch_multi_s<NDIM, FLUX_VL, false>(d, r, map, nreq, nblocks, stage, tick_step, ty, general, st);
-    } else {
-        if (d->charwise) launch_multi_s<NDIM, FLUX_ROE, true>(d, r, map, nreq, nblocks, stage, tick_step, ty, general, st);
-        else launch_multi_s<NDIM, FLUX_ROE, false>(d, r, map, nreq, nblocks, stage, tick_step, ty, general, st);
-    }
+    if (d->charwise) launch_multi_s<FLUX, true>(d, r, map, nreq, nblocks, stage, tick_step, ty, general, st);
+    else launch_multi_s<FLUX, false>(d, r, map, nreq, nblocks, stage, tick_step, ty, general, st);
 }
 
-hipError_t wcnst_launch_multi(const wcnst_desc* d, int ndim, const void* reqs, const int* map, int nreq, int nblocks,
-                              int stage, int tick_step, int ty, bool general, hipStream_t st)
+hipError_t wcnst_launch_multi(const wcnst_desc* d, const void* reqs, const int* map, int nreq, int nblocks, int stage,
+                              int tick_step, int ty, bool general, hipStream_t st)
 {
     const ReqGrid* r = (const ReqGrid*)reqs;
-    if (ndim == 2) launch_multi_d<2>(d, r, map, nreq, nblocks, stage, tick_step, ty, general, st);
-    else launch_multi_d<1>(d, r, map, nreq, nblocks, stage, tick_step, ty, general, st);
+    if (d->flux == WCNST_LF) launch_multi_f<FLUX_LF>(d, r, map, nreq, nblocks, stage, tick_step, ty, general, st);
+    else if (d->flux == WCNST_VANLEER)
+        launch_multi_f<FLUX_VL>(d, r, map, nreq, nblocks, stage, tick_step, ty, general, st);
+    else launch_multi_f<FLUX_ROE>(d, r, map, nreq, nblocks, stage, tick_step, ty, general, st);
     return hipGetLastError();
 }
 

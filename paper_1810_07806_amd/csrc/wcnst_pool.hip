@@ -41,7 +41,7 @@ struct PoolReq {
     double* U1 = nullptr;
     double* U2 = nullptr;
     double t_final = 0.0, cfl = 0.0;
-    int parity = 0;  // step parity of the current record
+    int parity = 0;  // step parity of the current record (1D: at which the state is in U)
     int status = 0;
     double t = 0.0;
     long long steps = 0;
@@ -226,9 +226,9 @@ static wcnst_status issue_dim(wcnst_pool* p, int ndim, const std::vector<int>& a
         wcnst_make_params(&r.d, &q.P);
         q.t_final = r.t_final;
         q.cfl = r.cfl;
-        q.nstrips = (r.d.nx + TX - 1) / TX;
+        q.nstrips = ndim == 2 ? (r.d.nx + TX - 1) / TX : wcnst_line_tiles(r.d.diff, r.d.nx);
         q.blk0 = blocks;
-        q.parity0 = r.parity;
+        q.parity0 = q.home = r.parity;
         blocks += q.nstrips * (ndim == 2 ? (r.d.ny + ty - 1) / ty : 1);
         r.parity = (int)((r.parity + steps) & 1);
     }
@@ -240,10 +240,16 @@ static wcnst_status issue_dim(wcnst_pool* p, int ndim, const std::vector<int>& a
         WCNST_HIP_TRY(wcnst_launch_block_map(p->d_req[ndim - 1], n, blocks, p->d_map[ndim - 1], st));
         map = p->d_map[ndim - 1];
     }
+    if (ndim == 1) {
+        for (int64_t s = 0; s < steps; ++s)
+            WCNST_HIP_TRY(wcnst_launch_line_multi(&p->scheme, p->d_req[0], map, n, blocks, (int)(s & 1), st));
+        WCNST_HIP_TRY(wcnst_launch_line_settle_multi(p->d_req[0], n, st));
+        return WCNST_OK;
+    }
     for (int64_t s = 0; s < steps; ++s)
         for (int stage = 0; stage < 3; ++stage)
-            WCNST_HIP_TRY(wcnst_launch_multi(&p->scheme, ndim, p->d_req[ndim - 1], map, n, blocks, stage, (int)(s & 1),
-                                             ty, general, st));
+            WCNST_HIP_TRY(wcnst_launch_multi(&p->scheme, p->d_req[1], map, n, blocks, stage, (int)(s & 1), ty, general,
+                                             st));
     return WCNST_OK;
 }
 
@@ -287,6 +293,7 @@ extern "C" wcnst_status wcnst_pool_tick_split(wcnst_pool* p, int64_t steps_1d, i
             r.steps = n.step;
             r.status = c.status;
             r.bad_key = c.bad_key;
+            if (r.d.ndim == 1) r.parity = &n == &c.rec[0] ? 0 : 1;
             r.finished = r.status != 0 || reached(r.t_final, r.t);
         }
     return WCNST_OK;
