@@ -183,22 +183,24 @@ wcnst_status wcnst_status_sync(wcnst_solver* s, double* t, int64_t* steps, int32
 /* Reset the device time, step counter and sticky status (asynchronous). */
 wcnst_status wcnst_reset(wcnst_solver* s, double t, int64_t steps);
 
-/* Launch shape of the 2D stage kernel: one 64-lane wavefront per strip of
- * 61 columns marches up a segment of rows_per_segment rows (>= 1).  The
- * default, chosen at wcnst_create from the grid and the device's CU count,
- * is in [2, 35]: 35 rows for grids that fill the device, shorter segments
- * (more wavefronts) for smaller ones; 0 restores it.  Changes only the work
- * decomposition, never the results.  Negative values: WCNST_E_INVALID_ARG. */
+/* Launch shape of the 2D stage kernel: strips of 61 columns, each cut into
+ * segments of rows_per_segment rows (>= 1); a workgroup of four wavefronts
+ * advances a segment four rows at a time.  The default, chosen at
+ * wcnst_create from the grid and the device's CU count, is a multiple of
+ * four in [4, 64]: as tall as keeps every CU at work.  0 restores it.
+ * Changes only the work decomposition, never the results.  Negative values:
+ * WCNST_E_INVALID_ARG. */
 wcnst_status wcnst_set_tuning(wcnst_solver* s, int32_t rows_per_segment);
 
 /* Launch shape of the stage kernels (wcnst_step / wcnst_solve).  2D: strips
  * of 61 columns; segments 0 .. nseg1-1 of each strip hold rows1 rows, the
  * later ones (to nseg in all, the last one ragged) rows2.  Two heights are
- * used only without an explicit tuning, for a launch of one round with two
- * wavefronts on most SIMDs: a SIMD issues from its oldest wavefront first,
- * and the first-dispatched segments get more rows so that both wavefronts
- * finish together.  1D: strips only (rows and segments 1).  Right-hand-side
- * launches use one height. */
+ * used only without an explicit tuning, for grids of 1.5 to 2 segments of 35
+ * rows per SIMD; the first-height segments are then worked by two workgroups
+ * each (half the rows each), the others by one, and their rows adapt
+ * (wcnst_stage_layout).  1D: strips of a right-hand side only (rows and
+ * segments 1; a step is one launch).  Right-hand-side launches use one
+ * height. */
 wcnst_status wcnst_stage_shape(const wcnst_solver* s, int32_t* strips, int32_t* rows1, int32_t* rows2,
                                int32_t* nseg1, int32_t* nseg);
 
@@ -206,7 +208,7 @@ wcnst_status wcnst_stage_shape(const wcnst_solver* s, int32_t* strips, int32_t* 
  * Those segments do not keep rows1 rows each: every launch records how long
  * each took, and the launch after next moves rows from the segments that
  * took longer (where the stencil-cut test of Sec. 2.3 runs in full, near
- * discontinuities) to the others, so that all wavefronts finish about
+ * discontinuities) to the others, so that all workgroups finish about
  * together; the first nseg1 * rows1 rows of a strip stay theirs.  Only the
  * decomposition changes, never the results.  On return *count is strips *
  * (nseg1 + 1), the boundaries [strip][0 .. nseg1] (row 0 up to nseg1 *
@@ -215,10 +217,11 @@ wcnst_status wcnst_stage_shape(const wcnst_solver* s, int32_t* strips, int32_t* 
  * when cap >= *count, after the solver's stream has drained. */
 wcnst_status wcnst_stage_layout(wcnst_solver* s, int32_t* rows, int32_t cap, int32_t* count);
 
-/* Kernel timing for roofline reports: when enabled, every stage kernel is
- * bracketed by HIP events on the solver's stream.  wcnst_profile_read
- * synchronises and returns the summed stage-kernel milliseconds and the
- * number of stage-kernel launches since the last reset. */
+/* Kernel timing for roofline reports: when enabled, every stage kernel (in
+ * 1D, every launch of one or more whole steps) is bracketed by HIP events on
+ * the solver's stream.  wcnst_profile_read synchronises and returns the
+ * summed milliseconds and the number of Runge-Kutta stages launched since
+ * the last reset. */
 wcnst_status wcnst_profile_enable(wcnst_solver* s, int enable);
 wcnst_status wcnst_profile_read(wcnst_solver* s, double* stage_ms, int64_t* stage_launches);
 
@@ -227,9 +230,9 @@ wcnst_status wcnst_destroy(wcnst_solver* s);
 
 /* ---------------------------------------------------------------- batches
  * Many independent 1D Euler problems of uneven length advanced together in
- * ticks: a tick is a chunk of SSP-RK3 steps, each stage one launch covering
- * the strips of every instance still running (own control block, dt and
- * step parity per instance), captured in a HIP graph and replayed while the
+ * ticks: a tick is a chunk of SSP-RK3 steps, each one launch covering the
+ * tiles of every instance still running (own control block, dt and step
+ * parity per instance), captured in a HIP graph and replayed while the
  * set of running instances is unchanged; between ticks finished instances
  * drop out of the launch table.  Every instance follows exactly the
  * arithmetic of wcnst_solve (Sec. 2-3 as above), so it gives the same bits
@@ -299,9 +302,9 @@ wcnst_status wcnst_batch_destroy(wcnst_batch* b);
  * that requests join and leave between ticks (continuous batching).  Each
  * request follows exactly the arithmetic of wcnst_solve (Sec. 2-3, SSP-RK3
  * with the CFL rule and final-step clipping), so its result is the same
- * bits alone or in any mix.  A tick issues, per dimension, one stage
- * launch per Runge-Kutta stage covering all active grids of that dimension
- * (each with its own control block and dt); no wave waits for another.
+ * bits alone or in any mix.  A tick issues one launch per step over all
+ * active 1D lines and one per Runge-Kutta stage over all active 2D grids
+ * (each with its own control block and dt); no workgroup waits for another.
  * The library allocates no device memory: the
  * pool's tables live in a caller workspace and every request brings its own
  * three state buffers.

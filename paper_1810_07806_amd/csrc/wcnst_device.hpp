@@ -20,9 +20,9 @@
 // the Roe dissipation R |Lambda| L (U_R - U_L) use explicit fused
 // multiply-adds, written at the same places in the oracle: one rounding
 // per a * x + y, and fewer instructions.  (The
-// reciprocals and roots of the Roe averages (the projection's; in 1D also
-// the flux's, with the physical fluxes) use the hardware's correctly rounded
-// sequences without their range scaling, which give the IEEE results bit
+// reciprocals and roots of the Roe averages and the node quantities use the
+// hardware's correctly rounded sequences without their range scaling, which
+// give the IEEE results bit
 // for bit over the argument range they are used in; lanes whose arguments
 // leave it redo that work with the IEEE operations.)
 // Only the cut-off test itself, which is decided far from its threshold
@@ -296,6 +296,17 @@ WCNST_HD bool any_lane(bool rare)
     return __builtin_expect(__builtin_amdgcn_ballot_w64(rare) != 0ull, 0);
 #else
     return rare;
+#endif
+}
+
+// Has the compiler form a value here rather than where it is used (it would
+// carry the operands instead).
+WCNST_HD void keep_here(double& x)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+v"(x));
+#else
+    (void)x;
 #endif
 }
 
@@ -733,12 +744,12 @@ WCNST_HD void node_quantities(const double* U, double gamma, Node<NV>& N)
     }
 }
 
-// Roe average of two nodes and its eigen-system.  With RANGED it is exact
-// (equal to the IEEE one) where the return value is true: sqrt(rho_A) +
-// sqrt(rho_B) and c^2 lie in [2^-767, 2^1022), and with them every argument
-// of a reciprocal or root here.
+// Roe average of two nodes and its eigen-system; returns c^2.  With RANGED it
+// is exact (equal to the IEEE one) where sqrt(rho_A) + sqrt(rho_B) and c^2
+// lie in [2^-767, 2^1022), and with them every argument of a reciprocal or
+// root here.
 template <int NV, bool RANGED>
-WCNST_HD bool roe_average(const Node<NV>& A, const Node<NV>& B, double gamma, Eigen<NV>& E)
+WCNST_HD double roe_average_c2(const Node<NV>& A, const Node<NV>& B, double gamma, Eigen<NV>& E)
 {
     const double ss = A.s + B.s;
     const double is = recip<RANGED>(ss);
@@ -755,15 +766,16 @@ WCNST_HD bool roe_average(const Node<NV>& A, const Node<NV>& B, double gamma, Ei
     E.b1 = (gamma - 1.0) * (E.ic * E.ic);
     E.b2 = 0.5 * E.q2 * E.b1;
     E.uc = E.u * E.ic;
-    return !RANGED || (in_ieee_range(ss) && in_ieee_range(c2));
+    return c2;
 }
 
 template <int NV>
 WCNST_HD void roe_average(const Node<NV>& A, const Node<NV>& B, double gamma, Eigen<NV>& E)
 {
-    const bool ok = roe_average<NV, true>(A, B, gamma, E);
+    const double c2 = roe_average_c2<NV, true>(A, B, gamma, E);
+    const bool ok = in_ieee_range(A.s + B.s) && in_ieee_range(c2);
     if (any_lane(!ok)) {
-        if (!ok) roe_average<NV, false>(A, B, gamma, E);
+        if (!ok) (void)roe_average_c2<NV, false>(A, B, gamma, E);
     }
 }
 
@@ -775,8 +787,9 @@ WCNST_HD bool roe_eigen(const double* A, const double* B, double gamma, Eigen<NV
     Node<NV> NA, NB;
     node_quantities<NV, RANGED>(A, gamma, NA);
     node_quantities<NV, RANGED>(B, gamma, NB);
-    const bool ok = roe_average<NV, RANGED>(NA, NB, gamma, E);
-    return !RANGED || (ok && in_ieee_range(A[0]) && in_ieee_range(B[0]));
+    const double c2 = roe_average_c2<NV, RANGED>(NA, NB, gamma, E);
+    // (with the densities the sum of their roots is in that range)
+    return !RANGED || (in_ieee_range(A[0]) && in_ieee_range(B[0]) && in_ieee_range(c2));
 }
 
 // van Leer's split normal flux (the flux named for the results of Sec. 3;
@@ -829,12 +842,10 @@ WCNST_HD void euler_num_flux(const double* UL, const double* UR, double gamma, d
         for (int v = 0; v < NV; ++v) F[v] = Fp[v] + Fm[v];
         return;
     }
-    // 1D Roe: the physical fluxes and the Roe average with the ranged
+    // Roe: the physical fluxes and the Roe average with the ranged
     // reciprocals and roots (1/rho of U_L and U_R shared by both), redone
     // with the IEEE operations on lanes whose arguments leave their range.
-    // The 2D kernels keep the IEEE operations here: at their register limit
-    // the test's branch costs what the ranged sequences save.
-    constexpr bool RG = NV == 3 && FLUX == FLUX_ROE;
+    constexpr bool RG = FLUX == FLUX_ROE;
     double FL[NV], FR[NV], dis[NV];
     euler_flux<NV, RG>(UL, gamma, FL);
     euler_flux<NV, RG>(UR, gamma, FR);
@@ -912,22 +923,25 @@ WCNST_HD void midpoint_eigen(ST& st, const Params& P, Eigen<NV>& E)
     }
 }
 
-// Characteristic field k of the six stencil nodes, w_m = l_k . U_m (sums
+// Characteristic fields of the six stencil nodes, w[k][m] = l_k . U_m (sums
 // over the conserved variables in increasing order, structural zeros
 // skipped).
 template <int NV, class ST>
-WCNST_HD void project_field(ST& st, const Eigen<NV>& E, int k, double (&w)[6])
+WCNST_HD void project_nodes(ST& st, const Eigen<NV>& E, double (&w)[NV][6])
 {
 #pragma unroll
-    for (int m = 0; m < 6; ++m) {
-        double acc = 0.0;
+    for (int m = 0; m < 6; ++m)
 #pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            if (Eigen<NV>::L_zero(k, v)) continue;
-            acc = v == 0 ? E.L(k, v) * st(m, v) : fma(E.L(k, v), st(m, v), acc);
+        for (int k = 0; k < NV; ++k) {
+            double acc = 0.0;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                if (Eigen<NV>::L_zero(k, v)) continue;
+                acc = v == 0 ? E.L(k, v) * st(m, v) : fma(E.L(k, v), st(m, v), acc);
+            }
+            w[k][m] = acc;
+            keep_here(w[k][m]);
         }
-        w[m] = acc;
-    }
 }
 
 // Field k's share of the back-projection U = sum_k r_k w_k (k in increasing
@@ -962,17 +976,28 @@ WCNST_HD void face_flux(ST& st, const Params& P, double (&F)[NV], unsigned& fb, 
         if constexpr (CHAR) {
             Eigen<NV> E;
             basis(E);
-            // one characteristic field at a time: project, interpolate both
-            // sides, and add its share of the back-projection
+            // All fields of all nodes first (node by node they take the
+            // registers of the states), then one field at a time: interpolate
+            // both sides and add its share of the back-projection.  Both are
+            // pinned where they stand: moved into the blocks after the
+            // interpolation's branch, as the compiler would, they carry the
+            // states, the basis and the candidates of every field along (2D
+            // stage 215 -> 145 registers, 1D step 145 -> 99).
+            double w[NV][6];
+            project_nodes<NV>(st, E, w);
 #pragma unroll
             for (int k = 0; k < NV; ++k) {
-                double w[6];
-                project_field<NV>(st, E, k, w);
                 unsigned mL, mR;
                 double wl, wr;
-                interp_pair<SCHEME>(w[0], w[1], w[2], w[3], w[4], w[5], P, wl, wr, mL, mR);
+                interp_pair<SCHEME>(w[k][0], w[k][1], w[k][2], w[k][3], w[k][4], w[k][5], P, wl, wr, mL, mR);
                 fb |= (mL | (mR << 3)) << (6 * k);
                 back_project_field<NV>(E, k, wl, wr, UL, UR);
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    if (Eigen<NV>::R_zero(v, k)) continue;
+                    keep_here(UL[v]);
+                    keep_here(UR[v]);
+                }
             }
         } else {
 #pragma unroll
@@ -1023,16 +1048,12 @@ template <int SYS, int NV>
 WCNST_HD void node_flux(const double* U, const Params& P, double* F)
 {
     if constexpr (SYS == SYS_EULER) {
-        if constexpr (NV == 3) {
-            // 1D: 1/rho by the ranged sequence, the IEEE division where rho
-            // leaves its range
-            euler_flux<NV, true>(U, P.gamma, F);
-            const bool ok = in_ieee_range(U[0]);
-            if (any_lane(!ok)) {
-                if (!ok) euler_flux<NV>(U, P.gamma, F);
-            }
-        } else {
-            euler_flux<NV>(U, P.gamma, F);
+        // 1/rho by the ranged sequence, the IEEE division where rho leaves its
+        // range
+        euler_flux<NV, true>(U, P.gamma, F);
+        const bool ok = in_ieee_range(U[0]);
+        if (any_lane(!ok)) {
+            if (!ok) euler_flux<NV>(U, P.gamma, F);
         }
     } else if constexpr (SYS == SYS_ADV) F[0] = P.adv * U[0];
     else F[0] = 0.5 * U[0] * U[0];

@@ -66,12 +66,11 @@ hipError_t wcnst_launch_persist(const wcnst_desc* d, const void* reqs, int nreq,
 hipError_t wcnst_launch_block_map(const void* reqs, int nreq, int total, int* map, hipStream_t st);
 // true when d has sides other than periodic / zero gradient, or gravity
 bool wcnst_general_bc(const wcnst_desc* d);
-// Wavefront slots of the current device for the 2D stage kernel (two per
-// SIMD, four SIMDs per CU).
+// Wavefronts of the current device at two per SIMD (four SIMDs per CU).
 int wcnst_wave_slots();
-// Rows per 2D segment in [2, 35] when the caller fixes none, for a launch
-// over the grids (strips[i], rows[i]), i < n, on a device of `slots`
-// wavefront slots (2 per SIMD): the height minimising a cost fitted to
+// Rows per 2D segment (a multiple of four in [4, 64]) when the caller fixes
+// none, for a launch over the grids (strips[i], rows[i]), i < n, on a device
+// of `slots` wavefronts (2 per SIMD): the height minimising a cost fitted to
 // measured stage times.  Never changes results.
 int wcnst_auto_rows(const int* strips, const int* rows, int n, int slots);
 // wcnst_launch_init_grid for every grid of a ReqGrid table (one launch).

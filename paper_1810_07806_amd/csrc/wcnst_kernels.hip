@@ -6,15 +6,14 @@
 // Eq. (4)), and the stage update of SSP-RK3 (Sec. 2); the last stage also
 // reduces the CFL wave speed of the new state.
 //
-// Work decomposition.  One wavefront (64 lanes) owns a strip of TX = 61
-// columns, so one row of the strip needs exactly 64 x-midpoints (j = x0-2 ..
-// x0+61): lane l computes midpoint x0-2+l.  In 2D the wavefront marches up a
-// segment of rows; lane l owns column x0+l and computes one y-midpoint per
-// row, keeping the last four y-midpoint fluxes in registers, so every
-// midpoint flux is computed once per strip.  The x-flux of a row is
-// exchanged through 512 bytes of LDS per variable.  Ghost cells are never
-// stored: an index remap at load time, plus a sign or a fixed state for
-// reflecting and fixed sides (no extra HBM traffic).
+// Work decomposition.  A grid is cut into strips of TX = 61 columns, so one
+// row of a strip needs exactly 64 x-midpoints (j = x0-2 .. x0+61): lane l
+// computes midpoint x0-2+l.  In 2D a workgroup of four wavefronts marches up
+// a segment of the strip four rows at a time with rows and y fluxes in LDS,
+// so every midpoint flux is computed once per strip.  1D lines run whole
+// steps per launch (wcnst_line.hip); their right-hand side is here.  Ghost
+// cells are never stored: an index remap at load time, plus a sign or a
+// fixed state for reflecting and fixed sides (no extra HBM traffic).
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -26,6 +25,7 @@
 #include <algorithm>
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "wcnst.h"
@@ -104,19 +104,23 @@ __device__ __forceinline__ unsigned long long wave_max_bits(unsigned long long m
     return m;
 }
 
-template <int SYS, int NV>
+template <int NV>
 __device__ __forceinline__ void stage_epilogue(Ctrl* ctrl, const Params& P, int stage, long long step,
                                                long long cell, const double* o,
                                                unsigned long long& smax_loc)
 {
-    if (cell_bad<SYS, NV>(o, P)) {
-        const unsigned long long key =
-            ((unsigned long long)(step * 3 + stage) << 36) | (unsigned long long)cell;
-        atomicMin(&ctrl->bad_key, key);
-        atomicOr(&ctrl->status, (int)WCNST_E_NONPHYSICAL);
+    Node<NV> N;
+    node_quantities<NV>(o, P.gamma, N);
+    if (any_lane(node_bad<NV>(o, N))) {
+        if (node_bad<NV>(o, N)) {
+            const unsigned long long key =
+                ((unsigned long long)(step * 3 + stage) << 36) | (unsigned long long)cell;
+            atomicMin(&ctrl->bad_key, key);
+            atomicOr(&ctrl->status, (int)WCNST_E_NONPHYSICAL);
+        }
     }
     if (stage == 2) {
-        const unsigned long long b = (unsigned long long)__double_as_longlong(cell_speed<SYS, NV>(o, P));
+        const unsigned long long b = (unsigned long long)__double_as_longlong(node_speed<NV>(N, P));
         smax_loc = b > smax_loc ? b : smax_loc;
     }
 }
@@ -124,13 +128,12 @@ __device__ __forceinline__ void stage_epilogue(Ctrl* ctrl, const Params& P, int 
 // One wave's CFL speed into the next step's record.  The record only grows
 // during the launch (stage 0 of the step cleared it in an earlier launch), so
 // a wave whose maximum it already held when the wave started (seen) skips
-// the atomic: on a long line tens of thousands of waves would otherwise queue
-// on the one address.
+// the atomic: thousands of waves would otherwise queue on the one address.
 __device__ __forceinline__ void flush_speed(Ctrl* ctrl, int parity, unsigned long long smax_loc,
                                             unsigned long long seen)
 {
     const unsigned long long m = wave_max_bits(smax_loc);
-    if (threadIdx.x == 0 && seen < m) atomicMax(&ctrl->rec[parity ^ 1].smax_bits, m);
+    if ((threadIdx.x & (WAVE - 1)) == 0 && seen < m) atomicMax(&ctrl->rec[parity ^ 1].smax_bits, m);
 }
 
 template <int NV>
@@ -497,18 +500,6 @@ sweep1d_persist(const ReqGrid* __restrict__ reqs, int nreq, int per_group, long 
 // Width of a staged row: columns x0-4 .. x0+64 cover the x-stencils of the
 // 64 midpoints and the y-stencils of the 64 lanes.
 constexpr int XW = WAVE + 5;
-constexpr int NSLOT = 6;  // rows j-2 .. j+3 around y-midpoint j
-
-template <int NV>
-__device__ __forceinline__ void load_row(const double* __restrict__ U, size_t plane, size_t rowoff,
-                                         int colA, int colB, bool hasB, double (&ra)[NV], double (&rb)[NV])
-{
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        ra[v] = U[(size_t)v * plane + rowoff + colA];
-        rb[v] = hasB ? U[(size_t)v * plane + rowoff + colB] : 0.0;
-    }
-}
 
 // Ghosts of a staged row: the row's own kind (y boundary, uniform) and each
 // lane's column kinds (x boundary).  Periodic and zero-gradient sides are
@@ -543,25 +534,24 @@ __device__ __forceinline__ void store_row(double (*slot)[XW], int lane, bool has
     }
 }
 
-// Adaptive rows of the first-height segments of a balanced 2D stage launch
-// (the older wavefront of each SIMD pair runs at its lone speed, so its
-// segment's cost sets when the SIMD is done; where the stencil-cut test
-// runs in full, near discontinuities, a segment of equal rows costs more).
+// Adaptive rows of the first-height segments of a two-height 2D stage launch
+// (a segment of equal rows costs more where the stencil-cut test runs in
+// full, near discontinuities).
 // In a launch of parity p (alternating, set by the host), strip s's
-// first-height segment i takes rows [tab[p][s][i], tab[p][s][i+1]).  Each
-// such wavefront records what it took in cost[p]; the first wavefront of
+// first-height segment i takes rows [tab[p][s][i], tab[p][s][i+1]).  The
+// segment's workgroups add what they took to cost[p]; the first workgroup of
 // the launch to finish re-plans tab[1-p] (the previous launch's layout)
 // from cost[1-p] (the previous launch's durations) for the next launch.
 // So no launch reads a table that it or a running launch writes, and every
 // table is a partition of the rows (plan_strip keeps it one).  The layout
-// moves only work between wavefronts: every cell's arithmetic, and so
+// moves only work between workgroups: every cell's arithmetic, and so
 // every result, is the same.  The block sits in the padding after the
 // solver's control block (no kernel argument holds registers through the
 // sweep); on == 0 there: fixed heights.
 struct SegCtl {
     int* tab[2];        // [strips][nseg1 + 1] boundaries
     unsigned* cost[2];  // [strips][nseg1] durations (10 ns ticks)
-    unsigned* ctr;      // wavefronts of the running launch that have finished (0 between launches)
+    unsigned* ctr;      // workgroups of the running launch that have finished (0 between launches)
     int minr;           // fewest rows of a segment
     int on;
 };
@@ -574,11 +564,11 @@ __host__ __device__ inline SegCtl* seg_ctl_of(Ctrl* ctrl)
     return reinterpret_cast<SegCtl*>(reinterpret_cast<char*>(ctrl) + SEGCTL_OFFSET);
 }
 
-// Records the duration of first-height segment cost_idx (-1: a
-// second-height one), counts the wavefront, and, in the launch's first
+// Adds to the duration of first-height segment cost_idx (-1: a
+// second-height one), counts the workgroup, and, in the launch's first
 // finisher, plans
 // every strip of the next launch, staging each strip's boundaries and
-// durations in LDS the wavefront no longer needs (lds: strips * (2 nseg1 +
+// durations in LDS the workgroup no longer needs (lds: strips * (2 nseg1 +
 // 1) ints, checked by the host).  The launch's last finisher clears the
 // count (as does the start of every solve call).
 __device__ __forceinline__ void seg_finish(SegCtl* __restrict__ seg, int par, int cost_idx, unsigned ticks, int nseg1,
@@ -587,201 +577,303 @@ __device__ __forceinline__ void seg_finish(SegCtl* __restrict__ seg, int par, in
     const int ns = (int)gridDim.x, total = (int)(gridDim.x * gridDim.y);
     unsigned old = 0u;
     if (threadIdx.x == 0) {
-        if (cost_idx >= 0) seg->cost[par][cost_idx] = ticks > 0u ? ticks : 1u;
+        if (cost_idx >= 0) atomicAdd(&seg->cost[par][cost_idx], ticks > 0u ? ticks : 1u);
         old = __hip_atomic_fetch_add(seg->ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        // the last to finish: every wavefront has counted
+        // the last to finish: every workgroup has counted
         if (old == (unsigned)total - 1u) __hip_atomic_store(seg->ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     old = __shfl(old, 0);
     if (old != 0u) return;
     const int n = nseg1;
     int* tab = seg->tab[par ^ 1];
-    const unsigned* cost = seg->cost[par ^ 1];
+    unsigned* cost = seg->cost[par ^ 1];
     for (int st = (int)threadIdx.x; st < ns; st += WAVE) {
         int* b = lds + (size_t)st * (2 * n + 1);
         unsigned* d = reinterpret_cast<unsigned*>(b + n + 1);
         for (int i = 0; i <= n; ++i) b[i] = tab[(size_t)st * (n + 1) + i];
-        for (int i = 0; i < n; ++i) d[i] = cost[(size_t)st * n + i];
+        for (int i = 0; i < n; ++i) {
+            d[i] = cost[(size_t)st * n + i];
+            cost[(size_t)st * n + i] = 0u;  // the next launch adds to it
+        }
         plan_strip(b, d, n, seg->minr, tab + (size_t)st * (n + 1));
     }
 }
 
-// One segment (strip bx, rows by*ty ..) of one 2D grid.  Thread 0 of
-// segment (0, 0) opens the next step record.
-// GB: general boundaries (reflecting walls, fixed ends, gravity); without
-// it only index-remap sides (periodic, zero gradient) and no source.
-template <int NV, int FLUX, int SCHEME, bool CHAR, int MODE, bool GB, bool ADAPT>
+// A segment of a strip is worked by a workgroup of four wavefronts, four
+// rows at a time: wavefront w takes one y-midpoint row and one x-midpoint row
+// of the four, then finishes one row.  The rows, their Roe quantities
+// (1/rho, pressure, enthalpy, sqrt(rho), formed once per node instead of four
+// times by the midpoints around it and three times by the node fluxes) and
+// the y fluxes stay in LDS, so a thread holds one midpoint only: 145
+// registers, three wavefronts per SIMD (the LDS of a workgroup, 52.8 KB,
+// allows three workgroups per CU).  Bound: FP64 issue.  Against one
+// wavefront per segment with the stencils, four y fluxes and the next row in
+// registers (256, two per SIMD; a segment's midpoints one after the other),
+// stage times: 128^2 27.5 -> 14.6 us, 256^2 28.8 -> 21.2, 512^2 49.9 ->
+// 41.8, 768^2 92 -> 63, 1024^2 109 -> 95, 1536^2 194 -> 172, 4096^2 1161 ->
+// 984.
+//
+// With rows i0 .. i0+3 under way: y-midpoints i0+1 .. i0+4 are formed (those
+// up to i0 were), from rows i0-1 .. i0+7, the nine rows the ring holds.
+constexpr int WG_WAVES = 4;
+constexpr int WG_ROWS = 4;       // rows per turn
+constexpr int WG_RING = 9;       // staged rows
+constexpr int WG_FY = 7;         // rows of y-midpoint fluxes i0-2 .. i0+4
+constexpr int WG_AUXW = 66;      // Roe quantities of columns 2 .. 66 of a staged row
+
+//
+// Segment by of strip bx: segments 0 .. nseg1-1 hold ty rows each (with an
+// adaptive layout, the rows its table gives), the later ones ty2 (ty2 == ty:
+// one height; cut flags need one height); half 0 or 1 takes the lower or the
+// upper rows of the segment, half -1 all of them.  Thread 0 of the first
+// workgroup opens the next step record.
+// GB: general boundaries (reflecting walls, fixed ends, gravity); without it
+// only index-remap sides (periodic, zero gradient) and no source.
+template <int FLUX, int SCHEME, bool CHAR, int MODE, bool GB, bool ADAPT>
 __device__ __forceinline__ void sweep2d_block(const double* __restrict__ U, const double* __restrict__ Un,
                                               double* __restrict__ out, uint8_t* __restrict__ flags,
-                                              Ctrl* __restrict__ ctrl, const Params& P, const StageArgs& A,
-                                              int ty, int ty2, int nseg1, int bx, int by, int seg_par)
+                                              Ctrl* __restrict__ ctrl, const Params& P, const StageArgs& A, int ty,
+                                              int ty2, int nseg1, int bx, int by, int half, int seg_par)
 {
-    // segment by of the strip: segments 0 .. nseg1-1 hold ty rows each, the
-    // later ones ty2 (ty2 == ty: one height; cut flags need one height)
-    static_assert(NV == 4, "2D sweeps carry the four Euler variables");
-    double dt = 0.0;
-    long long step = 0;
-    unsigned long long seen = 0ull;
-    if constexpr (MODE == MODE_STAGE) {
-        if (!stage_prologue(ctrl, A, dt, step, bx == 0 && by == 0 && threadIdx.x == 0, seen)) return;
-    }
-    // Ring of staged rows (all variables, XW columns) and the x-midpoint /
-    // x node fluxes of the current row.
-    __shared__ double ring[NSLOT][NV][XW];
-    __shared__ double sF[NV][WAVE];
-    __shared__ double sN[NV][WAVE];
-    init_weight_table();
+    constexpr int NV = 4;
+    __shared__ double ring[WG_RING][NV][XW];
+    __shared__ double aux[WG_RING][4][WG_AUXW];  // 1/rho, p, H, sqrt(rho)
+    __shared__ double fy[WG_FY][NV][TX];
+    __shared__ double s_dt;
+    __shared__ long long s_step;
+    __shared__ unsigned long long s_seen;
+    __shared__ int s_go;
     const int nx = P.nx, ny = P.ny;
     const size_t plane = (size_t)nx * ny;
-    const int lane = threadIdx.x;
+    const int lane = (int)threadIdx.x & (WAVE - 1);
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE);
     const int x0 = bx * TX;
     int y0 = by < nseg1 ? by * ty : nseg1 * ty + (by - nseg1) * ty2;
     int y1 = y0 + (by < nseg1 ? ty : ty2);
-    // the segment's duration slot and start time wait in LDS (kept out of
-    // registers through the sweep)
-    __shared__ int seg_slot, seg_p;
+    // the segment's duration slot and start time wait in LDS
+    __shared__ int seg_slot;
     __shared__ unsigned seg_t0;
     if constexpr (MODE == MODE_STAGE && ADAPT) {
         SegCtl* seg = seg_ctl_of(ctrl);
-        int slot = -1;
-        // plain loads of values no wave changes during the launch, kept
+        int sl = -1;
+        // plain loads of values nothing changes during the launch, kept
         // uniform (scalar) so that the sweep's row bounds stay scalar
         if (by < nseg1 && __builtin_amdgcn_readfirstlane(seg->on)) {
             const int* lrow = seg->tab[seg_par] + (size_t)bx * (nseg1 + 1) + by;
             y0 = __builtin_amdgcn_readfirstlane(lrow[0]);
             y1 = __builtin_amdgcn_readfirstlane(lrow[1]);
-            slot = bx * nseg1 + by;
+            sl = bx * nseg1 + by;
         }
         if (threadIdx.x == 0) {
-            seg_slot = slot;
-            seg_p = seg_par;
+            seg_slot = sl;
             seg_t0 = (unsigned)__builtin_amdgcn_s_memrealtime();
         }
     }
     y1 = min(y1, ny);
+    if (half >= 0) {
+        const int mid = min(y0 + (y1 - y0 + 2 * WG_ROWS - 1) / (2 * WG_ROWS) * WG_ROWS, y1);
+        if (half == 0) y1 = mid;
+        else y0 = mid;
+    }
     const int c = x0 + lane;
     const bool cell_ok = lane < TX && c < nx;
-    const int jx = x0 - 2 + lane;
-    // cut flags are reported by right-hand-side launches only
-    const bool own_x = MODE == MODE_RHS && flags && jx <= nx && face_owner(jx, nx, TX) == bx;
-    // columns this lane stages (ghost cells by index remap, any distance)
     const bool hasB = lane < XW - WAVE;
-    const int colA = ghost_map_any(x0 - 4 + lane, nx, P.bc_x);
-    const int colB = ghost_map_any(x0 - 4 + WAVE + lane, nx, P.bc_x);
+    // columns this lane stages (ghost cells by index remap, any distance)
+    // and writes; row addresses stay scalar
+    const unsigned colA = (unsigned)ghost_map_any(x0 - 4 + lane, nx, P.bc_x);
+    const unsigned colB = (unsigned)ghost_map_any(x0 - 4 + WAVE + lane, nx, P.bc_x);
+    const unsigned colC = (unsigned)(cell_ok ? c : 0);
     const int kA = GB ? ghost_kind(x0 - 4 + lane, nx, P.bc_x) : GH_COPY;
     const int kB = GB ? ghost_kind(x0 - 4 + WAVE + lane, nx, P.bc_x) : GH_COPY;
 
-    // y-midpoint fluxes j-3 .. j of this lane's column, in y-normal
-    // variable order (rho, rho v, rho u, E)
-    double fy[4][NV];
+    const auto node_at = [&](const double (*row)[XW], int col, double (*a)[WG_AUXW]) {
+        double u[NV];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) fy[0][v] = fy[1][v] = fy[2][v] = fy[3][v] = 0.0;
-    unsigned long long smax_loc = 0ull;
+        for (int v = 0; v < NV; ++v) u[v] = row[v][col];
+        Node<NV> N;
+        node_quantities<NV>(u, P.gamma, N);
+        a[0][col - 2] = N.ir;
+        a[1][col - 2] = N.p;
+        a[2][col - 2] = N.H;
+        a[3][col - 2] = N.s;
+    };
+    // Row r into slot sl, with the Roe quantities of its columns 2 .. 63 from
+    // registers (columns 64 and 65 by the lanes that hold columns 0 and 1;
+    // column 66, a 65th, later by one wavefront for four rows).
+    const auto stage_row = [&](int r, int sl, double (&ra)[NV], double (&rb)[NV]) {
+        if constexpr (GB) fix_row<NV>(P, ghost_kind(r, ny, P.bc_y), kA, kB, ra, rb);
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        store_row<NV>(ring[sl], ln, hasB, ra, rb);
+        double u[NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) u[v] = ln < 2 ? rb[v] : ra[v];
+        Node<NV> N;
+        node_quantities<NV>(u, P.gamma, N);
+        const int k = ln < 2 ? ln + 62 : ln - 2;
+        aux[sl][0][k] = N.ir;
+        aux[sl][1][k] = N.p;
+        aux[sl][2][k] = N.H;
+        aux[sl][3][k] = N.s;
+    };
+    const auto load = [&](int r, double (&ra)[NV], double (&rb)[NV]) {
+        const double* row = U + (size_t)ghost_map(r, ny, P.bc_y) * nx;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            ra[v] = (row + (size_t)v * plane)[colA];
+            rb[v] = hasB ? (row + (size_t)v * plane)[colB] : 0.0;
+        }
+    };
 
-    // stage rows y0-4 .. y0+1 into slots 0 .. 5
-#pragma unroll 1
-    for (int k = 0; k < NSLOT; ++k) {
-        double ra[NV], rb[NV];
-        const size_t rowoff = (size_t)ghost_map(y0 - 4 + k, ny, P.bc_y) * nx;
-        load_row<NV>(U, plane, rowoff, colA, colB, hasB, ra, rb);
-        if constexpr (GB) fix_row<NV>(P, ghost_kind(y0 - 4 + k, ny, P.bc_y), kA, kB, ra, rb);
-        store_row<NV>(ring[k], lane, hasB, ra, rb);
+    // rows y0-4 .. y0+3, two per wavefront, while thread 0 reads the record
+    {
+        double ra[2][NV], rb[2][NV];
+        load(y0 - 4 + w, ra[0], rb[0]);
+        load(y0 + w, ra[1], rb[1]);
+        if constexpr (MODE == MODE_STAGE) {
+            if (threadIdx.x == 0) {
+                double dt = 0.0;
+                long long step = 0;
+                unsigned long long seen = 0ull;
+                s_go = stage_prologue(ctrl, A, dt, step, bx == 0 && by == 0 && half <= 0, seen) ? 1 : 0;
+                s_dt = dt;
+                s_step = step;
+                s_seen = seen;
+            }
+        }
+        stage_row(y0 - 4 + w, 1 + w, ra[0], rb[0]);
+        stage_row(y0 + w, 5 + w, ra[1], rb[1]);
     }
-    __syncthreads();
+    init_weight_table();  // (its barrier also publishes the rows and the record)
+    if (MODE == MODE_STAGE && !s_go) return;  // one value for the whole workgroup
+    unsigned long long smax_loc = 0ull;
+    int s0 = 0;  // slot of row i0-1
+    int f0 = 0;  // slot of y flux i0+1
+    const auto slot = [&](int k) { return s0 + k < WG_RING ? s0 + k : s0 + k - WG_RING; };
+    const auto fslot = [&](int k) {  // k < 2 WG_FY
+        const int t = f0 + k < WG_FY ? f0 + k : f0 + k - WG_FY;
+        return t < WG_FY ? t : t - WG_FY;
+    };
 
-    int base = 0;  // slot of row j-2
-    for (int j = y0 - 2; j <= y1; ++j) {
-        const int i = j - 1;  // row finished once y-midpoint j is known
-        const int npass = i >= y0 ? 2 : 1;
-        // last pass: y-midpoint (c, j+1/2) from rows j-2 .. j+3 at this
-        // lane's column (normal momentum = rho v first); first pass (rows
-        // i >= y0): x-midpoint (jx+1/2, i) from row i.  Both passes run the
-        // same instructions on different staged data (selects, no branches),
-        // so they share one set of registers; the y flux is the one left in
-        // F when the loop ends.
-        double F[NV];
 #pragma unroll 1
-        for (int pass = 0; pass < npass; ++pass) {
-            const bool py = pass == npass - 1;
-            // the six stencil nodes, read once into registers: node m at
-            // ring[slot][var][col] with (slot, col) = (row j-2+m, c) in the
-            // y pass and (row i, jx-2+m) in the x pass
-            const double* rb = &ring[0][0][0];
-            const int slx = base + 1 < NSLOT ? base + 1 : base + 1 - NSLOT;
-            const int vs1 = py ? 2 * XW : XW, vs2 = py ? XW : 2 * XW;
+    for (int i0 = y0 - WG_ROWS; i0 < y1; i0 += WG_ROWS) {
+        // each phase forms its LDS addresses afresh from the lane (carried
+        // through the sweep they would fill the registers)
+        const auto fresh_lane = [&]() {
+            int l = lane;
+            asm volatile("" : "+v"(l));
+            return l;
+        };
+        const int i = i0 + w, j = i0 + 1 + w;
+        const bool do_x = i >= y0 && i < y1, do_y = j >= y0 - 2 && j <= y1;
+        double F[NV];
+        // the flux at this lane's midpoint from six nodes at row r(m), column
+        // col(m), normal variable order first, and the Roe quantities of
+        // nodes 2 and 3
+        const auto flux = [&](auto py, const auto& r, int col, unsigned& fb) {
+            constexpr bool PY = decltype(py)::value;
             double s[6][NV];
 #pragma unroll
             for (int m = 0; m < 6; ++m) {
-                const int sl = base + m < NSLOT ? base + m : base + m - NSLOT;
-                const int off = py ? sl * NV * XW + lane + 4 : slx * NV * XW + lane + m;
-                s[m][0] = rb[off];
-                s[m][1] = rb[off + vs1];
-                s[m][2] = rb[off + vs2];
-                s[m][3] = rb[off + 3 * XW];
+                const double(*n)[XW] = ring[r(m)];
+                const int q = PY ? col : col + m;
+                s[m][0] = n[0][q];
+                s[m][1] = n[PY ? 2 : 1][q];
+                s[m][2] = n[PY ? 1 : 2][q];
+                s[m][3] = n[3][q];
             }
             RegStencil<NV> st{s};
+            face_flux<SYS_EULER, NV, FLUX, SCHEME, CHAR>(st, P, F, fb, [&](Eigen<NV>& E) {
+                const double(*a2)[WG_AUXW] = aux[r(2)];
+                const double(*a3)[WG_AUXW] = aux[r(3)];
+                const int q2 = PY ? col - 2 : col, q3 = PY ? col - 2 : col + 1;
+                Node<NV> a, b;
+                a.u = s[2][1] * a2[0][q2];
+                a.v = s[2][2] * a2[0][q2];
+                a.H = a2[2][q2];
+                a.s = a2[3][q2];
+                b.u = s[3][1] * a3[0][q3];
+                b.v = s[3][2] * a3[0][q3];
+                b.H = a3[2][q3];
+                b.s = a3[3][q3];
+                roe_average<NV>(a, b, P.gamma, E);
+            });
+        };
+        if (do_y) {
+            // y-midpoint (c, j+1/2): rows j-2 .. j+3 = (i0-1) + w + m (idle
+            // lanes repeat the last column)
             unsigned fb;
-            face_flux<SYS_EULER, NV, FLUX, SCHEME, CHAR>(st, P, F, fb);
-            if (MODE == MODE_RHS && flags) {
-                if (py) {
-                    if (cell_ok && j <= ny && face_owner(j, ny, ty) == by)
-                        write_flags<NV>(flags + (size_t)NV * ny * (nx + 3) * 2, nx, ny + 3, c, j + 2, fb);
-                } else if (own_x) {
-                    write_flags<NV>(flags, ny, nx + 3, i, jx + 2, fb);
-                }
-            }
-            if (!py) {
-                // x node flux at node jx+1 of row i
-                double sn[NV], fn[NV];
+            const int ln = fresh_lane();
+            flux(std::true_type{}, [&](int m) { return slot(w + m); }, min(ln, TX - 1) + 4, fb);
+            if (MODE == MODE_RHS && flags && cell_ok && j <= ny && face_owner(j, ny, ty) == by)
+                write_flags<NV>(flags + (size_t)NV * ny * (nx + 3) * 2, nx, ny + 3, c, j + 2, fb);
+            if (lane < TX) {
+                const int fs = fslot(w);
 #pragma unroll
-                for (int v = 0; v < NV; ++v) sn[v] = s[3][v];
-                node_flux<SYS_EULER, NV>(sn, P, fn);
-#pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    sF[v][lane] = F[v];
-                    sN[v][lane] = fn[v];
-                }
+                for (int v = 0; v < NV; ++v) fy[fs][v][ln] = F[v];
             }
         }
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            fy[0][v] = fy[1][v];
-            fy[1][v] = fy[2][v];
-            fy[2][v] = fy[3][v];
-            fy[3][v] = F[v];
+        if (do_x) {
+            // x-midpoint (jx+1/2, i), jx = x0-2+lane
+            unsigned fb;
+            const int sl = slot(1 + w);
+            flux(std::false_type{}, [&](int) { return sl; }, fresh_lane(), fb);
+            const int jx = x0 - 2 + lane;
+            if (MODE == MODE_RHS && flags && jx <= nx && face_owner(jx, nx, TX) == bx)
+                write_flags<NV>(flags, ny, nx + 3, i, jx + 2, fb);
         }
-        __syncthreads();
-        // U^n of row i first, then row j+4, which travels while row i is
-        // finished (it replaces row j-2 = i-1, which the difference below
-        // still reads): the wait for U^n leaves row j+4 in flight
         double un[NV];
         {
-            const size_t cell = (size_t)(i < 0 ? 0 : i) * nx + (cell_ok ? c : 0);
+            const bool take = MODE == MODE_STAGE && A.stage && do_x && cell_ok;
+            const double* row = Un + (size_t)(do_x ? i : 0) * nx;
 #pragma unroll
-            for (int v = 0; v < NV; ++v)
-                un[v] = MODE == MODE_STAGE && A.stage && npass == 2 && cell_ok ? Un[(size_t)v * plane + cell] : 0.0;
+            for (int v = 0; v < NV; ++v) un[v] = take ? (row + (size_t)v * plane)[colC] : 0.0;
         }
+        const int rn = i0 + 2 * WG_ROWS + w;
+        const bool more = i0 + WG_ROWS < y1 && rn <= y1 + 3;
         double ra[NV], rb[NV];
-        if (j < y1) load_row<NV>(U, plane, (size_t)ghost_map(j + 4, ny, P.bc_y) * nx, colA, colB, hasB, ra, rb);
-        if (npass == 2 && cell_ok) {
-            // rows i-1, i, i+1 of this lane's column are still staged
-            const int s_im = base;                                  // row j-2 = i-1
-            const int s_i = base + 1 < NSLOT ? base + 1 : base + 1 - NSLOT;  // row i
-            const int s_ip = base + 2 < NSLOT ? base + 2 : base + 2 - NSLOT; // row i+1
-            double um[NV], up[NV], Uc[NV], gm[NV], gp[NV];
-            um[0] = ring[s_im][0][lane + 4]; um[1] = ring[s_im][2][lane + 4];
-            um[2] = ring[s_im][1][lane + 4]; um[3] = ring[s_im][3][lane + 4];
-            up[0] = ring[s_ip][0][lane + 4]; up[1] = ring[s_ip][2][lane + 4];
-            up[2] = ring[s_ip][1][lane + 4]; up[3] = ring[s_ip][3][lane + 4];
-            node_flux<SYS_EULER, NV>(um, P, gm);
-            node_flux<SYS_EULER, NV>(up, P, gp);
-            double Rx[NV], Ry[NV], R[NV];
+        if (more) load(rn, ra, rb);
+        double Rx[NV];
+        if (do_x) {
+            // x fluxes of lanes lane .. lane+3; node fluxes of columns c-1, c+1
+            const int sl = slot(1 + w), q = min(fresh_lane(), TX - 1) + 4;
+            double gm[NV], gp[NV], um[NV], up[NV];
+            Node<NV> nm, np;
 #pragma unroll
             for (int v = 0; v < NV; ++v) {
-                Uc[v] = ring[s_i][v][lane + 4];
-                Rx[v] = mnd(P.c1x, P.c2x, P.c3x, sF[v][lane], sF[v][lane + 1], sF[v][lane + 2],
-                            sF[v][lane + 3], sN[v][lane], sN[v][lane + 2]);
-                Ry[v] = mnd(P.c1y, P.c2y, P.c3y, fy[0][v], fy[1][v], fy[2][v], fy[3][v], gm[v], gp[v]);
+                um[v] = ring[sl][v][q - 1];
+                up[v] = ring[sl][v][q + 1];
+            }
+            nm.u = um[1] * aux[sl][0][q - 3];
+            nm.p = aux[sl][1][q - 3];
+            np.u = up[1] * aux[sl][0][q - 1];
+            np.p = aux[sl][1][q - 1];
+            node_flux<NV>(um, nm, gm);
+            node_flux<NV>(up, np, gp);
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+                Rx[v] = mnd(P.c1x, P.c2x, P.c3x, F[v], __shfl_down(F[v], 1), __shfl_down(F[v], 2), __shfl_down(F[v], 3),
+                            gm[v], gp[v]);
+        }
+        __syncthreads();
+        if (do_x && cell_ok) {
+            const int sm = slot(w), si = slot(1 + w), sp = slot(2 + w), ln = fresh_lane(), q = ln + 4;
+            const int fa = fslot(w + 4), fb = fslot(w + 5), fc = fslot(w + 6), fd = fslot(w);  // j-3 .. j
+            double um[NV], up[NV], Uc[NV], gm[NV], gp[NV], Ry[NV], R[NV];
+            um[0] = ring[sm][0][q]; um[1] = ring[sm][2][q]; um[2] = ring[sm][1][q]; um[3] = ring[sm][3][q];
+            up[0] = ring[sp][0][q]; up[1] = ring[sp][2][q]; up[2] = ring[sp][1][q]; up[3] = ring[sp][3][q];
+            Node<NV> nm, np;
+            nm.u = um[1] * aux[sm][0][q - 2];
+            nm.p = aux[sm][1][q - 2];
+            np.u = up[1] * aux[sp][0][q - 2];
+            np.p = aux[sp][1][q - 2];
+            node_flux<NV>(um, nm, gm);
+            node_flux<NV>(up, np, gp);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                Uc[v] = ring[si][v][q];
+                Ry[v] = mnd(P.c1y, P.c2y, P.c3y, fy[fa][v][ln], fy[fb][v][ln], fy[fc][v][ln], fy[fd][v][ln],
+                            gm[v], gp[v]);
             }
             R[0] = Rx[0] + Ry[0];
             R[1] = Rx[1] + Ry[2];
@@ -792,45 +884,50 @@ __device__ __forceinline__ void sweep2d_block(const double* __restrict__ U, cons
                 R[2] = R[2] + Uc[0] * P.gravity;
                 R[3] = R[3] + Uc[2] * P.gravity;
             }
-            const size_t cell = (size_t)i * nx + c;
+            double* row = out + (size_t)i * nx;
             if constexpr (MODE == MODE_RHS) {
 #pragma unroll
-                for (int v = 0; v < NV; ++v) out[(size_t)v * plane + cell] = R[v];
+                for (int v = 0; v < NV; ++v) (row + (size_t)v * plane)[colC] = R[v];
             } else {
                 double o[NV];
-                rk_combine<NV>(A.stage, dt, Uc, un, R, o);
+                rk_combine<NV>(A.stage, s_dt, Uc, un, R, o);
 #pragma unroll
-                for (int v = 0; v < NV; ++v) out[(size_t)v * plane + cell] = o[v];
-                stage_epilogue<SYS_EULER, NV>(ctrl, P, A.stage, step, (long long)cell, o, smax_loc);
+                for (int v = 0; v < NV; ++v) (row + (size_t)v * plane)[colC] = o[v];
+                stage_epilogue<NV>(ctrl, P, A.stage, s_step, (long long)i * nx + c, o, smax_loc);
             }
         }
+        if (i0 + WG_ROWS >= y1) break;
         __syncthreads();
-        // row j-2 is no longer read: its slot takes row j+4
-        if (j < y1) {
-            if constexpr (GB) fix_row<NV>(P, ghost_kind(j + 4, ny, P.bc_y), kA, kB, ra, rb);
-            store_row<NV>(ring[base], lane, hasB, ra, rb);
+        // rows i0-1 .. i0+2 are no longer read: their slots take i0+8 .. i0+11;
+        // column 66 of the rows whose x-midpoints come next
+        if (more) stage_row(rn, slot(w), ra, rb);
+        if (w == 0 && lane < WG_ROWS) {
+            const int sl = s0 + 5 + lane < WG_RING ? s0 + 5 + lane : s0 + 5 + lane - WG_RING;
+            node_at(ring[sl], 66, aux[sl]);
         }
-        base = base + 1 < NSLOT ? base + 1 : 0;
+        s0 = slot(WG_ROWS);
+        f0 = fslot(WG_ROWS);
         __syncthreads();
     }
     if constexpr (MODE == MODE_STAGE) {
-        if (A.stage == 2) flush_speed(ctrl, A.parity, smax_loc, seen);
+        if (A.stage == 2) flush_speed(ctrl, A.parity, smax_loc, s_seen);
         if constexpr (ADAPT) {
             SegCtl* seg = seg_ctl_of(ctrl);
-            if (__builtin_amdgcn_readfirstlane(seg->on))
-                seg_finish(seg, seg_p, seg_slot, (unsigned)__builtin_amdgcn_s_memrealtime() - seg_t0, nseg1,
-                           reinterpret_cast<int*>(&ring[0][0][0]));
+            if (__builtin_amdgcn_readfirstlane(seg->on)) {
+                __syncthreads();  // the segment is done; its ring is free
+                if (w == 0)
+                    seg_finish(seg, seg_par, seg_slot, (unsigned)__builtin_amdgcn_s_memrealtime() - seg_t0, nseg1,
+                               reinterpret_cast<int*>(&ring[0][0][0]));
+            }
         }
     }
 }
 
-// Two wavefronts per SIMD: the register budget is capped at 256 (a few
-// values spill); measured faster than one wavefront with no spills.
-template <int NV, int FLUX, int SCHEME, bool CHAR, int MODE, bool GB>
-__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(2, 2)))
+template <int FLUX, int SCHEME, bool CHAR, int MODE, bool GB>
+__global__ void __launch_bounds__(WAVE * WG_WAVES, 3)
 sweep2d(const double* __restrict__ U, const double* __restrict__ Un, double* __restrict__ out,
         uint8_t* __restrict__ flags, Ctrl* __restrict__ ctrl, Params P, StageArgs A, int ty, int ty2, int nseg1,
-        int seg_par)
+        int halves, int seg_par)
 {
     // Segments in strip-fastest order, each height group in its own XCD
     // runs: the strips on either side of a strip, which stage the same halo
@@ -838,10 +935,15 @@ sweep2d(const double* __restrict__ U, const double* __restrict__ Un, double* __r
     // them through the same L2 at about the same time.
     const int ns = (int)gridDim.x;
     const int L = (int)blockIdx.x + ns * (int)blockIdx.y;
-    const int n1 = ns * nseg1;
-    const int w = L < n1 ? xcd_order(L, 0, n1) : xcd_order(L, n1, ns * (int)gridDim.y - n1);
-    sweep2d_block<NV, FLUX, SCHEME, CHAR, MODE, GB, true>(U, Un, out, flags, ctrl, P, A, ty, ty2, nseg1, w % ns,
-                                                      w / ns, seg_par);
+    const int n1 = ns * nseg1 * (halves ? 2 : 1);
+    const int wk = L < n1 ? xcd_order(L, 0, n1) : xcd_order(L, n1, ns * (int)gridDim.y - n1);
+    int by = wk / ns, half = -1;
+    if (halves) {
+        half = by < 2 * nseg1 ? by & 1 : -1;
+        by = by < 2 * nseg1 ? by >> 1 : by - nseg1;
+    }
+    sweep2d_block<FLUX, SCHEME, CHAR, MODE, GB, true>(U, Un, out, flags, ctrl, P, A, ty, ty2, nseg1, wk % ns, by, half,
+                                                      seg_par);
 }
 
 // One stage of many independent 2D grids in one launch: block b belongs to
@@ -849,8 +951,8 @@ sweep2d(const double* __restrict__ U, const double* __restrict__ Un, double* __r
 // a search over the table, uniform per block), then runs segment
 // b - blk0[r] of that grid with the grid's own parameters, buffers, control
 // block and step parity.
-template <int NV, int FLUX, int SCHEME, bool CHAR, bool GB>
-__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(2, 2)))
+template <int FLUX, int SCHEME, bool CHAR, bool GB>
+__global__ void __launch_bounds__(WAVE * WG_WAVES, 3)
 sweep2d_multi(const ReqGrid* __restrict__ reqs, const int* __restrict__ map, int nreq, int stage, int tick_step,
               int ty)
 {
@@ -868,9 +970,9 @@ sweep2d_multi(const ReqGrid* __restrict__ reqs, const int* __restrict__ map, int
     double* out = stage == 0 ? R.U1 : (stage == 1 ? R.U2 : R.U);
     // one height: every segment of the grid is of the first kind (an exact
     // count keeps nseg1 * ty within the grid)
-    sweep2d_block<NV, FLUX, SCHEME, CHAR, MODE_STAGE, GB, false>(in, R.U, out, nullptr, R.ctrl, P, A, ty, ty,
-                                                             (P.ny + ty - 1) / ty, local % R.nstrips,
-                                                             local / R.nstrips, 0);
+    sweep2d_block<FLUX, SCHEME, CHAR, MODE_STAGE, GB, false>(in, R.U, out, nullptr, R.ctrl, P, A, ty, ty,
+                                                             (P.ny + ty - 1) / ty, local % R.nstrips, local / R.nstrips,
+                                                             -1, 0);
 }
 
 // ----------------------------------------------------- control kernels
@@ -1123,7 +1225,7 @@ extern "C" wcnst_status wcnst_desc_init(wcnst_desc* d)
 // planner also stages a strip's boundaries and durations in the LDS of the
 // 2D stage's row ring: strips * (2 nseg1 + 1) ints, at most LAYOUT_LDS_INTS.
 constexpr int LAYOUT_CAP = 2048;
-constexpr int LAYOUT_LDS_INTS = (int)(sizeof(double) * NSLOT * 4 * XW / sizeof(int));
+constexpr int LAYOUT_LDS_INTS = (int)(sizeof(double) * WG_RING * 4 * XW / sizeof(int));
 static size_t layout_bytes()
 {
     return 2 * sizeof(int) * LAYOUT_CAP + 2 * sizeof(unsigned) * LAYOUT_CAP + 256;
@@ -1304,28 +1406,27 @@ extern "C" wcnst_status wcnst_destroy(wcnst_solver* s)
 // ---------------------------------------------------------- launchers
 
 // Segments of a 2D launch: nseg1 segments of ty rows, then segments of ty2
-// rows, nseg in all.
+// rows, nseg in all; halves: two workgroups per first-height segment.
 struct SegMap {
     int ty, ty2, nseg1, nseg;
+    bool halves;
+    int blocks() const { return nseg + (halves ? nseg1 : 0); }
 };
 
-// One height in general.  A launch of one round with two wavefronts on most
-// SIMDs (more wavefronts than SIMDs, no more than the slots) is balanced:
-// a SIMD issues from its oldest wavefront first, so of the two that share
-// it (blocks b and b + SIMDs in dispatch order, measured) the first runs at
-// about its lone speed while the second, measured, advances about 0.48 as
-// fast, then finishes alone.  The first-dispatched rows of segments take a
-// rows and the others c rows with c + 3 = 0.48 (a + 3) (3: the extra rows
-// of y-midpoints of a segment), so that both wavefronts of a SIMD finish
-// together: 2048^2 stage 0.45 -> 0.41 ms (47 and 22 rows).
+// One height in general.  Single solves on grids of 1.5 to 2 segments of 35
+// rows per SIMD take two, the first adaptive (rows move between segments as
+// the flow moves: SegCtl): na segments of a rows, na the segments of a strip
+// per SIMD, and the rest of c rows with c + 3 = 0.48 (a + 3); the first are
+// halved between two workgroups, so that all hold about c rows (2048^2: 24,
+// 23 and 22).
 static SegMap stage_segments(int nstrips, int ny, int ty, int slots, bool balance)
 {
     const int nseg = (ny + ty - 1) / ty;
-    const SegMap one{ty, ty, nseg, nseg};
+    const SegMap one{ty, ty, nseg, nseg, false};
     if (!balance) return one;
     const long long simds = slots / 2;
-    const long long waves = (long long)nstrips * nseg;
-    if (waves <= simds || waves > slots) return one;
+    const long long waves = (long long)nstrips * ((ny + 34) / 35);
+    if (2 * waves <= 3 * simds || waves > slots) return one;
     const int na = (int)(simds / nstrips);
     if (na < 1) return one;
     const double r = 0.48;
@@ -1335,7 +1436,7 @@ static SegMap stage_segments(int nstrips, int ny, int ty, int slots, bool balanc
     const int c = (rest + na - 1) / na;
     const int nb = (rest + c - 1) / c;
     if ((long long)nstrips * (na + nb) > slots) return one;
-    return SegMap{a, c, na, na + nb};
+    return SegMap{a, c, na, na + nb, true};
 }
 
 // Adaptive layout for the solver's balanced stage shape (2D, heights chosen
@@ -1346,7 +1447,7 @@ static wcnst_status layout_reset(wcnst_solver* s)
 {
     s->seg_on = false;
     const int ns = (s->d.nx + TX - 1) / TX;
-    const SegMap m = s->d.ndim == 2 ? stage_segments(ns, s->d.ny, s->ty, s->slots, true) : SegMap{1, 1, 1, 1};
+    const SegMap m = s->d.ndim == 2 ? stage_segments(ns, s->d.ny, s->ty, s->slots, true) : SegMap{1, 1, 1, 1, false};
     const bool on = s->d.ndim == 2 && s->seg_tab && !s->ty_user && m.nseg1 < m.nseg &&
                     (long long)ns * (m.nseg1 + 1) <= LAYOUT_CAP && (long long)ns * (2 * m.nseg1 + 1) <= LAYOUT_LDS_INTS;
     hipLaunchKernelGGL(layout_init, dim3(1), dim3(256), 0, s->stream, s->ctrl, on ? 1 : 0, s->seg_tab, s->seg_cost,
@@ -1372,11 +1473,13 @@ static void launch_sweep_t(const wcnst_solver* s, const double* U, const double*
             s->seg_launch += 1;
         }
         if (wcnst_general_bc(&s->d))
-            hipLaunchKernelGGL((sweep2d<NV, FLUX, SCHEME, CHAR, MODE, true>), dim3(nstrips, m.nseg), dim3(WAVE), 0,
-                               s->stream, U, Un, out, flags, s->ctrl, s->P, A, m.ty, m.ty2, m.nseg1, seg_par);
+            hipLaunchKernelGGL((sweep2d<FLUX, SCHEME, CHAR, MODE, true>), dim3(nstrips, m.blocks()), dim3(WAVE * WG_WAVES),
+                               0, s->stream, U, Un, out, flags, s->ctrl, s->P, A, m.ty, m.ty2, m.nseg1,
+                               m.halves ? 1 : 0, seg_par);
         else
-            hipLaunchKernelGGL((sweep2d<NV, FLUX, SCHEME, CHAR, MODE, false>), dim3(nstrips, m.nseg), dim3(WAVE), 0,
-                               s->stream, U, Un, out, flags, s->ctrl, s->P, A, m.ty, m.ty2, m.nseg1, seg_par);
+            hipLaunchKernelGGL((sweep2d<FLUX, SCHEME, CHAR, MODE, false>), dim3(nstrips, m.blocks()), dim3(WAVE * WG_WAVES),
+                               0, s->stream, U, Un, out, flags, s->ctrl, s->P, A, m.ty, m.ty2, m.nseg1,
+                               m.halves ? 1 : 0, seg_par);
     } else if (s->d.diff == WCNST_MD) {
         constexpr int W = strip_cells<DIFF_MD>();
         hipLaunchKernelGGL((sweep1d<SYS, NV, FLUX, SCHEME, CHAR, DIFF_MD>), dim3((s->d.nx + W - 1) / W), dim3(WAVE), 0,
@@ -1817,20 +1920,25 @@ int wcnst_wave_slots()
 
 int wcnst_auto_rows(const int* strips, const int* rows, int n, int slots)
 {
-    // A wavefront's time grows with its segment's rows plus a fixed cost
-    // (3 extra rows of y-midpoints and the 6-row staging prologue: about 6
-    // rows in all), and the launch lasts as long as its busiest SIMD: w
-    // wavefronts share a SIMD's issue (w >= 2), a lone one uses about two
-    // thirds of it.  The segment height minimising (rows + 6) * g(w),
-    // ties to the taller, fits measured stage times from 128^2 to 8192^2.
-    const long long simds = slots / 2 > 0 ? slots / 2 : 1;
-    int best_ty = 35;
+    // A turn of four rows takes a workgroup about 7 us alone on its CU and
+    // 3.3 us of a full CU's time, and a segment about 2.4 us more (three
+    // extra rows of y-midpoints, the first rows' loads).  A launch of up to
+    // three workgroups per CU lasts as long as the fullest CU; beyond that
+    // the CUs take the next ones as they finish.  The height (a multiple of
+    // four) minimising this fits measured stage times from 64^2 to 4096^2
+    // within 15 %, ties to the taller.
+    const int cus = slots / 8 > 0 ? slots / 8 : 1;
+    int best_ty = 64;
     double best = 1e300;
-    for (int ty = 35; ty >= 2; --ty) {
-        long long waves = 0;
-        for (int i = 0; i < n; ++i) waves += (long long)strips[i] * ((rows[i] + ty - 1) / ty);
-        const long long w = (waves + simds - 1) / simds;
-        const double cost = (ty + 6) * (w <= 1 ? 1.5 : (double)w);
+    for (int ty = 64; ty >= WG_ROWS; ty -= WG_ROWS) {
+        long long groups = 0;
+        for (int i = 0; i < n; ++i) groups += (long long)strips[i] * ((rows[i] + ty - 1) / ty);
+        const double turns = ty / WG_ROWS, work = 3.3 * turns + 2.4;
+        const long long m = (groups + cus - 1) / cus;
+        const double cost = m <= 1   ? 7.0 * turns + 7.6
+                            : m == 2 ? std::max(7.0 * turns + 7.6, 2.9 * work + 6.0)
+                            : m == 3 ? 3.75 * work + 6.0
+                                     : work * ((double)groups / cus + 1.6) + 6.0;
         if (cost < best) {
             best = cost;
             best_ty = ty;
@@ -1951,10 +2059,10 @@ static void launch_multi_t(const ReqGrid* reqs, const int* map, int nreq, int nb
                            int ty, bool general, hipStream_t st)
 {
     if (general)
-        hipLaunchKernelGGL((sweep2d_multi<4, FLUX, SCHEME, CHAR, true>), dim3(nblocks), dim3(WAVE), 0, st, reqs, map,
+        hipLaunchKernelGGL((sweep2d_multi<FLUX, SCHEME, CHAR, true>), dim3(nblocks), dim3(WAVE * WG_WAVES), 0, st, reqs, map,
                            nreq, stage, tick_step, ty);
     else
-        hipLaunchKernelGGL((sweep2d_multi<4, FLUX, SCHEME, CHAR, false>), dim3(nblocks), dim3(WAVE), 0, st, reqs, map,
+        hipLaunchKernelGGL((sweep2d_multi<FLUX, SCHEME, CHAR, false>), dim3(nblocks), dim3(WAVE * WG_WAVES), 0, st, reqs, map,
                            nreq, stage, tick_step, ty);
 }
 
