@@ -324,6 +324,7 @@ extern "C" wcnst_status wcnst_batch_solve(wcnst_batch* b, double* U, const doubl
         q.t_final = t_final[i];
         q.cfl = cfl;
         q.nstrips = wcnst_line_tiles(d.diff, d.nx);
+        q.width = wcnst_line_width(d.diff, d.nx);
         q.parity0 = 0;
         q.home = 0;
     }

@@ -182,12 +182,12 @@ struct Tile1D {
     static constexpr int REACH = DIFF == DIFF_MD ? 5 : (DIFF == DIFF_HW ? 3 : 4);
     int c0, c1, nx;
     bool ghosts;
-    // tile t of nt equal tiles of a line of nx cells
-    WCNST_HD Tile1D(int t, int nt, int nx_, int bc) : nx(nx_)
+    // tile t of a line of nx cells cut every w cells
+    WCNST_HD Tile1D(int t, int w, int nx_, int bc) : nx(nx_)
     {
-        c0 = (int)((long long)t * nx / nt);
-        c1 = (int)((long long)(t + 1) * nx / nt);
-        ghosts = bc != BC_PERIODIC || nt == 1;
+        c0 = t * w;
+        c1 = nx - c0 < w ? nx : c0 + w;
+        ghosts = bc != BC_PERIODIC || w >= nx;
     }
     WCNST_HD int A(int s) const
     {
@@ -209,18 +209,20 @@ struct Tile1D {
     WCNST_HD int source(int p, int bc) const;
 };
 
-// Threads of a tile, and the tiles of a line of nx cells: as few as let every
-// midpoint and position of the widest stage have a thread of its own.
+// Threads of a tile, and the cells a line of nx cells is cut at: equal tiles,
+// as few as let every midpoint and position of the widest stage have a
+// thread of its own.
 constexpr int TILE_THREADS = 256;
 constexpr int LINE_CAP = TILE_THREADS + 8;  // positions of a tile, at most TILE_THREADS + 2 REACH - 2 G + 1
 template <int DIFF>
-WCNST_HD int line_tiles(int nx)
+WCNST_HD int line_tile_width(int nx)
 {
     using T = Tile1D<DIFF>;
     // one tile: nx + 2 REACH positions; else W + 4 REACH cells in stage 0
-    if (nx + 2 * T::REACH <= TILE_THREADS) return 1;
+    if (nx + 2 * T::REACH <= TILE_THREADS) return nx;
     constexpr int W = TILE_THREADS - 4 * T::REACH - 2 * T::G + 1;
-    return (nx + W - 1) / W;
+    const int nt = (nx + W - 1) / W;
+    return (nx + nt - 1) / nt;
 }
 
 struct Params {
@@ -275,8 +277,10 @@ struct ReqGrid {
     Params P;
     double t_final, cfl;
     int nstrips, blk0;
+    int width;    // 1D: cells per tile
     int parity0;  // step parity at tick step 0
     int home;     // 1D: step parity at which the state is in U (else in U1)
+    int pad;
 };
 
 // One step of a 1D line: dt = fixed_dt when > 0, else cfl / CFL speed,
@@ -375,12 +379,11 @@ WCNST_HD int ghost_kind(int g, int n, int bc)
 // boundary, `fixed` the two fixed states of that direction.
 WCNST_HD double ghost_value(int kind, int v, int normal, double val, const double (&fixed)[2][4])
 {
-    // selects, not an index computed from `kind`: the fixed states stay in
-    // registers instead of private memory
+    // selects of values, not of an address computed from `kind`: the fixed
+    // states stay in registers instead of private memory
+    const double lo = fixed[0][v], hi = fixed[1][v];
     if (kind == GH_REVERSE) return v == normal ? -val : val;
-    if (kind == GH_FIXED_LO) return fixed[0][v];
-    if (kind == GH_FIXED_HI) return fixed[1][v];
-    return val;
+    return kind == GH_FIXED_LO ? lo : (kind == GH_FIXED_HI ? hi : val);
 }
 
 // 1/x for the cut-off test: one Newton step on the hardware estimate

@@ -36,12 +36,13 @@ hipError_t wcnst_launch_init_grid(const wcnst_desc* d, const double* U, void* ct
 // without one each block searches the table.
 hipError_t wcnst_launch_multi(const wcnst_desc* d, const void* reqs, const int* map, int nreq, int nblocks, int stage,
                               int tick_step, int ty, bool general, hipStream_t st);
-// 1D lines.  Tiles (workgroups) of a line; one whole SSP-RK3 step of one
+// 1D lines.  Cells per tile and tiles (workgroups) of a line; one whole SSP-RK3 step of one
 // line, in -> out, or of every 1D Euler line of a ReqGrid table (nblocks =
 // total tiles), whose state alternates between U and U1 with the step
 // parity; and the end of a run of steps: the newest state into U (from U1
 // where the newest record's parity is not the line's home parity), the
 // status of a failure in the last step, the CFL speed into the newest record.
+int wcnst_line_width(int diff, int nx);
 int wcnst_line_tiles(int diff, int nx);
 hipError_t wcnst_launch_line_step(const wcnst_desc* d, const wcnst::Params& P, wcnst::Ctrl* ctrl, const double* in,
                                   double* out, const wcnst::LineStep& A, hipStream_t st);

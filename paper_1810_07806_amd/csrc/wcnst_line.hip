@@ -80,7 +80,7 @@ __device__ __forceinline__ void line_stage(const Tile1D<DIFF>& T, const LineLds<
                                            unsigned long long& bad, unsigned long long& speed)
 {
     constexpr int G = Tile1D<DIFF>::G;
-    const int tid = (int)threadIdx.x, nt = (int)blockDim.x, cap = lds.cap;
+    const int tid = (int)threadIdx.x, nt = ONE ? TILE_THREADS : (int)blockDim.x, cap = lds.cap;
     const int a = T.A(stage), base = T.base();
     const double* S = lds.state(stage);
     double* F = lds.flux();
@@ -202,18 +202,15 @@ __device__ __forceinline__ void line_stage(const Tile1D<DIFF>& T, const LineLds<
 }
 
 // Loads the tile's positions (cells, ghosts) from U and forms their Roe
-// quantities.  (No barrier.)
-template <int SYS, int NV, int DIFF>
+// quantities.  (No barrier.)  ONE: at most two positions per thread, both
+// loads in flight.
+template <int SYS, int NV, int DIFF, bool ONE>
 __device__ __forceinline__ void line_load(const Tile1D<DIFF>& T, const LineLds<SYS, NV, DIFF>& lds,
                                           const double* __restrict__ U, const Params& P)
 {
     const int base = T.base(), n = T.positions();
-    for (int i = (int)threadIdx.x; i < n; i += (int)blockDim.x) {
+    const auto store = [&](int i, double (&u)[NV]) {
         const int p = base + i;
-        const int c = T.ghosts ? ghost_map(p, P.nx, P.bc_x) : ghost_map_any(p, P.nx, P.bc_x);
-        double u[NV];
-#pragma unroll
-        for (int v = 0; v < NV; ++v) u[v] = U[(size_t)v * P.nx + c];
         if (P.bc_x >= BC_REFLECT && any_lane(p < 0 || p >= P.nx)) {
             const int kind = ghost_kind(p, P.nx, P.bc_x);
 #pragma unroll
@@ -222,6 +219,33 @@ __device__ __forceinline__ void line_load(const Tile1D<DIFF>& T, const LineLds<S
         Node<NV> N;
         if constexpr (SYS == SYS_EULER) node_quantities<NV>(u, P.gamma, N);
         put_position<SYS, NV>(lds, lds.state(0), i, u, N);
+    };
+    const auto fetch = [&](int i, double (&u)[NV]) {
+        const int p = base + i;
+        int c = p;
+        if (any_lane(p < 0 || p >= P.nx)) c = ghost_map(p, P.nx, P.bc_x);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) u[v] = U[(size_t)v * P.nx + c];
+    };
+    if constexpr (ONE) {
+        const int i = (int)threadIdx.x, k = i + TILE_THREADS;
+        double u[2][NV];
+        if (i < n) fetch(i, u[0]);
+        if (k < n) fetch(k, u[1]);
+#pragma unroll 1
+        for (int m = 0; m < 2; ++m) {
+            if (m * TILE_THREADS + i >= n) break;
+            double t[NV];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) t[v] = m ? u[1][v] : u[0][v];
+            store(m * TILE_THREADS + i, t);
+        }
+    } else {
+        for (int i = (int)threadIdx.x; i < n; i += (int)blockDim.x) {
+            double u[NV];
+            fetch(i, u);
+            store(i, u);
+        }
     }
 }
 
@@ -258,15 +282,15 @@ __device__ __forceinline__ bool line_dt(const LineStep& A, double t, unsigned lo
     return true;
 }
 
-// One SSP-RK3 step of tile t of nt of a line: in -> out.
+// One SSP-RK3 step of tile t of a line cut every w cells: in -> out.
 template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, int DIFF>
 __device__ __forceinline__ void line_tile_step(const double* __restrict__ in, double* __restrict__ out,
                                                Ctrl* __restrict__ ctrl, const Params& P, const LineStep& A, int t,
-                                               int nt, double* mem)
+                                               int w, double* mem)
 {
-    const Tile1D<DIFF> T(t, nt, P.nx, P.bc_x);
+    const Tile1D<DIFF> T(t, w, P.nx, P.bc_x);
     const LineLds<SYS, NV, DIFF> lds{mem, LINE_CAP};
-    line_load<SYS, NV, DIFF>(T, lds, in, P);
+    line_load<SYS, NV, DIFF, true>(T, lds, in, P);
     // Every workgroup takes the same decision from the record: an earlier
     // step's failure and the final time are fixed when the launch starts
     // (a failure in this launch has a key of this step; the status follows
@@ -323,10 +347,11 @@ __device__ __forceinline__ void line_tile_step(const double* __restrict__ in, do
 
 template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, int DIFF>
 __global__ void __launch_bounds__(TILE_THREADS, LINE_WAVES<SYS>)
-line_step(const double* __restrict__ in, double* __restrict__ out, Ctrl* __restrict__ ctrl, Params P, LineStep A)
+line_step(const double* __restrict__ in, double* __restrict__ out, Ctrl* __restrict__ ctrl, Params P, LineStep A,
+          int width)
 {
     __shared__ double mem[LineLds<SYS, NV, DIFF>::PER * LINE_CAP];
-    line_tile_step<SYS, NV, FLUX, SCHEME, CHAR, DIFF>(in, out, ctrl, P, A, (int)blockIdx.x, (int)gridDim.x, mem);
+    line_tile_step<SYS, NV, FLUX, SCHEME, CHAR, DIFF>(in, out, ctrl, P, A, (int)blockIdx.x, width, mem);
 }
 
 // One step of many independent 1D Euler lines: block b takes a tile of the
@@ -351,7 +376,7 @@ line_step_multi(const ReqGrid* __restrict__ reqs, const int* __restrict__ map, i
     }
     ReqGrid R = reqs[row];
     // the fields the tile and its loads need, in one round trip
-    asm volatile("" : "+s"(R.U), "+s"(R.U1), "+s"(R.ctrl), "+s"(R.P.nx), "+s"(R.P.bc_x), "+s"(R.blk0), "+s"(R.nstrips),
+    asm volatile("" : "+s"(R.U), "+s"(R.U1), "+s"(R.ctrl), "+s"(R.P.nx), "+s"(R.P.bc_x), "+s"(R.blk0), "+s"(R.width),
                  "+s"(R.parity0), "+s"(R.home));
     LineStep A;
     A.t_final = R.t_final;
@@ -360,7 +385,7 @@ line_step_multi(const ReqGrid* __restrict__ reqs, const int* __restrict__ map, i
     A.parity = (R.parity0 + tick_step) & 1;
     const bool at_home = A.parity == R.home;
     line_tile_step<SYS_EULER, 3, FLUX, SCHEME, CHAR, DIFF_MND>(at_home ? R.U : R.U1, at_home ? R.U1 : R.U, R.ctrl, R.P,
-                                                              A, b - R.blk0, R.nstrips, mem);
+                                                              A, b - R.blk0, R.width, mem);
 }
 
 // Many steps of a short line in one launch: one workgroup holds the whole
@@ -379,9 +404,9 @@ line_solo(double* __restrict__ U, Ctrl* __restrict__ ctrl, Params P, LineStep A,
     __shared__ unsigned long long red[3];  // step n's maximum in red[n % 3]
     __shared__ unsigned long long first_bad;
     const int tid = (int)threadIdx.x;
-    const Tile1D<DIFF> T(0, 1, P.nx, P.bc_x);
+    const Tile1D<DIFF> T(0, P.nx, P.nx, P.bc_x);
     LineLds<SYS, NV, DIFF> lds{mem, cap};
-    line_load<SYS, NV, DIFF>(T, lds, U, P);
+    line_load<SYS, NV, DIFF, false>(T, lds, U, P);
     int p = A.parity;
     const long long step0 = ctrl->rec[p].step;
     double time = ctrl->rec[p].t, before = time, dt = 0.0;
@@ -508,10 +533,16 @@ using namespace wcnst;
 
 // --------------------------------------------------------------- launchers
 
+int wcnst_line_width(int diff, int nx)
+{
+    return diff == WCNST_MD ? line_tile_width<DIFF_MD>(nx)
+                            : (diff == WCNST_HWCNS ? line_tile_width<DIFF_HW>(nx) : line_tile_width<DIFF_MND>(nx));
+}
+
 int wcnst_line_tiles(int diff, int nx)
 {
-    return diff == WCNST_MD ? line_tiles<DIFF_MD>(nx)
-                            : (diff == WCNST_HWCNS ? line_tiles<DIFF_HW>(nx) : line_tiles<DIFF_MND>(nx));
+    const int w = wcnst_line_width(diff, nx);
+    return (nx + w - 1) / w;
 }
 
 namespace {
@@ -546,12 +577,16 @@ struct LineLaunch {
             return;
         }
         const dim3 g((unsigned)wcnst_line_tiles(d->diff, d->nx)), b(TILE_THREADS);
+        const int w = wcnst_line_width(d->diff, d->nx);
         if (d->diff == WCNST_MD)
-            hipLaunchKernelGGL((line_step<SYS, NV, FLUX, SCHEME, CHAR, DIFF_MD>), g, b, 0, st, in, out, ctrl, *P, A);
+            hipLaunchKernelGGL((line_step<SYS, NV, FLUX, SCHEME, CHAR, DIFF_MD>), g, b, 0, st, in, out, ctrl, *P, A,
+                               w);
         else if (d->diff == WCNST_HWCNS)
-            hipLaunchKernelGGL((line_step<SYS, NV, FLUX, SCHEME, CHAR, DIFF_HW>), g, b, 0, st, in, out, ctrl, *P, A);
+            hipLaunchKernelGGL((line_step<SYS, NV, FLUX, SCHEME, CHAR, DIFF_HW>), g, b, 0, st, in, out, ctrl, *P, A,
+                               w);
         else
-            hipLaunchKernelGGL((line_step<SYS, NV, FLUX, SCHEME, CHAR, DIFF_MND>), g, b, 0, st, in, out, ctrl, *P, A);
+            hipLaunchKernelGGL((line_step<SYS, NV, FLUX, SCHEME, CHAR, DIFF_MND>), g, b, 0, st, in, out, ctrl, *P, A,
+                               w);
     }
     template <int SYS, int NV, int FLUX, bool CHAR>
     void scheme() const

@@ -227,6 +227,7 @@ static wcnst_status issue_dim(wcnst_pool* p, int ndim, const std::vector<int>& a
         q.t_final = r.t_final;
         q.cfl = r.cfl;
         q.nstrips = ndim == 2 ? (r.d.nx + TX - 1) / TX : wcnst_line_tiles(r.d.diff, r.d.nx);
+        q.width = wcnst_line_width(r.d.diff, r.d.nx);
         q.blk0 = blocks;
         q.parity0 = q.home = r.parity;
         blocks += q.nstrips * (ndim == 2 ? (r.d.ny + ty - 1) / ty : 1);

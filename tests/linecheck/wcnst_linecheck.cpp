@@ -12,19 +12,20 @@ using namespace wcnst;
 // every index the kernel forms stays inside the tile's positions and reads
 // only what the stage's input holds; else a code naming the first violation.
 template <int DIFF>
-static int check(int nx, int bc, int nt, int cap)
+static int check(int nx, int bc, int w, int cap)
 {
+    const int nt = (nx + w - 1) / w;
     using T1 = Tile1D<DIFF>;
     std::vector<int> owned((size_t)nx, 0);
     for (int t = 0; t < nt; ++t) {
-        const T1 T(t, nt, nx, bc);
+        const T1 T(t, w, nx, bc);
         const int base = T.base(), np = T.positions();
         if (T.c0 >= T.c1) return 1;
         for (int c = T.c0; c < T.c1; ++c) owned[(size_t)c] += 1;
         if (np > cap) return 2;
         // the load: every position has a source cell
         for (int p = base; p < base + np; ++p) {
-            const int c = T.ghosts ? ghost_map(p, nx, bc) : ghost_map_any(p, nx, bc);
+            const int c = ghost_map(p, nx, bc);
             if (c < 0 || c >= nx) return 3;
             if (T.ghosts && (p < -T1::REACH || p >= nx + T1::REACH)) return 4;
         }
@@ -42,7 +43,9 @@ static int check(int nx, int bc, int nt, int cap)
                     const int p = a - 2 + i;
                     if (p < lo || p >= hi || i >= cap) return 7;
                 }
-            for (int p = T.out_lo(s); p < T.out_hi(s); ++p) {
+            // (a tile of several writes only its own cells in the last stage)
+            const bool own = s == 2 && nt > 1;
+            for (int p = own ? a : T.out_lo(s); p < (own ? b : T.out_hi(s)); ++p) {
                 const int c = T.source(p, bc);
                 if (c < a || c >= b || c < lo || c >= hi) return 8;
                 if (p < base || p >= base + np) return 9;
@@ -64,9 +67,9 @@ extern "C" {
 
 int lc_check(int nx, int bc, int diff)
 {
-    if (diff == DIFF_MD) return check<DIFF_MD>(nx, bc, line_tiles<DIFF_MD>(nx), LINE_CAP);
-    if (diff == DIFF_HW) return check<DIFF_HW>(nx, bc, line_tiles<DIFF_HW>(nx), LINE_CAP);
-    return check<DIFF_MND>(nx, bc, line_tiles<DIFF_MND>(nx), LINE_CAP);
+    if (diff == DIFF_MD) return check<DIFF_MD>(nx, bc, line_tile_width<DIFF_MD>(nx), LINE_CAP);
+    if (diff == DIFF_HW) return check<DIFF_HW>(nx, bc, line_tile_width<DIFF_HW>(nx), LINE_CAP);
+    return check<DIFF_MND>(nx, bc, line_tile_width<DIFF_MND>(nx), LINE_CAP);
 }
 
 }  // extern "C"
