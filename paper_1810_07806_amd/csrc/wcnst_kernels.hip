@@ -671,9 +671,16 @@ __device__ __forceinline__ void sweep2d_block(const double* __restrict__ U, cons
     }
     y1 = min(y1, ny);
     if (half >= 0) {
-        const int mid = min(y0 + (y1 - y0 + 2 * WG_ROWS - 1) / (2 * WG_ROWS) * WG_ROWS, y1);
+        const int mid = y0 + (y1 - y0) / 2;
         if (half == 0) y1 = mid;
         else y0 = mid;
+    }
+    // Workgroups of a two-height launch meet at multiples of a turn's rows, so
+    // that only a strip's last turn is short (halves and later segments have
+    // WG_ROWS rows at least, except the last: none is left empty).
+    if (ADAPT && ty2 != ty) {
+        y0 &= -WG_ROWS;
+        if (y1 < ny) y1 &= -WG_ROWS;
     }
     const int c = x0 + lane;
     const bool cell_ok = lane < TX && c < nx;
@@ -1451,7 +1458,7 @@ static wcnst_status layout_reset(wcnst_solver* s)
     const bool on = s->d.ndim == 2 && s->seg_tab && !s->ty_user && m.nseg1 < m.nseg &&
                     (long long)ns * (m.nseg1 + 1) <= LAYOUT_CAP && (long long)ns * (2 * m.nseg1 + 1) <= LAYOUT_LDS_INTS;
     hipLaunchKernelGGL(layout_init, dim3(1), dim3(256), 0, s->stream, s->ctrl, on ? 1 : 0, s->seg_tab, s->seg_cost,
-                       s->seg_ctr, ns, m.nseg1, m.ty, std::max(1, m.ty / 4));
+                       s->seg_ctr, ns, m.nseg1, m.ty, std::max(2 * WG_ROWS, m.ty / 4));
     HIP_TRY(hipGetLastError());
     s->seg_n1 = m.nseg1;
     s->seg_launch = 0;
