@@ -345,7 +345,13 @@ WCNST_HD int ghost_map(int g, int n, int bc)
 // where lanes past the last needed column stage data.
 WCNST_HD int ghost_map_any(int g, int n, int bc)
 {
-    if (bc == BC_PERIODIC) return ((g % n) + n) % n;
+    if (bc == BC_PERIODIC) {
+        // (the divisions only where one period does not do)
+        g = g < 0 ? g + n : g;
+        g = g >= n ? g - n : g;
+        if (__builtin_expect(g < 0 || g >= n, 0)) g = ((g % n) + n) % n;
+        return g;
+    }
     if (bc == BC_REFLECT) {
         g = g < 0 ? -1 - g : g;
         g = g >= n ? 2 * n - 1 - g : g;
@@ -507,9 +513,11 @@ __device__ __forceinline__ double* weight_table()
     return tab;
 }
 
-__device__ __forceinline__ void init_weight_table()
+// The 24 threads from `first` on fill it.
+__device__ __forceinline__ void init_weight_table(unsigned first = 0)
 {
-    if (threadIdx.x < 24) weight_table()[threadIdx.x] = teno_weight(threadIdx.x / 3, threadIdx.x % 3);
+    const unsigned k = threadIdx.x - first;
+    if (k < 24) weight_table()[k] = teno_weight(k / 3, k % 3);
     __syncthreads();
 }
 

@@ -50,11 +50,9 @@ __device__ __forceinline__ bool first_thread()
 }
 
 // Reads the step record; stage 0 also decides dt (every block computes the
-// same value from the same inputs) and opens the next record.  Stage 2 also
-// reads the next record's CFL speed as it stands (seen): a lower bound of
-// the value the launch leaves there, which lets flush_speed skip atomics.
+// same value from the same inputs) and opens the next record.
 __device__ __forceinline__ bool stage_prologue(Ctrl* ctrl, const StageArgs& A, double& dt,
-                                               long long& step, bool lead, unsigned long long& seen)
+                                               long long& step, bool lead)
 {
     const StepRec* cur = &ctrl->rec[A.parity];
     // independent reads, issued together (stage 0's lead writes the record's
@@ -64,11 +62,6 @@ __device__ __forceinline__ bool stage_prologue(Ctrl* ctrl, const StageArgs& A, d
     const double t = cur->t;
     const unsigned long long sbits = cur->smax_bits;
     const double dt_rec = A.stage != 0 ? cur->dt : 0.0;
-    // (an atomic load: from L2, where the other waves' maxima arrive, not a
-    // per-CU cached copy of the launch's first read)
-    seen = A.stage == 2 ? __hip_atomic_load(&ctrl->rec[A.parity ^ 1].smax_bits, __ATOMIC_RELAXED,
-                                            __HIP_MEMORY_SCOPE_AGENT)
-                        : 0ull;
     if (status != 0 || done != 0) return false;
     step = stp;
     if (A.stage != 0) {
@@ -125,15 +118,24 @@ __device__ __forceinline__ void stage_epilogue(Ctrl* ctrl, const Params& P, int 
     }
 }
 
-// One wave's CFL speed into the next step's record.  The record only grows
-// during the launch (stage 0 of the step cleared it in an earlier launch), so
-// a wave whose maximum it already held when the wave started (seen) skips
-// the atomic: thousands of waves would otherwise queue on the one address.
+// A workgroup's CFL speed into the next step's record: the wavefronts' maxima
+// meet in LDS (red), and a workgroup whose maximum the record already holds
+// skips the atomic (the record only grows during the launch; stage 0 of the
+// step cleared it in an earlier one).  Atomics of one address take about
+// 12 ns each: one per wavefront held a 256^2 step up by 15 us.
+template <int WAVES>
 __device__ __forceinline__ void flush_speed(Ctrl* ctrl, int parity, unsigned long long smax_loc,
-                                            unsigned long long seen)
+                                            unsigned long long (&red)[WAVES])
 {
-    const unsigned long long m = wave_max_bits(smax_loc);
-    if ((threadIdx.x & (WAVE - 1)) == 0 && seen < m) atomicMax(&ctrl->rec[parity ^ 1].smax_bits, m);
+    unsigned long long m = wave_max_bits(smax_loc);
+    if ((threadIdx.x & (WAVE - 1)) == 0) red[threadIdx.x / WAVE] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) m = red[w] > m ? red[w] : m;
+        unsigned long long* dst = &ctrl->rec[parity ^ 1].smax_bits;
+        if (__hip_atomic_load(dst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < m) atomicMax(dst, m);
+    }
 }
 
 template <int NV>
@@ -523,6 +525,14 @@ __device__ __forceinline__ void fix_row(const Params& P, int ky, int kA, int kB,
     }
 }
 
+// A result another launch reads, written through to memory: at the end of a
+// launch the XCDs' L2 caches hold no dirty lines that the next one would wait
+// for (0.3 to 0.9 us of a 256^2 stage).
+__device__ __forceinline__ void store_agent(double* p, double v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 template <int NV>
 __device__ __forceinline__ void store_row(double (*slot)[XW], int lane, bool hasB, const double (&ra)[NV],
                                           const double (&rb)[NV])
@@ -641,7 +651,7 @@ __device__ __forceinline__ void sweep2d_block(const double* __restrict__ U, cons
     __shared__ double fy[WG_FY][NV][TX];
     __shared__ double s_dt;
     __shared__ long long s_step;
-    __shared__ unsigned long long s_seen;
+    __shared__ unsigned long long s_speed[WG_WAVES];
     __shared__ int s_go;
     const int nx = P.nx, ny = P.ny;
     const size_t plane = (size_t)nx * ny;
@@ -741,11 +751,9 @@ __device__ __forceinline__ void sweep2d_block(const double* __restrict__ U, cons
             if (threadIdx.x == 0) {
                 double dt = 0.0;
                 long long step = 0;
-                unsigned long long seen = 0ull;
-                s_go = stage_prologue(ctrl, A, dt, step, bx == 0 && by == 0 && half <= 0, seen) ? 1 : 0;
+                s_go = stage_prologue(ctrl, A, dt, step, bx == 0 && by == 0 && half <= 0) ? 1 : 0;
                 s_dt = dt;
                 s_step = step;
-                s_seen = seen;
             }
         }
         stage_row(y0 - 4 + w, 1 + w, ra[0], rb[0]);
@@ -899,7 +907,7 @@ __device__ __forceinline__ void sweep2d_block(const double* __restrict__ U, cons
                 double o[NV];
                 rk_combine<NV>(A.stage, s_dt, Uc, un, R, o);
 #pragma unroll
-                for (int v = 0; v < NV; ++v) (row + (size_t)v * plane)[colC] = o[v];
+                for (int v = 0; v < NV; ++v) store_agent(&(row + (size_t)v * plane)[colC], o[v]);
                 stage_epilogue<NV>(ctrl, P, A.stage, s_step, (long long)i * nx + c, o, smax_loc);
             }
         }
@@ -917,7 +925,7 @@ __device__ __forceinline__ void sweep2d_block(const double* __restrict__ U, cons
         __syncthreads();
     }
     if constexpr (MODE == MODE_STAGE) {
-        if (A.stage == 2) flush_speed(ctrl, A.parity, smax_loc, s_seen);
+        if (A.stage == 2) flush_speed(ctrl, A.parity, smax_loc, s_speed);
         if constexpr (ADAPT) {
             SegCtl* seg = seg_ctl_of(ctrl);
             if (__builtin_amdgcn_readfirstlane(seg->on)) {
