@@ -34,8 +34,13 @@ hipError_t wcnst_launch_init_grid(const wcnst_desc* d, const double* U, void* ct
 // (the tables then take the stage kernels that handle them).
 // map (nullable): the table row of every block (wcnst_launch_block_map);
 // without one each block searches the table.
+struct MultiShape {
+    int ty;        // rows per segment
+    bool general;  // as above
+    bool brief;    // whole short segments (wcnst_short_segments)
+};
 hipError_t wcnst_launch_multi(const wcnst_desc* d, const void* reqs, const int* map, int nreq, int nblocks, int stage,
-                              int tick_step, int ty, bool general, hipStream_t st);
+                              int tick_step, MultiShape m, hipStream_t st);
 // 1D lines.  Cells per tile and tiles (workgroups) of a line; one whole SSP-RK3 step of one
 // line, in -> out, or of every 1D Euler line of a ReqGrid table (nblocks =
 // total tiles), whose state alternates between U and U1 with the step
@@ -69,11 +74,14 @@ hipError_t wcnst_launch_block_map(const void* reqs, int nreq, int total, int* ma
 bool wcnst_general_bc(const wcnst_desc* d);
 // Wavefronts of the current device at two per SIMD (four SIMDs per CU).
 int wcnst_wave_slots();
-// Rows per 2D segment (a multiple of four in [4, 64]) when the caller fixes
-// none, for a launch over the grids (strips[i], rows[i]), i < n, on a device
-// of `slots` wavefronts (2 per SIMD): the height minimising a cost fitted to
-// measured stage times.  Never changes results.
+// Rows per 2D segment (1 to 12, or a multiple of four up to 64) when the
+// caller fixes none, for a launch over the grids (strips[i], rows[i]), i < n,
+// on a device of `slots` wavefronts (2 per SIMD): the height minimising a
+// cost fitted to measured stage times.  Never changes results.
 int wcnst_auto_rows(const int* strips, const int* rows, int n, int slots);
+// Whether a launch of `groups` segments of ty rows works them whole (twelve
+// wavefronts each) or by turns of four rows: the cheaper by the same fit.
+bool wcnst_short_segments(long long groups, int ty, int slots);
 // wcnst_launch_init_grid for every grid of a ReqGrid table (one launch).
 hipError_t wcnst_launch_multi_init(int ndim, const void* reqs, int nreq, hipStream_t st);
 

@@ -961,13 +961,229 @@ sweep2d(const double* __restrict__ U, const double* __restrict__ Un, double* __r
                                                       seg_par);
 }
 
+// A short segment whole: twelve wavefronts stage all its rows, share out its
+// 2 n + 3 rows of midpoints (one row each at a time, x rows first: they also
+// difference) and finish a row each; three barriers in all.  Where the grid
+// is too small to fill the CUs (one such workgroup fills a CU's registers)
+// the time is that of one segment from end to end, and the four-row turns
+// above, one wavefront per SIMD, leave it to the latency of a lone wavefront
+// and to a second round trip to memory.  x and y midpoints run the same code,
+// the stencil's stride a variable: 122 registers.  Stage times against the
+// turns: 64^2 14.6 -> 9.1 us, 128^2 14.5 -> 9.6, 192^2 14.5 -> 11.3, 256^2
+// 21.5 -> 13.7, 128x512 24.6 -> 15.9, 384^2 24.2 -> 20.6, 512^2 37.2 -> 33.2;
+// 768^2 54.6 -> 60.7, so full grids keep the turns, whose rows of extra
+// midpoints are shared by more cells.
+constexpr int ON_WAVES = 12;
+constexpr int ON_ROWS = 12;  // rows at most
+
+template <int FLUX, int SCHEME, bool CHAR, int MODE, bool GB>
+__device__ __forceinline__ void sweep2d_short_block(const double* __restrict__ U, const double* __restrict__ Un,
+                                                    double* __restrict__ out, uint8_t* __restrict__ flags,
+                                                    Ctrl* __restrict__ ctrl, const Params& P, const StageArgs& A,
+                                                    int ty, int bx, int by)
+{
+    constexpr int NV = 4;
+    __shared__ double ring[ON_ROWS + 8][NV][XW];      // rows y0-4 .. y1+3
+    __shared__ double aux[ON_ROWS + 8][4][WG_AUXW];   // 1/rho, p, H, sqrt(rho) of columns 2 .. 66
+    __shared__ double fy[ON_ROWS + 3][NV][TX];        // y-midpoint fluxes y0-2 .. y1
+    __shared__ double rx[ON_ROWS][NV][TX];            // x differences
+    __shared__ double s_dt;
+    __shared__ long long s_step;
+    __shared__ unsigned long long s_speed[ON_WAVES];
+    __shared__ int s_go;
+    const int nx = P.nx, ny = P.ny;
+    const size_t plane = (size_t)nx * ny;
+    const int lane = (int)threadIdx.x & (WAVE - 1);
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE);
+    const int x0 = bx * TX, y0 = by * ty, y1 = min(y0 + ty, ny), n = y1 - y0;
+    const int c = x0 + lane;
+    const bool cell_ok = lane < TX && c < nx;
+    const bool hasB = lane < XW - WAVE;
+    {
+        const unsigned colA = (unsigned)ghost_map_any(x0 - 4 + lane, nx, P.bc_x);
+        const unsigned colB = (unsigned)ghost_map_any(x0 - 4 + WAVE + lane, nx, P.bc_x);
+        double ra[2][NV], rb[2][NV];
+        const auto load = [&](int k, double (&a)[NV], double (&b)[NV]) {
+            const double* row = U + (size_t)ghost_map(y0 - 4 + k, ny, P.bc_y) * nx;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                a[v] = (row + (size_t)v * plane)[colA];
+                b[v] = hasB ? (row + (size_t)v * plane)[colB] : 0.0;
+            }
+        };
+        const auto put = [&](int k, double (&a)[NV], double (&b)[NV]) {
+            if constexpr (GB)
+                fix_row<NV>(P, ghost_kind(y0 - 4 + k, ny, P.bc_y), ghost_kind(x0 - 4 + lane, nx, P.bc_x),
+                            ghost_kind(x0 - 4 + WAVE + lane, nx, P.bc_x), a, b);
+            store_row<NV>(ring[k], lane, hasB, a, b);
+            const auto node = [&](const double (&u)[NV], int q) {
+                Node<NV> N;
+                node_quantities<NV>(u, P.gamma, N);
+                aux[k][0][q] = N.ir;
+                aux[k][1][q] = N.p;
+                aux[k][2][q] = N.H;
+                aux[k][3][q] = N.s;
+            };
+            double u[NV];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) u[v] = lane < 2 ? b[v] : a[v];
+            node(u, lane < 2 ? lane + 62 : lane - 2);
+            if (k >= 4 && k < n + 4 && lane == 2) node(b, 64);
+        };
+        const bool second = w + ON_WAVES < n + 8;
+        if (w < n + 8) load(w, ra[0], rb[0]);
+        if (second) load(w + ON_WAVES, ra[1], rb[1]);
+        if constexpr (MODE == MODE_STAGE) {
+            if (threadIdx.x == 0) {
+                double dt = 0.0;
+                long long step = 0;
+                s_go = stage_prologue(ctrl, A, dt, step, bx == 0 && by == 0) ? 1 : 0;
+                s_dt = dt;
+                s_step = step;
+            }
+        }
+        if (w < n + 8) put(w, ra[0], rb[0]);
+        if (second) put(w + ON_WAVES, ra[1], rb[1]);
+    }
+    init_weight_table((ON_WAVES - 1) * WAVE);  // (its barrier also publishes the rows and the record)
+    if (MODE == MODE_STAGE && !s_go) return;  // one value for the whole workgroup
+    double un[NV];
+    {
+        const bool take = MODE == MODE_STAGE && A.stage && w < n && cell_ok;
+        const double* row = Un + (size_t)(w < n ? y0 + w : 0) * nx;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) un[v] = take ? (row + (size_t)v * plane)[c] : 0.0;
+    }
+    // tasks 0 .. n-1: the x-midpoints of row y0+t and their differences;
+    // then the y-midpoints j+1/2, j = y0-2 .. y1
+#pragma unroll 1
+    for (int t = w; t < 2 * n + 3; t += ON_WAVES) {
+        const bool isx = t < n;
+        const int r0 = isx ? t + 4 : t - n;  // slot of the stencil's first node (x: of all)
+        const int col = isx ? lane : min(lane, TX - 1) + 4;
+        const double* p = &ring[r0][0][col];
+        const int to = isx ? 1 : NV * XW, o1 = isx ? XW : 2 * XW, o2 = isx ? 2 * XW : XW;
+        double s[6][NV], F[NV];
+#pragma unroll
+        for (int m = 0; m < 6; ++m) {
+            s[m][0] = p[m * to];
+            s[m][1] = p[m * to + o1];
+            s[m][2] = p[m * to + o2];
+            s[m][3] = p[m * to + 3 * XW];
+        }
+        RegStencil<NV> st{s};
+        unsigned fb;
+        face_flux<SYS_EULER, NV, FLUX, SCHEME, CHAR>(st, P, F, fb, [&](Eigen<NV>& E) {
+            const double* a2 = &aux[isx ? r0 : r0 + 2][0][isx ? col : col - 2];
+            const double* a3 = a2 + (isx ? 1 : 4 * WG_AUXW);
+            Node<NV> a, b;
+            a.u = s[2][1] * a2[0];
+            a.v = s[2][2] * a2[0];
+            a.H = a2[2 * WG_AUXW];
+            a.s = a2[3 * WG_AUXW];
+            b.u = s[3][1] * a3[0];
+            b.v = s[3][2] * a3[0];
+            b.H = a3[2 * WG_AUXW];
+            b.s = a3[3 * WG_AUXW];
+            roe_average<NV>(a, b, P.gamma, E);
+        });
+        if (isx) {
+            const int jx = x0 - 2 + lane;
+            if (MODE == MODE_RHS && flags && jx <= nx && face_owner(jx, nx, TX) == bx)
+                write_flags<NV>(flags, ny, nx + 3, y0 + t, jx + 2, fb);
+            const int q = min(lane, TX - 1) + 4;
+            double gm[NV], gp[NV], um[NV], up[NV];
+            Node<NV> nm, np;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                um[v] = ring[r0][v][q - 1];
+                up[v] = ring[r0][v][q + 1];
+            }
+            nm.u = um[1] * aux[r0][0][q - 3];
+            nm.p = aux[r0][1][q - 3];
+            np.u = up[1] * aux[r0][0][q - 1];
+            np.p = aux[r0][1][q - 1];
+            node_flux<NV>(um, nm, gm);
+            node_flux<NV>(up, np, gp);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                const double R = mnd(P.c1x, P.c2x, P.c3x, F[v], __shfl_down(F[v], 1), __shfl_down(F[v], 2),
+                                     __shfl_down(F[v], 3), gm[v], gp[v]);
+                if (lane < TX) rx[t][v][lane] = R;
+            }
+        } else {
+            const int k = t - n, j = y0 - 2 + k;
+            if (MODE == MODE_RHS && flags && cell_ok && j <= ny && face_owner(j, ny, ty) == by)
+                write_flags<NV>(flags + (size_t)NV * ny * (nx + 3) * 2, nx, ny + 3, c, j + 2, fb);
+            if (lane < TX) {
+#pragma unroll
+                for (int v = 0; v < NV; ++v) fy[k][v][lane] = F[v];
+            }
+        }
+    }
+    __syncthreads();
+    unsigned long long smax_loc = 0ull;
+    if (w < n && cell_ok) {
+        const int i = y0 + w, sm = w + 3, si = w + 4, sp = w + 5, q = lane + 4;
+        double um[NV], up[NV], Uc[NV], gm[NV], gp[NV], Rx[NV], Ry[NV], R[NV];
+        um[0] = ring[sm][0][q]; um[1] = ring[sm][2][q]; um[2] = ring[sm][1][q]; um[3] = ring[sm][3][q];
+        up[0] = ring[sp][0][q]; up[1] = ring[sp][2][q]; up[2] = ring[sp][1][q]; up[3] = ring[sp][3][q];
+        Node<NV> nm, np;
+        nm.u = um[1] * aux[sm][0][q - 2];
+        nm.p = aux[sm][1][q - 2];
+        np.u = up[1] * aux[sp][0][q - 2];
+        np.p = aux[sp][1][q - 2];
+        node_flux<NV>(um, nm, gm);
+        node_flux<NV>(up, np, gp);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            Uc[v] = ring[si][v][q];
+            Rx[v] = rx[w][v][lane];
+            Ry[v] = mnd(P.c1y, P.c2y, P.c3y, fy[w][v][lane], fy[w + 1][v][lane], fy[w + 2][v][lane],
+                        fy[w + 3][v][lane], gm[v], gp[v]);
+        }
+        R[0] = Rx[0] + Ry[0];
+        R[1] = Rx[1] + Ry[2];
+        R[2] = Rx[2] + Ry[1];
+        R[3] = Rx[3] + Ry[3];
+        if (GB && P.gravity != 0.0) {
+            R[2] = R[2] + Uc[0] * P.gravity;
+            R[3] = R[3] + Uc[2] * P.gravity;
+        }
+        double* row = out + (size_t)i * nx;
+        if constexpr (MODE == MODE_RHS) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) (row + (size_t)v * plane)[c] = R[v];
+        } else {
+            double o[NV];
+            rk_combine<NV>(A.stage, s_dt, Uc, un, R, o);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) store_agent(&(row + (size_t)v * plane)[c], o[v]);
+            stage_epilogue<NV>(ctrl, P, A.stage, s_step, (long long)i * nx + c, o, smax_loc);
+        }
+    }
+    if constexpr (MODE == MODE_STAGE) {
+        if (A.stage == 2) flush_speed(ctrl, A.parity, smax_loc, s_speed);
+    }
+}
+
+template <int FLUX, int SCHEME, bool CHAR, int MODE, bool GB>
+__global__ void __launch_bounds__(WAVE * ON_WAVES, 3)
+sweep2d_short(const double* __restrict__ U, const double* __restrict__ Un, double* __restrict__ out,
+              uint8_t* __restrict__ flags, Ctrl* __restrict__ ctrl, Params P, StageArgs A, int ty)
+{
+    sweep2d_short_block<FLUX, SCHEME, CHAR, MODE, GB>(U, Un, out, flags, ctrl, P, A, ty, (int)blockIdx.x,
+                                                      (int)blockIdx.y);
+}
+
 // One stage of many independent 2D grids in one launch: block b belongs to
 // the request r with blk0[r] <= b < blk0[r+1] (from the block map, else by
 // a search over the table, uniform per block), then runs segment
 // b - blk0[r] of that grid with the grid's own parameters, buffers, control
 // block and step parity.
-template <int FLUX, int SCHEME, bool CHAR, bool GB>
-__global__ void __launch_bounds__(WAVE * WG_WAVES, 3)
+// SHORT: segments of at most ON_ROWS rows, whole (sweep2d_short_block).
+template <int FLUX, int SCHEME, bool CHAR, bool GB, bool SHORT>
+__global__ void __launch_bounds__(WAVE * (SHORT ? ON_WAVES : WG_WAVES), 3)
 sweep2d_multi(const ReqGrid* __restrict__ reqs, const int* __restrict__ map, int nreq, int stage, int tick_step,
               int ty)
 {
@@ -983,11 +1199,15 @@ sweep2d_multi(const ReqGrid* __restrict__ reqs, const int* __restrict__ map, int
     const StageArgs A = request_stage(R, stage, tick_step);
     const double* in = stage == 0 ? R.U : (stage == 1 ? R.U1 : R.U2);
     double* out = stage == 0 ? R.U1 : (stage == 1 ? R.U2 : R.U);
-    // one height: every segment of the grid is of the first kind (an exact
-    // count keeps nseg1 * ty within the grid)
-    sweep2d_block<FLUX, SCHEME, CHAR, MODE_STAGE, GB, false>(in, R.U, out, nullptr, R.ctrl, P, A, ty, ty,
-                                                             (P.ny + ty - 1) / ty, local % R.nstrips, local / R.nstrips,
-                                                             -1, 0);
+    if constexpr (SHORT)
+        sweep2d_short_block<FLUX, SCHEME, CHAR, MODE_STAGE, GB>(in, R.U, out, nullptr, R.ctrl, P, A, ty,
+                                                                local % R.nstrips, local / R.nstrips);
+    else
+        // one height: every segment of the grid is of the first kind (an exact
+        // count keeps nseg1 * ty within the grid)
+        sweep2d_block<FLUX, SCHEME, CHAR, MODE_STAGE, GB, false>(in, R.U, out, nullptr, R.ctrl, P, A, ty, ty,
+                                                                 (P.ny + ty - 1) / ty, local % R.nstrips,
+                                                                 local / R.nstrips, -1, 0);
 }
 
 // ----------------------------------------------------- control kernels
@@ -1487,7 +1707,15 @@ static void launch_sweep_t(const wcnst_solver* s, const double* U, const double*
             seg_par = (int)(s->seg_launch & 1);
             s->seg_launch += 1;
         }
-        if (wcnst_general_bc(&s->d))
+        const bool gb = wcnst_general_bc(&s->d);
+        if (m.ty == m.ty2 && wcnst_short_segments((long long)nstrips * m.nseg, m.ty, s->slots)) {
+            if (gb)
+                hipLaunchKernelGGL((sweep2d_short<FLUX, SCHEME, CHAR, MODE, true>), dim3(nstrips, m.nseg),
+                                   dim3(WAVE * ON_WAVES), 0, s->stream, U, Un, out, flags, s->ctrl, s->P, A, m.ty);
+            else
+                hipLaunchKernelGGL((sweep2d_short<FLUX, SCHEME, CHAR, MODE, false>), dim3(nstrips, m.nseg),
+                                   dim3(WAVE * ON_WAVES), 0, s->stream, U, Un, out, flags, s->ctrl, s->P, A, m.ty);
+        } else if (gb)
             hipLaunchKernelGGL((sweep2d<FLUX, SCHEME, CHAR, MODE, true>), dim3(nstrips, m.blocks()), dim3(WAVE * WG_WAVES),
                                0, s->stream, U, Un, out, flags, s->ctrl, s->P, A, m.ty, m.ty2, m.nseg1,
                                m.halves ? 1 : 0, seg_par);
@@ -1933,27 +2161,51 @@ int wcnst_wave_slots()
     return 8 * cus;
 }
 
+// Stage time (us) of a launch of `groups` workgroups with segments of ty
+// rows, by turns of four rows.  A turn takes a workgroup about 7 us alone on
+// its CU and 3.3 us of a full CU's time, and a segment about 2.4 us more
+// (three extra rows of y-midpoints, the first rows' loads).  A launch of up
+// to three workgroups per CU lasts as long as the fullest CU, beyond that
+// little longer than its rounds.  Fits stage times measured from
+// 64^2 to 4096^2 within 8 %.
+static double turns_cost(long long groups, int ty, int cus)
+{
+    const double turns = (ty + WG_ROWS - 1) / WG_ROWS, work = 3.3 * turns + 2.4;
+    const long long m = (groups + cus - 1) / cus;
+    return m <= 1   ? 7.0 * turns + 7.6
+           : m == 2 ? std::max(7.0 * turns + 7.6, 2.7 * work + 6.0)
+           : m == 3 ? 3.35 * work + 6.0
+                    : work * ((double)m + 0.3) + 6.0;
+}
+
+// The same with whole short segments: a CU works one at a time, 2.15 us for
+// every row of midpoints per SIMD and 0.1 us a row, in rounds.  Fits 16^2 to
+// 768^2 with 1 to 12 rows within 10 % where the last round is not nearly
+// empty.
+static double short_cost(long long groups, int ty, int cus)
+{
+    const int per_simd = (2 * ty + 3 + 3) / 4;
+    return 4.2 + (double)((groups + cus - 1) / cus) * (2.15 * per_simd + 0.1 * ty);
+}
+
+bool wcnst_short_segments(long long groups, int ty, int slots)
+{
+    const int cus = slots / 8 > 0 ? slots / 8 : 1;
+    return ty <= ON_ROWS && short_cost(groups, ty, cus) < turns_cost(groups, ty, cus);
+}
+
 int wcnst_auto_rows(const int* strips, const int* rows, int n, int slots)
 {
-    // A turn of four rows takes a workgroup about 7 us alone on its CU and
-    // 3.3 us of a full CU's time, and a segment about 2.4 us more (three
-    // extra rows of y-midpoints, the first rows' loads).  A launch of up to
-    // three workgroups per CU lasts as long as the fullest CU; beyond that
-    // the CUs take the next ones as they finish.  The height (a multiple of
-    // four) minimising this fits measured stage times from 64^2 to 4096^2
-    // within 15 %, ties to the taller.
     const int cus = slots / 8 > 0 ? slots / 8 : 1;
     int best_ty = 64;
     double best = 1e300;
-    for (int ty = 64; ty >= WG_ROWS; ty -= WG_ROWS) {
+    // ties to the taller
+    for (int ty = 64; ty >= 1; --ty) {
+        if (ty > ON_ROWS && ty % WG_ROWS) continue;
         long long groups = 0;
         for (int i = 0; i < n; ++i) groups += (long long)strips[i] * ((rows[i] + ty - 1) / ty);
-        const double turns = ty / WG_ROWS, work = 3.3 * turns + 2.4;
-        const long long m = (groups + cus - 1) / cus;
-        const double cost = m <= 1   ? 7.0 * turns + 7.6
-                            : m == 2 ? std::max(7.0 * turns + 7.6, 2.9 * work + 6.0)
-                            : m == 3 ? 3.75 * work + 6.0
-                                     : work * ((double)groups / cus + 1.6) + 6.0;
+        double cost = ty <= ON_ROWS ? short_cost(groups, ty, cus) : 1e300;
+        if (ty % WG_ROWS == 0) cost = std::min(cost, turns_cost(groups, ty, cus));
         if (cost < best) {
             best = cost;
             best_ty = ty;
@@ -2069,57 +2321,66 @@ hipError_t wcnst_launch_multi_init(int ndim, const void* reqs, int nreq, hipStre
     return hipGetLastError();
 }
 
+template <int FLUX, int SCHEME, bool CHAR, bool GB, bool SHORT>
+static void launch_multi_k(const ReqGrid* reqs, const int* map, int nreq, int nblocks, int stage, int tick_step,
+                           int ty, hipStream_t st)
+{
+    hipLaunchKernelGGL((sweep2d_multi<FLUX, SCHEME, CHAR, GB, SHORT>), dim3(nblocks),
+                       dim3(WAVE * (SHORT ? ON_WAVES : WG_WAVES)), 0, st, reqs, map, nreq, stage, tick_step, ty);
+}
+
 template <int FLUX, int SCHEME, bool CHAR>
 static void launch_multi_t(const ReqGrid* reqs, const int* map, int nreq, int nblocks, int stage, int tick_step,
-                           int ty, bool general, hipStream_t st)
+                           MultiShape m, hipStream_t st)
 {
-    if (general)
-        hipLaunchKernelGGL((sweep2d_multi<FLUX, SCHEME, CHAR, true>), dim3(nblocks), dim3(WAVE * WG_WAVES), 0, st, reqs, map,
-                           nreq, stage, tick_step, ty);
-    else
-        hipLaunchKernelGGL((sweep2d_multi<FLUX, SCHEME, CHAR, false>), dim3(nblocks), dim3(WAVE * WG_WAVES), 0, st, reqs, map,
-                           nreq, stage, tick_step, ty);
+    if (m.brief) {
+        if (m.general) launch_multi_k<FLUX, SCHEME, CHAR, true, true>(reqs, map, nreq, nblocks, stage, tick_step, m.ty, st);
+        else launch_multi_k<FLUX, SCHEME, CHAR, false, true>(reqs, map, nreq, nblocks, stage, tick_step, m.ty, st);
+    } else {
+        if (m.general) launch_multi_k<FLUX, SCHEME, CHAR, true, false>(reqs, map, nreq, nblocks, stage, tick_step, m.ty, st);
+        else launch_multi_k<FLUX, SCHEME, CHAR, false, false>(reqs, map, nreq, nblocks, stage, tick_step, m.ty, st);
+    }
 }
 
 template <int FLUX, bool CHAR>
 static void launch_multi_s(const wcnst_desc* d, const ReqGrid* reqs, const int* map, int nreq, int nblocks, int stage,
-                           int tick_step, int ty, bool general, hipStream_t st)
+                           int tick_step, MultiShape m, hipStream_t st)
 {
     switch (d->scheme) {
     case WCNST_LINEAR:
-        launch_multi_t<FLUX, SCH_LINEAR, CHAR>(reqs, map, nreq, nblocks, stage, tick_step, ty, general, st);
+        launch_multi_t<FLUX, SCH_LINEAR, CHAR>(reqs, map, nreq, nblocks, stage, tick_step, m, st);
         break;
     case WCNST_JS:
-        launch_multi_t<FLUX, SCH_JS, CHAR>(reqs, map, nreq, nblocks, stage, tick_step, ty, general, st);
+        launch_multi_t<FLUX, SCH_JS, CHAR>(reqs, map, nreq, nblocks, stage, tick_step, m, st);
         break;
     case WCNST_Z:
-        launch_multi_t<FLUX, SCH_Z, CHAR>(reqs, map, nreq, nblocks, stage, tick_step, ty, general, st);
+        launch_multi_t<FLUX, SCH_Z, CHAR>(reqs, map, nreq, nblocks, stage, tick_step, m, st);
         break;
     default:
         if (d->q == 6)
-            launch_multi_t<FLUX, SCH_TENO, CHAR>(reqs, map, nreq, nblocks, stage, tick_step, ty, general, st);
+            launch_multi_t<FLUX, SCH_TENO, CHAR>(reqs, map, nreq, nblocks, stage, tick_step, m, st);
         else
-            launch_multi_t<FLUX, SCH_TENO_Q, CHAR>(reqs, map, nreq, nblocks, stage, tick_step, ty, general, st);
+            launch_multi_t<FLUX, SCH_TENO_Q, CHAR>(reqs, map, nreq, nblocks, stage, tick_step, m, st);
         break;
     }
 }
 
 template <int FLUX>
 static void launch_multi_f(const wcnst_desc* d, const ReqGrid* r, const int* map, int nreq, int nblocks, int stage,
-                           int tick_step, int ty, bool general, hipStream_t st)
+                           int tick_step, MultiShape m, hipStream_t st)
 {
-    if (d->charwise) launch_multi_s<FLUX, true>(d, r, map, nreq, nblocks, stage, tick_step, ty, general, st);
-    else launch_multi_s<FLUX, false>(d, r, map, nreq, nblocks, stage, tick_step, ty, general, st);
+    if (d->charwise) launch_multi_s<FLUX, true>(d, r, map, nreq, nblocks, stage, tick_step, m, st);
+    else launch_multi_s<FLUX, false>(d, r, map, nreq, nblocks, stage, tick_step, m, st);
 }
 
 hipError_t wcnst_launch_multi(const wcnst_desc* d, const void* reqs, const int* map, int nreq, int nblocks, int stage,
-                              int tick_step, int ty, bool general, hipStream_t st)
+                              int tick_step, MultiShape m, hipStream_t st)
 {
     const ReqGrid* r = (const ReqGrid*)reqs;
-    if (d->flux == WCNST_LF) launch_multi_f<FLUX_LF>(d, r, map, nreq, nblocks, stage, tick_step, ty, general, st);
+    if (d->flux == WCNST_LF) launch_multi_f<FLUX_LF>(d, r, map, nreq, nblocks, stage, tick_step, m, st);
     else if (d->flux == WCNST_VANLEER)
-        launch_multi_f<FLUX_VL>(d, r, map, nreq, nblocks, stage, tick_step, ty, general, st);
-    else launch_multi_f<FLUX_ROE>(d, r, map, nreq, nblocks, stage, tick_step, ty, general, st);
+        launch_multi_f<FLUX_VL>(d, r, map, nreq, nblocks, stage, tick_step, m, st);
+    else launch_multi_f<FLUX_ROE>(d, r, map, nreq, nblocks, stage, tick_step, m, st);
     return hipGetLastError();
 }
 

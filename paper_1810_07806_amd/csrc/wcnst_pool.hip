@@ -247,10 +247,10 @@ static wcnst_status issue_dim(wcnst_pool* p, int ndim, const std::vector<int>& a
         WCNST_HIP_TRY(wcnst_launch_line_settle_multi(p->d_req[0], n, st));
         return WCNST_OK;
     }
+    const MultiShape shape{ty, general, wcnst_short_segments(blocks, ty, p->slots)};
     for (int64_t s = 0; s < steps; ++s)
         for (int stage = 0; stage < 3; ++stage)
-            WCNST_HIP_TRY(wcnst_launch_multi(&p->scheme, p->d_req[1], map, n, blocks, stage, (int)(s & 1), ty, general,
-                                             st));
+            WCNST_HIP_TRY(wcnst_launch_multi(&p->scheme, p->d_req[1], map, n, blocks, stage, (int)(s & 1), shape, st));
     return WCNST_OK;
 }
 

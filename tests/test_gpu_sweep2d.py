@@ -1,5 +1,6 @@
-"""GPU: the four-rows-at-a-time 2D stage against the oracle, bit for bit, at
-the edges of its strips, segments and turns."""
+"""GPU: the 2D stage (short segments whole, longer ones four rows at a time)
+against the oracle, bit for bit, at the edges of its strips, segments and
+turns."""
 from __future__ import annotations
 
 import numpy as np
@@ -19,8 +20,10 @@ def torch():
     return T
 
 
-# segments of one turn, of part of a turn, one row past a turn, the whole grid
-@pytest.mark.parametrize("rows", [1, 3, 4, 5, 8, 9, 0])
+# whole segments of one row up to the most (12: two staged rows per wavefront
+# from 5, two midpoint rows from 5, three from 11), one row past it, and whole
+# turns of a longer segment
+@pytest.mark.parametrize("rows", [1, 3, 4, 5, 8, 9, 11, 12, 13, 16, 0])
 @pytest.mark.parametrize("nx,ny", [(5, 5), (61, 8), (62, 9), (123, 14)])
 @pytest.mark.parametrize("bc", ["zero_gradient", "periodic", "reflect"])
 def test_rhs_flags_and_steps_equal_the_oracle(orc, torch, nx, ny, rows, bc):
@@ -41,5 +44,22 @@ def test_rhs_flags_and_steps_equal_the_oracle(orc, torch, nx, ny, rows, bc):
         assert np.array_equal(a, b)
     r = orc.solve(p, U, cfl=0.5, max_steps=3)
     s.solve(Ug, cfl=0.5, max_steps=3)
+    assert s.status()["t"] == r["t"] and np.array_equal(Ug.cpu().numpy(), r["U"])
+    s.close()
+
+
+# more workgroups than the device takes at once: short segments by turns (4),
+# whole turns (16) and a last turn of one row (13)
+@pytest.mark.parametrize("rows", [4, 13, 16])
+def test_crowded_launches_equal_the_oracle(orc, torch, rows):
+    from paper_1810_07806_amd.wcnst import Solver
+    d, U = W.random_euler2d(np.random.default_rng(7), 400, 301)
+    d.update(bc_x="periodic", bc_y="zero_gradient")
+    p = orc.problem(d)
+    r = orc.solve(p, U, cfl=0.5, max_steps=2)
+    s = Solver(d)
+    s.set_tuning(rows)
+    Ug = s.new_state(U)
+    s.solve(Ug, cfl=0.5, max_steps=2)
     assert s.status()["t"] == r["t"] and np.array_equal(Ug.cpu().numpy(), r["U"])
     s.close()
