@@ -525,14 +525,6 @@ __device__ __forceinline__ void fix_row(const Params& P, int ky, int kA, int kB,
     }
 }
 
-// A result another launch reads, written through to memory: at the end of a
-// launch the XCDs' L2 caches hold no dirty lines that the next one would wait
-// for (0.3 to 0.9 us of a 256^2 stage).
-__device__ __forceinline__ void store_agent(double* p, double v)
-{
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 template <int NV>
 __device__ __forceinline__ void store_row(double (*slot)[XW], int lane, bool hasB, const double (&ra)[NV],
                                           const double (&rb)[NV])

@@ -177,7 +177,7 @@ __device__ __forceinline__ void line_stage(const Tile1D<DIFF>& T, const LineLds<
         if constexpr (SYS == SYS_EULER) node_quantities<NV>(o, P.gamma, N);
         if (out) {
 #pragma unroll
-            for (int v = 0; v < NV; ++v) out[(size_t)v * P.nx + p] = o[v];
+            for (int v = 0; v < NV; ++v) store_agent(&out[(size_t)v * P.nx + p], o[v]);
         } else {
             put_position<SYS, NV>(lds, So, p - base, o, N);
         }
@@ -322,7 +322,7 @@ __device__ __forceinline__ void line_tile_step(const double* __restrict__ in, do
     }
     init_weight_table();  // (its barrier also publishes the positions)
     unsigned long long bad = ~0ull, speed = 0ull;
-#pragma unroll 1
+#pragma unroll
     for (int stage = 0; stage < 3; ++stage) {
         line_stage<SYS, NV, FLUX, SCHEME, CHAR, DIFF, true>(T, lds, stage, dt, step, P, stage == 2 ? out : nullptr,
                                                             bad, speed);
@@ -450,7 +450,7 @@ line_solo(double* __restrict__ U, Ctrl* __restrict__ ctrl, Params P, LineStep A,
         unsigned long long bad = ~0ull, speed = 0ull;
         bool whole = true;
         const int next = slot == 2 ? 0 : slot + 1;
-#pragma unroll 1
+#pragma unroll
         for (int stage = 0; stage < 3; ++stage) {
             if (stage == 2 && first_bad != ~0ull) {
                 whole = false;
