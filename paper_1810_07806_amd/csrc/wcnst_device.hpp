@@ -521,11 +521,17 @@ __device__ __forceinline__ double* weight_table()
     return tab;
 }
 
-// The 24 threads from `first` on fill it.
-__device__ __forceinline__ void init_weight_table(unsigned first = 0)
+// The 24 threads from `first` on fill it (a barrier must follow: kernels
+// call it while their first loads are in flight).
+__device__ __forceinline__ void put_weight_table(unsigned first = 0)
 {
     const unsigned k = threadIdx.x - first;
     if (k < 24) weight_table()[k] = teno_weight(k / 3, k % 3);
+}
+
+__device__ __forceinline__ void init_weight_table()
+{
+    put_weight_table();
     __syncthreads();
 }
 

@@ -739,6 +739,7 @@ __device__ __forceinline__ void sweep2d_block(const double* __restrict__ U, cons
         double ra[2][NV], rb[2][NV];
         load(y0 - 4 + w, ra[0], rb[0]);
         load(y0 + w, ra[1], rb[1]);
+        put_weight_table((WG_WAVES - 1) * WAVE);
         if constexpr (MODE == MODE_STAGE) {
             if (threadIdx.x == 0) {
                 double dt = 0.0;
@@ -751,7 +752,7 @@ __device__ __forceinline__ void sweep2d_block(const double* __restrict__ U, cons
         stage_row(y0 - 4 + w, 1 + w, ra[0], rb[0]);
         stage_row(y0 + w, 5 + w, ra[1], rb[1]);
     }
-    init_weight_table();  // (its barrier also publishes the rows and the record)
+    __syncthreads();
     if (MODE == MODE_STAGE && !s_go) return;  // one value for the whole workgroup
     unsigned long long smax_loc = 0ull;
     int s0 = 0;  // slot of row i0-1
@@ -1025,6 +1026,7 @@ __device__ __forceinline__ void sweep2d_short_block(const double* __restrict__ U
         const bool second = w + ON_WAVES < n + 8;
         if (w < n + 8) load(w, ra[0], rb[0]);
         if (second) load(w + ON_WAVES, ra[1], rb[1]);
+        put_weight_table((ON_WAVES - 1) * WAVE);
         if constexpr (MODE == MODE_STAGE) {
             if (threadIdx.x == 0) {
                 double dt = 0.0;
@@ -1037,7 +1039,7 @@ __device__ __forceinline__ void sweep2d_short_block(const double* __restrict__ U
         if (w < n + 8) put(w, ra[0], rb[0]);
         if (second) put(w + ON_WAVES, ra[1], rb[1]);
     }
-    init_weight_table((ON_WAVES - 1) * WAVE);  // (its barrier also publishes the rows and the record)
+    __syncthreads();
     if (MODE == MODE_STAGE && !s_go) return;  // one value for the whole workgroup
     double un[NV];
     {

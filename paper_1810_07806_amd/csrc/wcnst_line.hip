@@ -203,7 +203,7 @@ __device__ __forceinline__ void line_stage(const Tile1D<DIFF>& T, const LineLds<
 
 // Loads the tile's positions (cells, ghosts) from U and forms their Roe
 // quantities.  (No barrier.)  ONE: at most two positions per thread, both
-// loads in flight.
+// loads in flight, and the weight table.
 template <int SYS, int NV, int DIFF, bool ONE>
 __device__ __forceinline__ void line_load(const Tile1D<DIFF>& T, const LineLds<SYS, NV, DIFF>& lds,
                                           const double* __restrict__ U, const Params& P)
@@ -232,6 +232,7 @@ __device__ __forceinline__ void line_load(const Tile1D<DIFF>& T, const LineLds<S
         double u[2][NV];
         if (i < n) fetch(i, u[0]);
         if (k < n) fetch(k, u[1]);
+        put_weight_table(TILE_THREADS - WAVE);
 #pragma unroll 1
         for (int m = 0; m < 2; ++m) {
             if (m * TILE_THREADS + i >= n) break;
@@ -320,7 +321,7 @@ __device__ __forceinline__ void line_tile_step(const double* __restrict__ in, do
         nx->smax_bits = 0ull;
         ctrl->speed[after] = 0ull;
     }
-    init_weight_table();  // (its barrier also publishes the positions)
+    __syncthreads();
     unsigned long long bad = ~0ull, speed = 0ull;
 #pragma unroll
     for (int stage = 0; stage < 3; ++stage) {
