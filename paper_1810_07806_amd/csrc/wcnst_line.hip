@@ -203,10 +203,10 @@ __device__ __forceinline__ void line_stage(const Tile1D<DIFF>& T, const LineLds<
 
 // Loads the tile's positions (cells, ghosts) from U and forms their Roe
 // quantities.  (No barrier.)  ONE: at most two positions per thread, both
-// loads in flight, and the weight table.
-template <int SYS, int NV, int DIFF, bool ONE>
+// loads in flight, then the caller's (read) and the weight table.
+template <int SYS, int NV, int DIFF, bool ONE, class READ>
 __device__ __forceinline__ void line_load(const Tile1D<DIFF>& T, const LineLds<SYS, NV, DIFF>& lds,
-                                          const double* __restrict__ U, const Params& P)
+                                          const double* __restrict__ U, const Params& P, const READ& read)
 {
     const int base = T.base(), n = T.positions();
     const auto store = [&](int i, double (&u)[NV]) {
@@ -232,6 +232,7 @@ __device__ __forceinline__ void line_load(const Tile1D<DIFF>& T, const LineLds<S
         double u[2][NV];
         if (i < n) fetch(i, u[0]);
         if (k < n) fetch(k, u[1]);
+        read();
         put_weight_table(TILE_THREADS - WAVE);
 #pragma unroll 1
         for (int m = 0; m < 2; ++m) {
@@ -284,24 +285,42 @@ __device__ __forceinline__ bool line_dt(const LineStep& A, double t, unsigned lo
 }
 
 // One SSP-RK3 step of tile t of a line cut every w cells: in -> out.
-template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, int DIFF>
+template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, int DIFF, bool AHEAD>
 __device__ __forceinline__ void line_tile_step(const double* __restrict__ in, double* __restrict__ out,
                                                Ctrl* __restrict__ ctrl, const Params& P, const LineStep& A, int t,
                                                int w, double* mem)
 {
     const Tile1D<DIFF> T(t, w, P.nx, P.bc_x);
     const LineLds<SYS, NV, DIFF> lds{mem, LINE_CAP};
-    line_load<SYS, NV, DIFF, true>(T, lds, in, P);
     // Every workgroup takes the same decision from the record: an earlier
     // step's failure and the final time are fixed when the launch starts
     // (a failure in this launch has a key of this step; the status follows
-    // in the next launch).
-    const StepRec* cur = &ctrl->rec[A.parity];
-    const long long step = cur->step;
-    const double time = cur->t;
-    const unsigned long long key = ctrl->bad_key, sp0 = ctrl->speed[0], sp1 = ctrl->speed[1], sp2 = ctrl->speed[2];
+    // in the next launch).  AHEAD: read with the state, in one round trip
+    // (Shu-Osher 2048 cells 40.1 -> 39.3 ms); the multi-line launch, which has
+    // its table entry to wait for, measured 1 % slower so.
+    long long step = 0;
+    double time = 0.0;
+    unsigned long long key = 0, sp0 = 0, sp1 = 0, sp2 = 0;
+    int done = 0, status = 0;
+    const auto record = [&]() {
+        const StepRec* cur = &ctrl->rec[A.parity];
+        step = cur->step;
+        time = cur->t;
+        key = ctrl->bad_key;
+        sp0 = ctrl->speed[0];
+        sp1 = ctrl->speed[1];
+        sp2 = ctrl->speed[2];
+        done = ctrl->done;
+        status = ctrl->status;
+    };
+    if constexpr (AHEAD) {
+        line_load<SYS, NV, DIFF, true>(T, lds, in, P, record);
+    } else {
+        line_load<SYS, NV, DIFF, true>(T, lds, in, P, [] {});
+        record();
+    }
     const bool lead = t == 0 && threadIdx.x == 0;
-    if (ctrl->done != 0 || ctrl->status != 0) return;
+    if (done != 0 || status != 0) return;
     if ((long long)(key >> 36) < 3 * step) {
         if (lead) ctrl->status = (int)WCNST_E_NONPHYSICAL;
         return;
@@ -352,7 +371,7 @@ line_step(const double* __restrict__ in, double* __restrict__ out, Ctrl* __restr
           int width)
 {
     __shared__ double mem[LineLds<SYS, NV, DIFF>::PER * LINE_CAP];
-    line_tile_step<SYS, NV, FLUX, SCHEME, CHAR, DIFF>(in, out, ctrl, P, A, (int)blockIdx.x, width, mem);
+    line_tile_step<SYS, NV, FLUX, SCHEME, CHAR, DIFF, true>(in, out, ctrl, P, A, (int)blockIdx.x, width, mem);
 }
 
 // One step of many independent 1D Euler lines: block b takes a tile of the
@@ -385,8 +404,8 @@ line_step_multi(const ReqGrid* __restrict__ reqs, const int* __restrict__ map, i
     A.fixed_dt = 0.0;
     A.parity = (R.parity0 + tick_step) & 1;
     const bool at_home = A.parity == R.home;
-    line_tile_step<SYS_EULER, 3, FLUX, SCHEME, CHAR, DIFF_MND>(at_home ? R.U : R.U1, at_home ? R.U1 : R.U, R.ctrl, R.P,
-                                                              A, b - R.blk0, R.width, mem);
+    line_tile_step<SYS_EULER, 3, FLUX, SCHEME, CHAR, DIFF_MND, false>(at_home ? R.U : R.U1, at_home ? R.U1 : R.U,
+                                                                     R.ctrl, R.P, A, b - R.blk0, R.width, mem);
 }
 
 // Many steps of a short line in one launch: one workgroup holds the whole
@@ -407,7 +426,7 @@ line_solo(double* __restrict__ U, Ctrl* __restrict__ ctrl, Params P, LineStep A,
     const int tid = (int)threadIdx.x;
     const Tile1D<DIFF> T(0, P.nx, P.nx, P.bc_x);
     LineLds<SYS, NV, DIFF> lds{mem, cap};
-    line_load<SYS, NV, DIFF, false>(T, lds, U, P);
+    line_load<SYS, NV, DIFF, false>(T, lds, U, P, [] {});
     int p = A.parity;
     const long long step0 = ctrl->rec[p].step;
     double time = ctrl->rec[p].t, before = time, dt = 0.0;
