@@ -27,7 +27,7 @@ arrival times.
 `--workload tubes`: 4096 independent 1D Euler shock tubes of uneven length
 (N log-uniform in [256, 8192], random left/right states, t = 0.15, Roe,
 characteristic TENO, MND) advanced to their final times by the batched
-solver (graph-captured ticks of multi-instance stage launches).  One benchmark step = the
+solver (graph-captured ticks of multi-instance step launches).  One benchmark step = the
 whole batch solved once.  Also times the plain one-solve-per-instance path
 on a seeded subset of the same tubes and the CPU oracle on a bounded sample.
 """
@@ -534,7 +534,7 @@ def bench_singles() -> dict:
     linear advection of a sine plus a square pulse (N = 200, periodic, to
     t = 2) and the Shu-Osher problem (N = 2048, zero gradient, to t = 1.8),
     both WCNS-T TENO with MND and SSP-RK3 at CFL 0.5.  One grid fills a
-    handful of CUs, so there is no roofline claim: each stage costs about
+    handful of CUs, so there is no roofline claim: each step costs about
     one wavefront's latency."""
     import torch
 

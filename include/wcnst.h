@@ -184,12 +184,13 @@ wcnst_status wcnst_status_sync(wcnst_solver* s, double* t, int64_t* steps, int32
 wcnst_status wcnst_reset(wcnst_solver* s, double t, int64_t steps);
 
 /* Launch shape of the 2D stage kernel: strips of 61 columns, each cut into
- * segments of rows_per_segment rows (>= 1); a workgroup of four wavefronts
- * advances a segment four rows at a time.  The default, chosen at
- * wcnst_create from the grid and the device's CU count, is a multiple of
- * four in [4, 64]: as tall as keeps every CU at work.  0 restores it.
- * Changes only the work decomposition, never the results.  Negative values:
- * WCNST_E_INVALID_ARG. */
+ * segments of rows_per_segment rows (>= 1).  A segment of up to 12 rows is
+ * worked whole by a workgroup of twelve wavefronts where that is the faster
+ * (grids too small to fill the CUs), any other by four wavefronts, four rows
+ * at a time.  The default, chosen at wcnst_create from the grid and the
+ * device's CU count, is the height of least estimated time: 1 to 12, or a
+ * multiple of four up to 64.  0 restores it.  Changes only the work
+ * decomposition, never the results.  Negative values: WCNST_E_INVALID_ARG. */
 wcnst_status wcnst_set_tuning(wcnst_solver* s, int32_t rows_per_segment);
 
 /* Launch shape of the stage kernels (wcnst_step / wcnst_solve).  2D: strips
@@ -197,8 +198,8 @@ wcnst_status wcnst_set_tuning(wcnst_solver* s, int32_t rows_per_segment);
  * later ones (to nseg in all, the last one ragged) rows2.  Two heights are
  * used only without an explicit tuning, for grids of 1.5 to 2 segments of 35
  * rows per SIMD; the first-height segments are then worked by two workgroups
- * each (half the rows each), the others by one, and their rows adapt
- * (wcnst_stage_layout).  1D: strips of a right-hand side only (rows and
+ * each, the others by one, bounds rounded down to multiples of four rows, and
+ * their rows adapt (wcnst_stage_layout).  1D: strips of a right-hand side only (rows and
  * segments 1; a step is one launch).  Right-hand-side launches use one
  * height. */
 wcnst_status wcnst_stage_shape(const wcnst_solver* s, int32_t* strips, int32_t* rows1, int32_t* rows2,

@@ -1,14 +1,13 @@
 """Autotuners for the launch decomposition of 2D solves and batched solves.
 
-2D solves (`tune_rows`): the height of the row segment that one 64-lane
-wavefront marches up in a strip of 61 columns.  Taller segments compute
-fewer halo y-midpoints (3 per segment and column), shorter ones give more
-wavefronts; the default two-height shape (0) balances the two wavefronts
-that share a SIMD.  A copy of the state is first advanced by `pre_steps`
+2D solves (`tune_rows`): the height of the row segment that one workgroup
+takes in a strip of 61 columns.  Taller segments compute fewer halo
+y-midpoints (3 per segment and column), shorter ones give more workgroups;
+the default (0) is the height of least estimated time (two heights on grids
+of 1.5 to 2 segments of 35 rows per SIMD).  A copy of the state is first advanced by `pre_steps`
 steps with the default shape (the ranking of the shapes changes as the
-solution develops: timed at the initial state alone, 35-row segments beat
-the default by 3 % and then lose by 5 % over 200 steps of the 2048^2
-benchmark); each candidate then runs a few steps with a fixed,
+solution develops: segments where the stencil-cut test runs in full take
+longer); each candidate then runs a few steps with a fixed,
 tiny dt on that state, and a candidate replaces the default only when it
 is faster by `margin`.  The solver's step record is restored afterwards.
 
@@ -29,10 +28,10 @@ Candidates are timed on a proxy of the real batch: the same instances run
 to a fraction of their final times.  Step counts scale with t_final, so the
 proxy keeps the relative lengths of the instances while costing a few
 percent of the real run.  The search is greedy: the tick length first
-(stage launches only), then the switch point at 8 waves x 1 instance, then
-the workgroup shape at the best switch point (skipped when stage launches
+(step launches only), then the switch point at 8 waves x 1 instance, then
+the workgroup shape at the best switch point (skipped when step launches
 to the end win).  A persistent winner is confirmed on a longer proxy
-against stage launches to the end: on the short one its share of the run
+against step launches to the end: on the short one its share of the run
 (the tail) is larger than on the real run, and measured batches of shock
 tubes (N in [256, 8192] and in [64, 512]) ran slower with it.
 
@@ -168,7 +167,7 @@ def tune_batch(batch, Ug_init, t_final, cfl: float = 0.5, proxy: float = 0.05, t
                 r = trial(dict(cfg, waves_per_group=w, instances_per_group=g))
                 best = r if r["ms"] < best["ms"] else best
         # the short proxy favours the persistent finish (its tail is a larger
-        # share of the run): confirm against stage launches to the end on a
+        # share of the run): confirm against step launches to the end on a
         # proxy of `confirm` of the final times
         tf_short = tf
         tf = tf_short / proxy * confirm

@@ -5,14 +5,14 @@
 // Each request advances with exactly the arithmetic of wcnst_solve, so its
 // result does not depend on what else is in the pool or on when it joined.
 // One tick advances every active 1D request by up to `steps_1d` and every
-// active 2D request by up to `steps_2d` SSP-RK3 steps, with 3 x steps stage
-// launches per dimension, each covering the strips
-// (1D, caller's stream) or row segments (2D, the pool's own stream) of all
-// active grids of that dimension; a grid has its own table row, control
-// block, dt and step parity, and grids that reach t_final stop inside the
-// launches.  Kernel boundaries order the stages, so no wave ever waits for
-// another.  The tick is synchronous: it ends with both streams drained and
-// the per-request outcome (finished, status, t, steps) read back.
+// active 2D request by up to `steps_2d` SSP-RK3 steps, with one launch per 1D
+// step and three per 2D step, each covering the tiles (1D, caller's stream)
+// or row segments (2D, the pool's own stream) of all active grids of that
+// dimension; a grid has its own table row, control block, dt and step parity,
+// and grids that reach t_final stop inside the launches.  Kernel boundaries
+// order the steps and stages, so no wave ever waits for another.  The tick is
+// synchronous: it ends with both streams drained and the per-request outcome
+// (finished, status, t, steps) read back.
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -190,7 +190,7 @@ extern "C" wcnst_status wcnst_pool_admit(wcnst_pool* p, const wcnst_desc* d, dou
 
 static bool reached(double t_final, double t) { return t_final - t <= 1e-12 * t_final; }
 
-// Table rows of the active grids of one dimension and their stage launches.
+// Table rows of the active grids of one dimension and their launches.
 static wcnst_status issue_dim(wcnst_pool* p, int ndim, const std::vector<int>& act, int64_t steps, hipStream_t st)
 {
     if (act.empty()) return WCNST_OK;

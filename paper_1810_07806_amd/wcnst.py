@@ -322,7 +322,7 @@ def split_flags(desc: dict, fl):
 
 class Batch:
     """Many independent 1D Euler problems advanced together in graph-captured
-    ticks of multi-instance stage launches.
+    ticks of multi-instance step launches.
 
     States are packed into one device tensor (``pack``/``unpack``); instance i
     occupies ``offsets[i] : offsets[i] + 3 * nx_i`` with layout [v][nx_i]."""
@@ -374,7 +374,7 @@ class Batch:
 
     def set_persist(self, switch_strips: int = 0, waves_per_group: int = 8, instances_per_group: int = 1):
         """Persistent finish once the running instances hold at most
-        switch_strips strips (0: stage launches to the end)."""
+        switch_strips strips (0: step launches to the end)."""
         _check(lib().wcnst_batch_set_persist(self._h, int(switch_strips), int(waves_per_group),
                                              int(instances_per_group)))
 
