@@ -125,7 +125,7 @@ static wcnst_status batch_check(const wcnst_desc* descs, int32_t n, long long* t
 {
     if (!descs || n < 1) return wcnst_fail(WCNST_E_INVALID_ARG, "need at least one descriptor");
     const wcnst_desc& a = descs[0];
-    long long off = 0, nstr = 0;
+    long long off = 0, nstr = 0, npair = 0;
     if (offs) offs->assign((size_t)n + 1, 0);
     for (int i = 0; i < n; ++i) {
         const wcnst_desc& d = descs[i];
@@ -139,11 +139,14 @@ static wcnst_status batch_check(const wcnst_desc* descs, int32_t n, long long* t
             return wcnst_fail(WCNST_E_INVALID_ARG, "descriptor %d: scheme parameters differ from descriptor 0", i);
         if (offs) (*offs)[i] = off;
         off += ((long long)NV * d.nx + 63) / 64 * 64;  // 512-byte aligned instances
-        nstr += wcnst_line_tiles(d.diff, d.nx);
+        nstr += wcnst_line_tiles(d.diff, d.nx, false);
+        npair += wcnst_line_tiles(d.diff, d.nx, true);
     }
     if (offs) (*offs)[n] = off;
     if (total) *total = off;
-    if (strips) *strips = nstr;
+    // blocks of the largest launch: every instance's tiles, or tiles of two
+    // threads a midpoint where a few instances take them (set_tiles)
+    if (strips) *strips = std::max(nstr, std::min(npair, (long long)WCNST_PAIR_TILES));
     return WCNST_OK;
 }
 
@@ -254,6 +257,23 @@ extern "C" wcnst_status wcnst_batch_stats(const wcnst_batch* b, int32_t* ticks, 
     return WCNST_OK;
 }
 
+// Tile widths and first blocks of the table rows [0, n); the blocks of a
+// launch and whether its tiles take two threads a midpoint.
+static int set_tiles(ReqGrid* tab, int n, bool* pair)
+{
+    long long tiles = 0;
+    for (int j = 0; j < n; ++j) tiles += wcnst_line_tiles(WCNST_MND, tab[j].P.nx, true);
+    *pair = wcnst_line_pair(tiles);
+    int blocks = 0;
+    for (int j = 0; j < n; ++j) {
+        tab[j].nstrips = wcnst_line_tiles(WCNST_MND, tab[j].P.nx, *pair);
+        tab[j].width = wcnst_line_width(WCNST_MND, tab[j].P.nx, *pair);
+        tab[j].blk0 = blocks;
+        blocks += tab[j].nstrips;
+    }
+    return blocks;
+}
+
 static bool reached(double t_final, double t) { return t_final - t <= 1e-12 * t_final; }
 
 static const StepRec& newest(const Ctrl& c) { return c.rec[0].step >= c.rec[1].step ? c.rec[0] : c.rec[1]; }
@@ -263,11 +283,12 @@ static const StepRec& newest(const Ctrl& c) { return c.rec[0].step >= c.rec[1].s
 // (a tick of fewer steps than steps_per_tick is launched directly).  A
 // replaced graph is retired, not destroyed: the previous tick, which may
 // have launched it, can still be running.
-static wcnst_status run_tick(wcnst_batch* b, int nreq, int blocks, int steps, bool table_changed, long long tick)
+static wcnst_status run_tick(wcnst_batch* b, int nreq, int blocks, bool pair, int steps, bool table_changed,
+                             long long tick)
 {
     if (steps != b->steps_per_tick) {
         for (int s = 0; s < steps; ++s)
-            WCNST_HIP_TRY(wcnst_launch_line_multi(&b->d0, b->d_req, b->d_map, nreq, blocks, s & 1, b->stream));
+            WCNST_HIP_TRY(wcnst_launch_line_multi(&b->d0, b->d_req, b->d_map, nreq, blocks, s & 1, pair, b->stream));
         return WCNST_OK;
     }
     if (!b->exec || table_changed) {
@@ -279,7 +300,7 @@ static wcnst_status run_tick(wcnst_batch* b, int nreq, int blocks, int steps, bo
         WCNST_HIP_TRY(hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal));
         hipError_t le = hipSuccess;
         for (int s = 0; s < steps && le == hipSuccess; ++s)
-            le = wcnst_launch_line_multi(&b->d0, b->d_req, b->d_map, nreq, blocks, s & 1, b->cap);
+            le = wcnst_launch_line_multi(&b->d0, b->d_req, b->d_map, nreq, blocks, s & 1, pair, b->cap);
         hipError_t ce = hipStreamEndCapture(b->cap, &g);
         if (le != hipSuccess || ce != hipSuccess)
             return wcnst_fail(WCNST_E_HIP, "graph capture failed: %s / %s", hipGetErrorString(le),
@@ -323,8 +344,6 @@ extern "C" wcnst_status wcnst_batch_solve(wcnst_batch* b, double* U, const doubl
         wcnst_make_params(&d, &q.P);
         q.t_final = t_final[i];
         q.cfl = cfl;
-        q.nstrips = wcnst_line_tiles(d.diff, d.nx);
-        q.width = wcnst_line_width(d.diff, d.nx);
         q.parity0 = 0;
         q.home = 0;
     }
@@ -344,12 +363,9 @@ extern "C" wcnst_status wcnst_batch_solve(wcnst_batch* b, double* U, const doubl
     std::vector<int> parity((size_t)n, 0);
 
     // table of all rows; control blocks reset and initial speeds in one launch
-    int blocks = 0;
-    for (int i = 0; i < n; ++i) {
-        b->h_req[i] = rows[(size_t)i];
-        b->h_req[i].blk0 = blocks;
-        blocks += rows[(size_t)i].nstrips;
-    }
+    for (int i = 0; i < n; ++i) b->h_req[i] = rows[(size_t)i];
+    bool pair = false;
+    int blocks = set_tiles(b->h_req, n, &pair);
     WCNST_HIP_TRY(hipMemcpyAsync(b->d_req, b->h_req, sizeof(ReqGrid) * (size_t)n, hipMemcpyHostToDevice, b->stream));
     WCNST_HIP_TRY(hipEventRecord(b->ev0, b->stream));
     WCNST_HIP_TRY(wcnst_launch_multi_init(1, b->d_req, n, b->stream));
@@ -372,20 +388,18 @@ extern "C" wcnst_status wcnst_batch_solve(wcnst_batch* b, double* U, const doubl
             // buffer not used by the last upload (the one before it has
             // completed: the host waited on a later tick's snapshot)
             ReqGrid* tab = tabs[uploads & 1];
-            blocks = 0;
             for (size_t j = 0; j < active.size(); ++j) {
                 const int i = active[j];
                 tab[j] = rows[(size_t)i];
-                tab[j].blk0 = blocks;
                 tab[j].parity0 = parity[(size_t)i];
-                blocks += rows[(size_t)i].nstrips;
             }
+            blocks = set_tiles(tab, (int)active.size(), &pair);
             WCNST_HIP_TRY(hipMemcpyAsync(b->d_req, tab, sizeof(ReqGrid) * active.size(), hipMemcpyHostToDevice,
                                          b->stream));
             WCNST_HIP_TRY(wcnst_launch_block_map(b->d_req, (int)active.size(), blocks, b->d_map, b->stream));
             uploads += 1;
         }
-        wcnst_status st = run_tick(b, (int)active.size(), blocks, steps, changed, k);
+        wcnst_status st = run_tick(b, (int)active.size(), blocks, pair, steps, changed, k);
         if (st) {
             (void)hipStreamSynchronize(b->stream);
             reap_retired(b, -1);

@@ -214,13 +214,17 @@ struct Tile1D {
 // thread of its own.
 constexpr int TILE_THREADS = 256;
 constexpr int LINE_CAP = TILE_THREADS + 8;  // positions of a tile, at most TILE_THREADS + 2 REACH - 2 G + 1
-template <int DIFF>
+// PAIR: two threads a midpoint, so half as many to a tile.
+constexpr int PAIR_FACES = TILE_THREADS / 2;
+constexpr int PAIR_CAP = PAIR_FACES + 8;
+template <int DIFF, bool PAIR = false>
 WCNST_HD int line_tile_width(int nx)
 {
     using T = Tile1D<DIFF>;
+    constexpr int FACES = PAIR ? PAIR_FACES : TILE_THREADS;
     // one tile: nx + 2 REACH positions; else W + 4 REACH cells in stage 0
-    if (nx + 2 * T::REACH <= TILE_THREADS) return nx;
-    constexpr int W = TILE_THREADS - 4 * T::REACH - 2 * T::G + 1;
+    if (nx + 2 * T::REACH <= FACES) return nx;
+    constexpr int W = FACES - 4 * T::REACH - 2 * T::G + 1;
     const int nt = (nx + W - 1) / W;
     return (nx + nt - 1) / nt;
 }
@@ -662,6 +666,18 @@ WCNST_HD void interp_pair(double w0, double w1, double w2, double w3, double w4,
                              P, mR);
 }
 
+// One side alone: u_L from n0 .. n4 = w0 .. w4, u_R from n0 .. n4 = w5 .. w1.
+// The mirrored differences are the negated ones of interp_pair, exactly, so
+// every operation has the same operands and u_R the same bits.
+template <int SCHEME>
+WCNST_HD double interp_one(double n0, double n1, double n2, double n3, double n4, const Params& P)
+{
+    const double d0 = n1 - n0, d1 = n2 - n1, d2 = n3 - n2, d3 = n4 - n3;
+    unsigned m;
+    return interp_side<SCHEME>(n2, fma(3.0, d1, -d0) * 0.5, (n3 - n1) * 0.5, fma(3.0, d2, -d3) * 0.5, d1 - d0,
+                               d2 - d1, d3 - d2, P, m);
+}
+
 // ------------------------------------------------------------ Euler
 
 // Ideal gas p = (gamma - 1)(E - |m|^2 / (2 rho)).
@@ -1057,6 +1073,68 @@ template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, class ST>
 WCNST_HD void face_flux(ST& st, const Params& P, double (&F)[NV], unsigned& fb)
 {
     face_flux<SYS, NV, FLUX, SCHEME, CHAR>(st, P, F, fb, [&](auto& E) { midpoint_eigen<NV>(st, P, E); });
+}
+
+#if defined(__HIP_DEVICE_COMPILE__)
+// The neighbour lane's value (lane ^ 1).
+__device__ __forceinline__ double pair_swap(double x)
+{
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_mov_dpp((int)b, 0xB1, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0xB1, 0xF, 0xF, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+#else
+__device__ double pair_swap(double x);
+#endif
+
+// The flux at a midpoint by two neighbouring lanes, one side each: n holds
+// the five nodes of the lane's side, centre third (right: the mirrored ones),
+// and both lanes receive F.  The operations of face_flux on each value.
+template <int NV, int FLUX, int SCHEME, bool CHAR, class BASIS>
+__device__ __forceinline__ void face_flux_pair(const double (&n)[5][NV], bool right, const Params& P, double (&F)[NV],
+                                               const BASIS& basis)
+{
+    double mine[NV];
+    if constexpr (CHAR) {
+        Eigen<NV> E;
+        basis(E);
+        double w[NV][5];
+#pragma unroll
+        for (int m = 0; m < 5; ++m)
+#pragma unroll
+            for (int k = 0; k < NV; ++k) {
+                double acc = 0.0;
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    if (Eigen<NV>::L_zero(k, v)) continue;
+                    acc = v == 0 ? E.L(k, v) * n[m][v] : fma(E.L(k, v), n[m][v], acc);
+                }
+                w[k][m] = acc;
+                keep_here(w[k][m]);
+            }
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            const double x = interp_one<SCHEME>(w[k][0], w[k][1], w[k][2], w[k][3], w[k][4], P);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                if (Eigen<NV>::R_zero(v, k)) continue;
+                mine[v] = k == 0 ? E.R(v, k) * x : fma(E.R(v, k), x, mine[v]);
+                keep_here(mine[v]);
+            }
+        }
+    } else {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) mine[v] = interp_one<SCHEME>(n[0][v], n[1][v], n[2][v], n[3][v], n[4][v], P);
+    }
+    double UL[NV], UR[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const double other = pair_swap(mine[v]);
+        UL[v] = right ? other : mine[v];
+        UR[v] = right ? mine[v] : other;
+    }
+    euler_num_flux<NV, FLUX>(UL, UR, P.gamma, F);
 }
 
 // Normal flux of a node from its quantities (the operations of euler_flux).

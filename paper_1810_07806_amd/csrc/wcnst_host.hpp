@@ -47,12 +47,16 @@ hipError_t wcnst_launch_multi(const wcnst_desc* d, const void* reqs, const int* 
 // parity; and the end of a run of steps: the newest state into U (from U1
 // where the newest record's parity is not the line's home parity), the
 // status of a failure in the last step, the CFL speed into the newest record.
-int wcnst_line_width(int diff, int nx);
-int wcnst_line_tiles(int diff, int nx);
+// (pair: tiles of two threads a midpoint, MND only, for which wcnst_line_pair
+// has the rule, from the launch's tiles at that width).
+int wcnst_line_width(int diff, int nx, bool pair);
+int wcnst_line_tiles(int diff, int nx, bool pair);
+constexpr int WCNST_PAIR_TILES = 256;
+bool wcnst_line_pair(long long tiles);
 hipError_t wcnst_launch_line_step(const wcnst_desc* d, const wcnst::Params& P, wcnst::Ctrl* ctrl, const double* in,
                                   double* out, const wcnst::LineStep& A, hipStream_t st);
 hipError_t wcnst_launch_line_multi(const wcnst_desc* d, const void* reqs, const int* map, int nreq, int nblocks,
-                                   int tick_step, hipStream_t st);
+                                   int tick_step, bool pair, hipStream_t st);
 // Whether one workgroup runs the whole line, and up to `steps` steps of it in
 // one launch, in place (open: the start of a solve or step call; nothing
 // else has to be launched before it).

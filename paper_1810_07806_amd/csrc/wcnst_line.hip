@@ -74,7 +74,11 @@ __device__ __forceinline__ void put_position(const L& lds, double* S, int q, con
 // step's start at their source cell while that cell's thread writes).  bad: key of this thread's first non-physical cell
 // (~0 if none); speed: CFL speed bits of its cells after stage 2.
 // ONE: every thread has at most one midpoint and one position.
-template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, int DIFF, bool ONE>
+// PAIR (with ONE, Euler): two threads a midpoint, one side each, for lines that
+// leave most SIMDs a wavefront at most: a midpoint's chain (4400 cycles of a
+// stage's 6200) loses three of its six interpolations, for half as many
+// midpoints to a wavefront.
+template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, int DIFF, bool ONE, bool PAIR>
 __device__ __forceinline__ void line_stage(const Tile1D<DIFF>& T, const LineLds<SYS, NV, DIFF>& lds, int stage,
                                            double dt, long long step, const Params& P, double* __restrict__ out,
                                            unsigned long long& bad, unsigned long long& speed)
@@ -86,7 +90,42 @@ __device__ __forceinline__ void line_stage(const Tile1D<DIFF>& T, const LineLds<
     double* F = lds.flux();
     double* fn = lds.node();
     const double* aux = lds.aux();
-    for (int i = tid; i < T.faces(stage); i += nt) {
+    if constexpr (PAIR) {
+        const int i = tid >> 1;
+        const bool right = tid & 1;
+        if (i < T.faces(stage)) {
+            const int q = a - G - 2 + i - base;
+            double n[5][NV], f[NV];
+#pragma unroll
+            for (int m = 0; m < 5; ++m)
+#pragma unroll
+                for (int v = 0; v < NV; ++v) n[m][v] = S[v * cap + (right ? q + 5 - m : q + m)];
+            Node<NV> A, B;
+            A.u = aux[q + 2];
+            A.H = aux[2 * cap + q + 2];
+            A.s = aux[3 * cap + q + 2];
+            B.u = aux[q + 3];
+            B.p = aux[cap + q + 3];
+            B.H = aux[2 * cap + q + 3];
+            B.s = aux[3 * cap + q + 3];
+            face_flux_pair<NV, FLUX, SCHEME, CHAR>(n, right, P, f,
+                                                   [&](Eigen<NV>& E) { roe_average<NV>(A, B, P.gamma, E); });
+            if constexpr (DIFF == DIFF_MND) {
+                // (the right lane's centre is node j+1)
+                double g[NV];
+                node_flux<NV>(n[2], B, g);
+                if (right) {
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) fn[v * cap + i] = g[v];
+                }
+            }
+            if (!right) {
+#pragma unroll
+                for (int v = 0; v < NV; ++v) F[v * cap + i] = f[v];
+            }
+        }
+    }
+    for (int i = tid; !PAIR && i < T.faces(stage); i += nt) {
         const int q = a - G - 2 + i - base;  // node j-2 of midpoint j = a - G + i
         double s[6][NV];
 #pragma unroll
@@ -285,13 +324,13 @@ __device__ __forceinline__ bool line_dt(const LineStep& A, double t, unsigned lo
 }
 
 // One SSP-RK3 step of tile t of a line cut every w cells: in -> out.
-template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, int DIFF, bool AHEAD>
+template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, int DIFF, bool AHEAD, bool PAIR>
 __device__ __forceinline__ void line_tile_step(const double* __restrict__ in, double* __restrict__ out,
                                                Ctrl* __restrict__ ctrl, const Params& P, const LineStep& A, int t,
                                                int w, double* mem)
 {
     const Tile1D<DIFF> T(t, w, P.nx, P.bc_x);
-    const LineLds<SYS, NV, DIFF> lds{mem, LINE_CAP};
+    const LineLds<SYS, NV, DIFF> lds{mem, PAIR ? PAIR_CAP : LINE_CAP};
     // Every workgroup takes the same decision from the record: an earlier
     // step's failure and the final time are fixed when the launch starts
     // (a failure in this launch has a key of this step; the status follows
@@ -344,7 +383,7 @@ __device__ __forceinline__ void line_tile_step(const double* __restrict__ in, do
     unsigned long long bad = ~0ull, speed = 0ull;
 #pragma unroll
     for (int stage = 0; stage < 3; ++stage) {
-        line_stage<SYS, NV, FLUX, SCHEME, CHAR, DIFF, true>(T, lds, stage, dt, step, P, stage == 2 ? out : nullptr,
+        line_stage<SYS, NV, FLUX, SCHEME, CHAR, DIFF, true, PAIR>(T, lds, stage, dt, step, P, stage == 2 ? out : nullptr,
                                                             bad, speed);
         __syncthreads();
     }
@@ -365,22 +404,22 @@ __device__ __forceinline__ void line_tile_step(const double* __restrict__ in, do
     }
 }
 
-template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, int DIFF>
+template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, int DIFF, bool PAIR>
 __global__ void __launch_bounds__(TILE_THREADS, LINE_WAVES<SYS>)
 line_step(const double* __restrict__ in, double* __restrict__ out, Ctrl* __restrict__ ctrl, Params P, LineStep A,
           int width)
 {
-    __shared__ double mem[LineLds<SYS, NV, DIFF>::PER * LINE_CAP];
-    line_tile_step<SYS, NV, FLUX, SCHEME, CHAR, DIFF, true>(in, out, ctrl, P, A, (int)blockIdx.x, width, mem);
+    __shared__ double mem[LineLds<SYS, NV, DIFF>::PER * (PAIR ? PAIR_CAP : LINE_CAP)];
+    line_tile_step<SYS, NV, FLUX, SCHEME, CHAR, DIFF, true, PAIR>(in, out, ctrl, P, A, (int)blockIdx.x, width, mem);
 }
 
 // One step of many independent 1D Euler lines: block b takes a tile of the
 // grid map[b] of the table (a search over the table without a map).
-template <int FLUX, int SCHEME, bool CHAR>
+template <int FLUX, int SCHEME, bool CHAR, bool PAIR>
 __global__ void __launch_bounds__(TILE_THREADS, LINE_WAVES<SYS_EULER>)
 line_step_multi(const ReqGrid* __restrict__ reqs, const int* __restrict__ map, int nreq, int tick_step)
 {
-    __shared__ double mem[LineLds<SYS_EULER, 3, DIFF_MND>::PER * LINE_CAP];
+    __shared__ double mem[LineLds<SYS_EULER, 3, DIFF_MND>::PER * (PAIR ? PAIR_CAP : LINE_CAP)];
     // the tiles of one XCD are one contiguous run of the table's tiles
     const int b = xcd_order((int)blockIdx.x, 0, (int)gridDim.x);
     int row = 0;
@@ -404,7 +443,7 @@ line_step_multi(const ReqGrid* __restrict__ reqs, const int* __restrict__ map, i
     A.fixed_dt = 0.0;
     A.parity = (R.parity0 + tick_step) & 1;
     const bool at_home = A.parity == R.home;
-    line_tile_step<SYS_EULER, 3, FLUX, SCHEME, CHAR, DIFF_MND, false>(at_home ? R.U : R.U1, at_home ? R.U1 : R.U,
+    line_tile_step<SYS_EULER, 3, FLUX, SCHEME, CHAR, DIFF_MND, false, PAIR>(at_home ? R.U : R.U1, at_home ? R.U1 : R.U,
                                                                      R.ctrl, R.P, A, b - R.blk0, R.width, mem);
 }
 
@@ -476,7 +515,7 @@ line_solo(double* __restrict__ U, Ctrl* __restrict__ ctrl, Params P, LineStep A,
                 whole = false;
                 break;
             }
-            line_stage<SYS, NV, FLUX, SCHEME, CHAR, DIFF, false>(T, lds, stage, dt, step0 + n, P, nullptr, bad, speed);
+            line_stage<SYS, NV, FLUX, SCHEME, CHAR, DIFF, false, false>(T, lds, stage, dt, step0 + n, P, nullptr, bad, speed);
             if (bad != ~0ull) atomicMin(&first_bad, bad);
             if (stage == 0 && tid == 0) red[next] = 0ull;
             if (stage < 2) __syncthreads();
@@ -553,17 +592,24 @@ using namespace wcnst;
 
 // --------------------------------------------------------------- launchers
 
-int wcnst_line_width(int diff, int nx)
+int wcnst_line_width(int diff, int nx, bool pair)
 {
+    if (pair) return line_tile_width<DIFF_MND, true>(nx);
     return diff == WCNST_MD ? line_tile_width<DIFF_MD>(nx)
                             : (diff == WCNST_HWCNS ? line_tile_width<DIFF_HW>(nx) : line_tile_width<DIFF_MND>(nx));
 }
 
-int wcnst_line_tiles(int diff, int nx)
+int wcnst_line_tiles(int diff, int nx, bool pair)
 {
-    const int w = wcnst_line_width(diff, nx);
+    const int w = wcnst_line_width(diff, nx, pair);
     return (nx + w - 1) / w;
 }
+
+// Two threads a midpoint while that leaves the launch within one workgroup
+// per CU, where a step lasts as long as one wavefront's chain: 2048 cells 11.2
+// -> 9.7 us, 27 000 (248 tiles) 11.1 -> 9.7; 30 000 (276) 11.4 -> 11.8, 110 000
+// 14.9 -> 19.2.
+bool wcnst_line_pair(long long tiles) { return tiles <= WCNST_PAIR_TILES; }
 
 namespace {
 
@@ -596,17 +642,18 @@ struct LineLaunch {
             else solo<SYS, NV, FLUX, SCHEME, CHAR, DIFF_MND>();
             return;
         }
-        const dim3 g((unsigned)wcnst_line_tiles(d->diff, d->nx)), b(TILE_THREADS);
-        const int w = wcnst_line_width(d->diff, d->nx);
-        if (d->diff == WCNST_MD)
-            hipLaunchKernelGGL((line_step<SYS, NV, FLUX, SCHEME, CHAR, DIFF_MD>), g, b, 0, st, in, out, ctrl, *P, A,
-                               w);
-        else if (d->diff == WCNST_HWCNS)
-            hipLaunchKernelGGL((line_step<SYS, NV, FLUX, SCHEME, CHAR, DIFF_HW>), g, b, 0, st, in, out, ctrl, *P, A,
-                               w);
-        else
-            hipLaunchKernelGGL((line_step<SYS, NV, FLUX, SCHEME, CHAR, DIFF_MND>), g, b, 0, st, in, out, ctrl, *P, A,
-                               w);
+        if (d->diff == WCNST_MD) tiles<SYS, NV, FLUX, SCHEME, CHAR, DIFF_MD, false>();
+        else if (d->diff == WCNST_HWCNS) tiles<SYS, NV, FLUX, SCHEME, CHAR, DIFF_HW, false>();
+        else if (SYS == SYS_EULER && wcnst_line_pair(wcnst_line_tiles(d->diff, d->nx, true)))
+            tiles<SYS, NV, FLUX, SCHEME, CHAR, DIFF_MND, SYS == SYS_EULER>();
+        else tiles<SYS, NV, FLUX, SCHEME, CHAR, DIFF_MND, false>();
+    }
+    template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, int DIFF, bool PAIR>
+    void tiles() const
+    {
+        hipLaunchKernelGGL((line_step<SYS, NV, FLUX, SCHEME, CHAR, DIFF, PAIR>),
+                           dim3((unsigned)wcnst_line_tiles(d->diff, d->nx, PAIR)), dim3(TILE_THREADS), 0, st, in, out,
+                           ctrl, *P, A, wcnst_line_width(d->diff, d->nx, PAIR));
     }
     template <int SYS, int NV, int FLUX, bool CHAR>
     void scheme() const
@@ -644,13 +691,18 @@ struct MultiLaunch {
     const ReqGrid* reqs;
     const int* map;
     int nreq, nblocks, tick_step;
+    bool pair;
     hipStream_t st;
 
     template <int FLUX, int SCHEME, bool CHAR>
     void go() const
     {
-        hipLaunchKernelGGL((line_step_multi<FLUX, SCHEME, CHAR>), dim3((unsigned)nblocks), dim3(TILE_THREADS), 0, st,
-                           reqs, map, nreq, tick_step);
+        if (pair)
+            hipLaunchKernelGGL((line_step_multi<FLUX, SCHEME, CHAR, true>), dim3((unsigned)nblocks),
+                               dim3(TILE_THREADS), 0, st, reqs, map, nreq, tick_step);
+        else
+            hipLaunchKernelGGL((line_step_multi<FLUX, SCHEME, CHAR, false>), dim3((unsigned)nblocks),
+                               dim3(TILE_THREADS), 0, st, reqs, map, nreq, tick_step);
     }
     template <int FLUX, bool CHAR>
     void scheme() const
@@ -705,9 +757,9 @@ hipError_t wcnst_launch_line_solo(const wcnst_desc* d, const Params& P, Ctrl* ct
 }
 
 hipError_t wcnst_launch_line_multi(const wcnst_desc* d, const void* reqs, const int* map, int nreq, int nblocks,
-                                   int tick_step, hipStream_t st)
+                                   int tick_step, bool pair, hipStream_t st)
 {
-    const MultiLaunch L{d, (const ReqGrid*)reqs, map, nreq, nblocks, tick_step, st};
+    const MultiLaunch L{d, (const ReqGrid*)reqs, map, nreq, nblocks, tick_step, pair, st};
     if (d->flux == WCNST_LF) L.chars<FLUX_LF>();
     else if (d->flux == WCNST_VANLEER) L.chars<FLUX_VL>();
     else L.chars<FLUX_ROE>();

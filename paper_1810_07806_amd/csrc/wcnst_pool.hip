@@ -205,6 +205,12 @@ static wcnst_status issue_dim(wcnst_pool* p, int ndim, const std::vector<int>& a
         ty = wcnst_auto_rows(strips.data(), rows.data(), (int)act.size(), p->slots);
     }
     if (ty == 0) ty = 35;  // (unused in 1D)
+    bool pair = false;
+    if (ndim == 1) {
+        long long tiles = 0;
+        for (int i : act) tiles += wcnst_line_tiles(p->reqs[(size_t)i].d.diff, p->reqs[(size_t)i].d.nx, true);
+        pair = wcnst_line_pair(tiles);
+    }
     int blocks = 0;
     int n = 0;
     bool general = false;
@@ -226,8 +232,8 @@ static wcnst_status issue_dim(wcnst_pool* p, int ndim, const std::vector<int>& a
         wcnst_make_params(&r.d, &q.P);
         q.t_final = r.t_final;
         q.cfl = r.cfl;
-        q.nstrips = ndim == 2 ? (r.d.nx + TX - 1) / TX : wcnst_line_tiles(r.d.diff, r.d.nx);
-        q.width = wcnst_line_width(r.d.diff, r.d.nx);
+        q.nstrips = ndim == 2 ? (r.d.nx + TX - 1) / TX : wcnst_line_tiles(r.d.diff, r.d.nx, pair);
+        q.width = wcnst_line_width(r.d.diff, r.d.nx, pair);
         q.blk0 = blocks;
         q.parity0 = q.home = r.parity;
         blocks += q.nstrips * (ndim == 2 ? (r.d.ny + ty - 1) / ty : 1);
@@ -243,7 +249,7 @@ static wcnst_status issue_dim(wcnst_pool* p, int ndim, const std::vector<int>& a
     }
     if (ndim == 1) {
         for (int64_t s = 0; s < steps; ++s)
-            WCNST_HIP_TRY(wcnst_launch_line_multi(&p->scheme, p->d_req[0], map, n, blocks, (int)(s & 1), st));
+            WCNST_HIP_TRY(wcnst_launch_line_multi(&p->scheme, p->d_req[0], map, n, blocks, (int)(s & 1), pair, st));
         WCNST_HIP_TRY(wcnst_launch_line_settle_multi(p->d_req[0], n, st));
         return WCNST_OK;
     }

@@ -12,7 +12,7 @@ using namespace wcnst;
 // every index the kernel forms stays inside the tile's positions and reads
 // only what the stage's input holds; else a code naming the first violation.
 template <int DIFF>
-static int check(int nx, int bc, int w, int cap)
+static int check(int nx, int bc, int w, int cap, int threads)
 {
     const int nt = (nx + w - 1) / w;
     using T1 = Tile1D<DIFF>;
@@ -32,7 +32,8 @@ static int check(int nx, int bc, int w, int cap)
         int lo = base, hi = base + np;  // positions the stage's input holds
         for (int s = 0; s < 3; ++s) {
             const int a = T.A(s), b = T.B(s), nf = T.faces(s);
-            if (nf > cap || nf != b - a + 2 * T1::G - 1) return 5;
+            // (a thread, or a pair of threads, for every midpoint)
+            if (nf > cap || nf > threads || nf != b - a + 2 * T1::G - 1) return 5;
             for (int i = 0; i < nf; ++i)
                 for (int m = 0; m < 6; ++m) {
                     const int p = a - T1::G - 2 + i + m;
@@ -65,11 +66,14 @@ static int check(int nx, int bc, int w, int cap)
 
 extern "C" {
 
-int lc_check(int nx, int bc, int diff)
+// pair: tiles of two threads a midpoint (MND)
+int lc_check(int nx, int bc, int diff, int pair)
 {
-    if (diff == DIFF_MD) return check<DIFF_MD>(nx, bc, line_tile_width<DIFF_MD>(nx), LINE_CAP);
-    if (diff == DIFF_HW) return check<DIFF_HW>(nx, bc, line_tile_width<DIFF_HW>(nx), LINE_CAP);
-    return check<DIFF_MND>(nx, bc, line_tile_width<DIFF_MND>(nx), LINE_CAP);
+    constexpr int N = TILE_THREADS;
+    if (pair) return check<DIFF_MND>(nx, bc, line_tile_width<DIFF_MND, true>(nx), PAIR_CAP, PAIR_FACES);
+    if (diff == DIFF_MD) return check<DIFF_MD>(nx, bc, line_tile_width<DIFF_MD>(nx), LINE_CAP, N);
+    if (diff == DIFF_HW) return check<DIFF_HW>(nx, bc, line_tile_width<DIFF_HW>(nx), LINE_CAP, N);
+    return check<DIFF_MND>(nx, bc, line_tile_width<DIFF_MND>(nx), LINE_CAP, N);
 }
 
 }  // extern "C"

@@ -36,9 +36,11 @@ def _burgers(nx, diff, bc):
 
 
 # smallest lines; one workgroup holding the line up to its last position, one
-# past it; one, two and three tiles around their edges
+# past it; tiles of two threads a midpoint around their edges and up to the
+# most (27904 cells, 256 tiles), one thread a midpoint past them
 EULER = [(n, "mnd", bc) for n in (5, 57, 247, 248, 249, 474, 475) for bc in ("zero_gradient", "periodic", "reflect", "fixed")]
 EULER += [(n, diff, "periodic") for n in (5, 61, 246, 247, 250, 251, 463) for diff in ("md", "hwcns")]
+EULER += [(n, "mnd", bc) for n in (327, 328, 436, 27904, 27905) for bc in ("zero_gradient", "periodic", "reflect")]
 SCALAR = [(n, diff, bc) for n in (5, 641, 1023, 1525, 1529, 1600) for diff, bc in
           (("mnd", "periodic"), ("md", "periodic"), ("hwcns", "zero_gradient"))]
 
@@ -100,3 +102,27 @@ def test_timed_solves_continue(orc, torch, nx):
     t2, n2 = s.solve(Ug, t_final=0.05)
     assert abs(t2 - 0.05) <= 1e-13 and n2 > 0 and s.status()["steps"] == n + n2
     s.close()
+
+
+@pytest.mark.parametrize("kw", [{}, dict(flux="lf", scheme="js"), dict(flux="vanleer", charwise=0)])
+def test_batch_whose_tiles_change_equals_single_solves(torch, kw):
+    """40 tubes of 1000 cells start with a thread a midpoint (400 pair tiles
+    would not fit the CUs) and end, as most of them finish, with two."""
+    from paper_1810_07806_amd.wcnst import Batch, Solver
+    items = [W.random_tube(np.random.default_rng(i), 1000) for i in range(40)]
+    for d, _ in items:
+        d.update(kw)
+    ts = [0.01 if i % 4 else 0.03 for i in range(40)]
+    b = Batch([d for d, _ in items])
+    b.set_tuning(4)
+    U = b.pack([U for _, U in items])
+    r = b.solve(U, ts)
+    got = b.unpack(U)
+    for i in (0, 1, 20, 39):
+        s = Solver(items[i][0])
+        V = s.new_state(items[i][1])
+        t, n = s.solve(V, t_final=ts[i])
+        assert r["status"][i] == 0 and r["steps"][i] == n and r["t"][i] == t
+        assert np.array_equal(got[i], V.cpu().numpy().reshape(got[i].shape))
+        s.close()
+    b.close()

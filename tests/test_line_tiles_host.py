@@ -22,9 +22,9 @@ def lc(tmp_path_factory):
     return ctypes.CDLL(lib)
 
 
-@pytest.mark.parametrize("diff", [0, 1, 2])
+@pytest.mark.parametrize("diff,pair", [(0, 0), (0, 1), (1, 0), (2, 0)])
 @pytest.mark.parametrize("bc", [0, 1, 2, 3])
-def test_line_tiles_stay_in_their_positions(lc, bc, diff):
+def test_line_tiles_stay_in_their_positions(lc, bc, diff, pair):
     sizes = list(range(5, 1100)) + [2047, 2048, 4096, 16383, 16384, 54321, 56169, 100003, 1000001]
     for nx in sizes:
-        assert lc.lc_check(nx, bc, diff) == 0, nx
+        assert lc.lc_check(nx, bc, diff, pair) == 0, nx
