@@ -135,7 +135,9 @@ wcnst_status wcnst_rhs(wcnst_solver* s, const double* U, double* R, uint8_t* fla
 /* One SSP-RK3 step of U in place (Sec. 2, Shu-Osher form).  dt > 0 is used
  * as given; dt <= 0 takes dt = cfl / max((|u|+c)/dx [+ (|v|+c)/dy]) from U
  * (|a|/dx for advection, |u|/dx for Burgers).  Asynchronous; advances the
- * device time by dt.  A non-physical stage output sets the sticky status. */
+ * device time by dt.  A non-physical stage output sets the sticky status;
+ * until wcnst_reset later calls on the handle then take no step and leave U
+ * alone. */
 wcnst_status wcnst_step(wcnst_solver* s, double* U, double dt, double cfl);
 
 /* Advance U in place from the current device time until t_final (dt clipped

@@ -1260,14 +1260,16 @@ __global__ void ctrl_init(Ctrl* ctrl, double t, long long step)
 }
 
 // Opens a solve / step call: clears the done flag and the speed
-// accumulators of the current record and remembers the step counter.
+// accumulators of the current record and remembers the newest record's step
+// counter (of both: after a failure the host's parity no longer follows the
+// records), which is how the end of the call knows whether it took a step.
 __global__ void ctrl_open(Ctrl* ctrl, int parity)
 {
     if (threadIdx.x != 0) return;
     ctrl->rec[parity].smax_bits = 0ull;
     for (int k = 0; k < 3; ++k) ctrl->speed[k] = 0ull;
     ctrl->done = 0;
-    ctrl->call_step0 = ctrl->rec[parity].step;
+    ctrl->call_step0 = max(ctrl->rec[0].step, ctrl->rec[1].step);
     // a launch that stopped part of its wavefronts early (a non-physical
     // state found during it) leaves the adaptive layout's count behind
     SegCtl* seg = seg_ctl_of(ctrl);

@@ -473,7 +473,7 @@ line_solo(double* __restrict__ U, Ctrl* __restrict__ ctrl, Params P, LineStep A,
     if (ctrl->status != 0 || (!open && ctrl->done != 0)) {  // (one workgroup: uniform)
         if (open && tid == 0) {
             ctrl->done = 0;
-            ctrl->call_step0 = step0;
+            ctrl->call_step0 = max(ctrl->rec[0].step, ctrl->rec[1].step);
         }
         return;
     }
@@ -559,11 +559,14 @@ line_solo(double* __restrict__ U, Ctrl* __restrict__ ctrl, Params P, LineStep A,
 // Ends a run of line steps: the newest state into U (it is in U1 when its
 // parity is not `home`), the status of a failure in the last step, and the
 // speed into the newest record.  A step that failed in its first or second
-// stage leaves U at the step's start.
+// stage leaves U at the step's start.  A call that took no step (one on a
+// line that had failed before, or of no steps) has nothing to end: U is the
+// caller's, and U1 may hold a step that was rejected.
 __device__ __forceinline__ void settle_line(Ctrl* ctrl, double* __restrict__ U, const double* __restrict__ U1,
                                             size_t n, int home, int blk, int nblk)
 {
     const int p = ctrl->rec[0].step >= ctrl->rec[1].step ? 0 : 1;
+    if (ctrl->rec[p].step == ctrl->call_step0) return;
     const unsigned long long key = ctrl->bad_key;
     const int at = key != ~0ull && (key >> 36) % 3 != 2 ? p ^ 1 : p;
     if (at != home)
