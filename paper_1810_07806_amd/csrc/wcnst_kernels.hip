@@ -2011,7 +2011,8 @@ extern "C" wcnst_status wcnst_solve(wcnst_solver* s, double* U, double t_final, 
     Ctrl c;
     wcnst_status st = read_ctrl(s, &c);
     if (st) return st;
-    if (s->kind != K_EUL2) s->parity = &newest(c) == &c.rec[0] ? 0 : 1;
+    // (steps queued past t_final flipped the host's parity but no record)
+    s->parity = &newest(c) == &c.rec[0] ? 0 : 1;
     return solve_outcome(c, t_final, max_steps, t_out, steps_out);
 }
 
