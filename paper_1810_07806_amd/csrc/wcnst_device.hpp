@@ -263,7 +263,7 @@ struct Ctrl {
     long long call_step0;        // step counter at the start of the current solve call
     int status;                  // sticky WCNST_E_NONPHYSICAL
     int done;                    // sticky: t_final reached in the current call
-    // max CFL speed (bit pattern) of the state after step n in speed[n % 3]:
+    // max CFL speed (bit pattern) of the state after step n in speed[n mod 3]:
     // a launch that runs a whole step reads one, accumulates the next, and
     // clears the one after
     unsigned long long speed[3];
@@ -293,6 +293,14 @@ struct LineStep {
     double t_final, cfl, fixed_dt;
     int parity;
 };
+
+// The element of Ctrl::speed for the state after step n (any sign: a caller
+// may number its steps from wherever it likes).
+WCNST_HD int speed_slot(long long n)
+{
+    const int k = (int)(n % 3);
+    return k < 0 ? k + 3 : k;
+}
 
 // ------------------------------------------------------------ helpers
 

@@ -1300,7 +1300,7 @@ __global__ void __launch_bounds__(256) wavespeed(const double* __restrict__ U, C
     __syncthreads();
     if (threadIdx.x != 0) return;
     for (int i = 1; i < 256 / WAVE; ++i) m = red[i] > m ? red[i] : m;
-    unsigned long long* dst = NV == 4 ? &ctrl->rec[parity].smax_bits : &ctrl->speed[ctrl->rec[parity].step % 3];
+    unsigned long long* dst = NV == 4 ? &ctrl->rec[parity].smax_bits : &ctrl->speed[speed_slot(ctrl->rec[parity].step)];
     if (__hip_atomic_load(dst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < m) atomicMax(dst, m);
 }
 

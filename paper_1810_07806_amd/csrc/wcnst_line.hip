@@ -364,7 +364,7 @@ __device__ __forceinline__ void line_tile_step(const double* __restrict__ in, do
         if (lead) ctrl->status = (int)WCNST_E_NONPHYSICAL;
         return;
     }
-    const int cell = (int)(step % 3), next = cell == 2 ? 0 : cell + 1, after = next == 2 ? 0 : next + 1;
+    const int cell = speed_slot(step), next = cell == 2 ? 0 : cell + 1, after = next == 2 ? 0 : next + 1;
     double dt;
     if (!line_dt(A, time, cell == 0 ? sp0 : (cell == 1 ? sp1 : sp2), dt)) {
         if (lead) ctrl->done = 1;
@@ -469,7 +469,7 @@ line_solo(double* __restrict__ U, Ctrl* __restrict__ ctrl, Params P, LineStep A,
     int p = A.parity;
     const long long step0 = ctrl->rec[p].step;
     double time = ctrl->rec[p].t, before = time, dt = 0.0;
-    unsigned long long smax = ctrl->speed[step0 % 3];
+    unsigned long long smax = ctrl->speed[speed_slot(step0)];
     if (ctrl->status != 0 || (!open && ctrl->done != 0)) {  // (one workgroup: uniform)
         if (open && tid == 0) {
             ctrl->done = 0;
@@ -553,7 +553,7 @@ line_solo(double* __restrict__ U, Ctrl* __restrict__ ctrl, Params P, LineStep A,
         ctrl->rec[p].step = step;
     }
     ctrl->rec[p].smax_bits = smax;
-    for (int k = 0; k < 3; ++k) ctrl->speed[k] = k == (int)(step % 3) ? smax : 0ull;
+    for (int k = 0; k < 3; ++k) ctrl->speed[k] = k == speed_slot(step) ? smax : 0ull;
 }
 
 // Ends a run of line steps: the newest state into U (it is in U1 when its
@@ -573,7 +573,7 @@ __device__ __forceinline__ void settle_line(Ctrl* ctrl, double* __restrict__ U, 
         for (size_t i = (size_t)blk * blockDim.x + threadIdx.x; i < n; i += (size_t)nblk * blockDim.x) U[i] = U1[i];
     if (blk == 0 && threadIdx.x == 0) {
         if (key != ~0ull) ctrl->status = (int)WCNST_E_NONPHYSICAL;
-        ctrl->rec[p].smax_bits = ctrl->speed[ctrl->rec[p].step % 3];
+        ctrl->rec[p].smax_bits = ctrl->speed[speed_slot(ctrl->rec[p].step)];
     }
 }
 
