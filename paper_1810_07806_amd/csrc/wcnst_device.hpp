@@ -302,6 +302,14 @@ WCNST_HD int speed_slot(long long n)
     return k < 0 ? k + 3 : k;
 }
 
+// A failure's key holds its global stage, 3 * step + stage, in 28 bits above
+// the cell's 36.  The stage of step n that a key names: 0 to 2, or a larger
+// value where it names another step (steps wrap around with those bits).
+WCNST_HD unsigned bad_stage_of(unsigned long long key, long long n)
+{
+    return (unsigned)((key >> 36) - 3ull * (unsigned long long)n) & ((1u << 28) - 1u);
+}
+
 // ------------------------------------------------------------ helpers
 
 // Whether a rare condition holds on any lane of the wavefront: one scalar

@@ -360,7 +360,7 @@ __device__ __forceinline__ void line_tile_step(const double* __restrict__ in, do
     }
     const bool lead = t == 0 && threadIdx.x == 0;
     if (done != 0 || status != 0) return;
-    if ((long long)(key >> 36) < 3 * step) {
+    if (key != ~0ull && bad_stage_of(key, step) > 2u) {
         if (lead) ctrl->status = (int)WCNST_E_NONPHYSICAL;
         return;
     }
@@ -568,7 +568,8 @@ __device__ __forceinline__ void settle_line(Ctrl* ctrl, double* __restrict__ U, 
     const int p = ctrl->rec[0].step >= ctrl->rec[1].step ? 0 : 1;
     if (ctrl->rec[p].step == ctrl->call_step0) return;
     const unsigned long long key = ctrl->bad_key;
-    const int at = key != ~0ull && (key >> 36) % 3 != 2 ? p ^ 1 : p;
+    // (the newest record is the one that a failed step opened)
+    const int at = key != ~0ull && bad_stage_of(key, ctrl->rec[p].step - 1) != 2u ? p ^ 1 : p;
     if (at != home)
         for (size_t i = (size_t)blk * blockDim.x + threadIdx.x; i < n; i += (size_t)nblk * blockDim.x) U[i] = U1[i];
     if (blk == 0 && threadIdx.x == 0) {

@@ -29,3 +29,14 @@ def test_speed_slots_stay_in_their_array(sc, start):
     slots = [sc.sc_speed_slot(n) for n in range(start, start + 9)]
     assert set(slots) == {0, 1, 2}
     assert all(b == (a + 1) % 3 for a, b in zip(slots, slots[1:]))
+
+
+@pytest.mark.parametrize("start", STARTS)
+def test_a_failure_names_its_own_step(sc, start):
+    sc.sc_bad_stage.argtypes = [ctypes.c_longlong, ctypes.c_int, ctypes.c_longlong, ctypes.c_longlong]
+    sc.sc_bad_stage.restype = ctypes.c_uint
+    for stage in range(3):
+        for cell in (0, 2**34 - 1):
+            assert sc.sc_bad_stage(start, stage, cell, start) == stage
+            for other in (-5, -1, 1, 2, 1000):
+                assert sc.sc_bad_stage(start, stage, cell, start + other) > 2
