@@ -1825,18 +1825,19 @@ static void prof_end(wcnst_solver* s, hipEvent_t end, int stages)
 
 // One SSP-RK3 step: one launch on a 1D line (the state is in U when the
 // step parity is the home parity, else in U1), three fused stage kernels in
-// 2D.
-static void launch_step(wcnst_solver* s, double* U, double t_final, double cfl, double fixed_dt)
+// 2D.  Returns the error of these launches or of one before them.
+static hipError_t launch_step(wcnst_solver* s, double* U, double t_final, double cfl, double fixed_dt)
 {
     hipEvent_t end;
     if (s->kind != K_EUL2) {
         const bool at_home = s->parity == s->home;
         const LineStep A{t_final, cfl, fixed_dt, s->parity};
         (void)prof_begin(s, &end);
-        (void)wcnst_launch_line_step(&s->d, s->P, s->ctrl, at_home ? U : s->U1, at_home ? s->U1 : U, A, s->stream);
+        const hipError_t e =
+            wcnst_launch_line_step(&s->d, s->P, s->ctrl, at_home ? U : s->U1, at_home ? s->U1 : U, A, s->stream);
         prof_end(s, end, 3);
         s->parity ^= 1;
-        return;
+        return e;
     }
     const double* in[3] = {U, s->U1, s->U2};
     double* outp[3] = {s->U1, s->U2, U};
@@ -1852,6 +1853,7 @@ static void launch_step(wcnst_solver* s, double* U, double t_final, double cfl, 
         prof_end(s, end, 1);
     }
     s->parity ^= 1;
+    return hipGetLastError();
 }
 
 static wcnst_status read_ctrl(wcnst_solver* s, Ctrl* c)
@@ -1947,9 +1949,8 @@ extern "C" wcnst_status wcnst_step(wcnst_solver* s, double* U, double dt, double
     hipLaunchKernelGGL(ctrl_open, dim3(1), dim3(64), 0, s->stream, s->ctrl, s->parity);
     if (!(dt > 0.0)) launch_wavespeed(s, U);
     s->home = s->parity;
-    launch_step(s, U, INFINITY, cfl, dt > 0.0 ? dt : 0.0);
+    HIP_TRY(launch_step(s, U, INFINITY, cfl, dt > 0.0 ? dt : 0.0));
     HIP_TRY(launch_settle(s, U));
-    HIP_TRY(hipGetLastError());
     return WCNST_OK;
 }
 
@@ -1979,9 +1980,8 @@ extern "C" wcnst_status wcnst_solve(wcnst_solver* s, double* U, double t_final, 
     int64_t prev_launched = 0;
     while (launched < max_steps) {
         const int64_t k = std::min(chunk, max_steps - launched);
-        for (int64_t i = 0; i < k; ++i) launch_step(s, U, t_final, cfl, 0.0);
+        for (int64_t i = 0; i < k; ++i) HIP_TRY(launch_step(s, U, t_final, cfl, 0.0));
         launched += k;
-        HIP_TRY(hipGetLastError());
         if (!timed) continue;
         // snapshot after this chunk; inspect the previous one (one chunk of look-ahead)
         HIP_TRY(hipMemcpyAsync(s->host_ctrl[slot], s->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s->stream));
@@ -2104,9 +2104,8 @@ extern "C" wcnst_status wcnst_solve_noalloc(const wcnst_desc* d, void* hip_strea
     int64_t launched = 0, chunk = 4;
     while (launched < max_steps) {
         const int64_t k = std::min(chunk, max_steps - launched);
-        for (int64_t i = 0; i < k; ++i) launch_step(&s, U, t_final, cfl, 0.0);
+        for (int64_t i = 0; i < k; ++i) HIP_TRY(launch_step(&s, U, t_final, cfl, 0.0));
         launched += k;
-        HIP_TRY(hipGetLastError());
         if (!timed) continue;
         st = read_ctrl(&s, &c);
         if (st) return st;
