@@ -224,7 +224,8 @@ wcnst_status wcnst_stage_layout(wcnst_solver* s, int32_t* rows, int32_t cap, int
  * 1D, every launch of one or more whole steps) is bracketed by HIP events on
  * the solver's stream.  wcnst_profile_read synchronises and returns the
  * summed milliseconds and the number of Runge-Kutta stages launched since
- * the last reset. */
+ * the last reset (of a solve that runs a short 1D line in launches of many
+ * steps: the stages of the steps it took). */
 wcnst_status wcnst_profile_enable(wcnst_solver* s, int enable);
 wcnst_status wcnst_profile_read(wcnst_solver* s, double* stage_ms, int64_t* stage_launches);
 

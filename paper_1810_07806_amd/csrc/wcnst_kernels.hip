@@ -1885,7 +1885,7 @@ static wcnst_status solve_short_line(wcnst_solver* s, double* U, double t_final,
         hipEvent_t end;
         (void)prof_begin(s, &end);
         HIP_TRY(wcnst_launch_line_solo(&s->d, s->P, s->ctrl, U, A, k, open, s->stream));
-        prof_end(s, end, 3 * k);
+        prof_end(s, end, 0);
         open = false;
         launched += k;
         if (!std::isfinite(t_final) && launched < max_steps) {
@@ -1897,6 +1897,8 @@ static wcnst_status solve_short_line(wcnst_solver* s, double* U, double t_final,
         s->parity = &newest(*c) == &c->rec[0] ? 0 : 1;
         if (c->status != 0 || c->done) break;
     } while (launched < max_steps);
+    // (a launch ends at the final time or a failure: the steps it ran)
+    if (s->prof) s->prof_stages += 3 * (newest(*c).step - c->call_step0);
     return WCNST_OK;
 }
 
