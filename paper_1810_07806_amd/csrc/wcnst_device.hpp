@@ -203,8 +203,20 @@ struct Tile1D {
     WCNST_HD int positions() const { return B(0) + REACH - base(); }
     // midpoints A(s) - G + i, i < faces(s): those the cells [A(s), B(s)) need
     WCNST_HD int faces(int s) const { return B(s) - A(s) + 2 * G - 1; }
-    WCNST_HD int out_lo(int s) const { return ghosts && A(s) == 0 ? -REACH : A(s); }
-    WCNST_HD int out_hi(int s) const { return ghosts && B(s) == nx ? nx + REACH : B(s); }
+    // (ghosts: those that the next stage reads; after the last stage, where the
+    // line is one tile, all of them, for the next step)
+    WCNST_HD int out_lo(int s) const
+    {
+        if (!ghosts || s == 2) return ghosts && c0 == 0 ? -REACH : A(s);
+        const int a = c0 - REACH * (2 - s);
+        return a < -REACH ? -REACH : a;
+    }
+    WCNST_HD int out_hi(int s) const
+    {
+        if (!ghosts || s == 2) return ghosts && c1 == nx ? nx + REACH : B(s);
+        const int b = c1 + REACH * (2 - s);
+        return b > nx + REACH ? nx + REACH : b;
+    }
     // the cell whose stage output position p takes
     WCNST_HD int source(int p, int bc) const;
 };
