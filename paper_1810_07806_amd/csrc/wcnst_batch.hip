@@ -258,16 +258,21 @@ extern "C" wcnst_status wcnst_batch_stats(const wcnst_batch* b, int32_t* ticks, 
 }
 
 // Tile widths and first blocks of the table rows [0, n); the blocks of a
-// launch and whether its tiles take two threads a midpoint.
-static int set_tiles(ReqGrid* tab, int n, bool* pair)
+// launch and the kind of its tiles.
+static int set_tiles(ReqGrid* tab, int n, LineTiles* shape)
 {
     long long tiles = 0;
-    for (int j = 0; j < n; ++j) tiles += wcnst_line_tiles(WCNST_MND, tab[j].P.nx, true);
-    *pair = wcnst_line_pair(tiles);
+    int longest = 0;
+    for (int j = 0; j < n; ++j) {
+        tiles += wcnst_line_tiles(WCNST_MND, tab[j].P.nx, true);
+        longest = std::max(longest, tab[j].P.nx);
+    }
+    *shape = wcnst_line_shape(n, tiles, longest);
+    const bool pair = *shape == LineTiles::PAIR;
     int blocks = 0;
     for (int j = 0; j < n; ++j) {
-        tab[j].nstrips = wcnst_line_tiles(WCNST_MND, tab[j].P.nx, *pair);
-        tab[j].width = wcnst_line_width(WCNST_MND, tab[j].P.nx, *pair);
+        tab[j].nstrips = wcnst_line_tiles(WCNST_MND, tab[j].P.nx, pair);
+        tab[j].width = wcnst_line_width(WCNST_MND, tab[j].P.nx, pair);
         tab[j].blk0 = blocks;
         blocks += tab[j].nstrips;
     }
@@ -283,12 +288,12 @@ static const StepRec& newest(const Ctrl& c) { return c.rec[0].step >= c.rec[1].s
 // (a tick of fewer steps than steps_per_tick is launched directly).  A
 // replaced graph is retired, not destroyed: the previous tick, which may
 // have launched it, can still be running.
-static wcnst_status run_tick(wcnst_batch* b, int nreq, int blocks, bool pair, int steps, bool table_changed,
+static wcnst_status run_tick(wcnst_batch* b, int nreq, int blocks, LineTiles shape, int steps, bool table_changed,
                              long long tick)
 {
     if (steps != b->steps_per_tick) {
         for (int s = 0; s < steps; ++s)
-            WCNST_HIP_TRY(wcnst_launch_line_multi(&b->d0, b->d_req, b->d_map, nreq, blocks, s & 1, pair, b->stream));
+            WCNST_HIP_TRY(wcnst_launch_line_multi(&b->d0, b->d_req, b->d_map, nreq, blocks, s & 1, shape, b->stream));
         return WCNST_OK;
     }
     if (!b->exec || table_changed) {
@@ -300,7 +305,7 @@ static wcnst_status run_tick(wcnst_batch* b, int nreq, int blocks, bool pair, in
         WCNST_HIP_TRY(hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal));
         hipError_t le = hipSuccess;
         for (int s = 0; s < steps && le == hipSuccess; ++s)
-            le = wcnst_launch_line_multi(&b->d0, b->d_req, b->d_map, nreq, blocks, s & 1, pair, b->cap);
+            le = wcnst_launch_line_multi(&b->d0, b->d_req, b->d_map, nreq, blocks, s & 1, shape, b->cap);
         hipError_t ce = hipStreamEndCapture(b->cap, &g);
         if (le != hipSuccess || ce != hipSuccess)
             return wcnst_fail(WCNST_E_HIP, "graph capture failed: %s / %s", hipGetErrorString(le),
@@ -364,8 +369,8 @@ extern "C" wcnst_status wcnst_batch_solve(wcnst_batch* b, double* U, const doubl
 
     // table of all rows; control blocks reset and initial speeds in one launch
     for (int i = 0; i < n; ++i) b->h_req[i] = rows[(size_t)i];
-    bool pair = false;
-    int blocks = set_tiles(b->h_req, n, &pair);
+    LineTiles shape;
+    int blocks = set_tiles(b->h_req, n, &shape);
     WCNST_HIP_TRY(hipMemcpyAsync(b->d_req, b->h_req, sizeof(ReqGrid) * (size_t)n, hipMemcpyHostToDevice, b->stream));
     WCNST_HIP_TRY(hipEventRecord(b->ev0, b->stream));
     WCNST_HIP_TRY(wcnst_launch_multi_init(1, b->d_req, n, b->stream));
@@ -393,13 +398,13 @@ extern "C" wcnst_status wcnst_batch_solve(wcnst_batch* b, double* U, const doubl
                 tab[j] = rows[(size_t)i];
                 tab[j].parity0 = parity[(size_t)i];
             }
-            blocks = set_tiles(tab, (int)active.size(), &pair);
+            blocks = set_tiles(tab, (int)active.size(), &shape);
             WCNST_HIP_TRY(hipMemcpyAsync(b->d_req, tab, sizeof(ReqGrid) * active.size(), hipMemcpyHostToDevice,
                                          b->stream));
             WCNST_HIP_TRY(wcnst_launch_block_map(b->d_req, (int)active.size(), blocks, b->d_map, b->stream));
             uploads += 1;
         }
-        wcnst_status st = run_tick(b, (int)active.size(), blocks, pair, steps, changed, k);
+        wcnst_status st = run_tick(b, (int)active.size(), blocks, shape, steps, changed, k);
         if (st) {
             (void)hipStreamSynchronize(b->stream);
             reap_retired(b, -1);

@@ -319,7 +319,7 @@ WCNST_HD int speed_slot(long long n)
 // value where it names another step (steps wrap around with those bits).
 WCNST_HD unsigned bad_stage_of(unsigned long long key, long long n)
 {
-    return (unsigned)((key >> 36) - 3ull * (unsigned long long)n) & ((1u << 28) - 1u);
+    return ((unsigned)(key >> 36) - 3u * (unsigned)n) & ((1u << 28) - 1u);
 }
 
 // ------------------------------------------------------------ helpers

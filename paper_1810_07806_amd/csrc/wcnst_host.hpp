@@ -53,10 +53,16 @@ int wcnst_line_width(int diff, int nx, bool pair);
 int wcnst_line_tiles(int diff, int nx, bool pair);
 constexpr int WCNST_PAIR_TILES = 256;
 bool wcnst_line_pair(long long tiles);
+// The tiles of a multi-line launch: a thread a midpoint, two, or a thread a
+// midpoint in workgroups of one or two wavefronts that hold short lines whole.
+enum class LineTiles { WIDE, PAIR, WAVES_1, WAVES_2 };
+// The rule, from the number of lines, their tiles of two threads a midpoint
+// and the longest.
+LineTiles wcnst_line_shape(int lines, long long pair_tiles, int longest);
 hipError_t wcnst_launch_line_step(const wcnst_desc* d, const wcnst::Params& P, wcnst::Ctrl* ctrl, const double* in,
                                   double* out, const wcnst::LineStep& A, hipStream_t st);
 hipError_t wcnst_launch_line_multi(const wcnst_desc* d, const void* reqs, const int* map, int nreq, int nblocks,
-                                   int tick_step, bool pair, hipStream_t st);
+                                   int tick_step, LineTiles shape, hipStream_t st);
 // Whether one workgroup runs the whole line, and up to `steps` steps of it in
 // one launch, in place (open: the start of a solve or step call; nothing
 // else has to be launched before it).

@@ -32,6 +32,16 @@ namespace wcnst {
 template <int SYS>
 constexpr int LINE_SOLO_THREADS = SYS == SYS_EULER ? 256 : 1024;
 
+// Threads of a tile, and positions it has room for.
+constexpr int tile_threads(LineTiles t)
+{
+    return t == LineTiles::WAVES_2 ? 2 * WAVE : (t == LineTiles::WAVES_1 ? WAVE : TILE_THREADS);
+}
+constexpr int tile_cap(LineTiles t)
+{
+    return t == LineTiles::WIDE ? LINE_CAP : (t == LineTiles::PAIR ? PAIR_CAP : tile_threads(t));
+}
+
 // Wavefronts per SIMD the tile kernels are held to (168 registers for Euler).
 template <int SYS>
 constexpr int LINE_WAVES = SYS == SYS_EULER ? 3 : 4;
@@ -73,18 +83,19 @@ __device__ __forceinline__ void put_position(const L& lds, double* S, int q, con
 // other stages, to LDS (in place of the first stage: ghosts still read the
 // step's start at their source cell while that cell's thread writes).  bad: key of this thread's first non-physical cell
 // (~0 if none); speed: CFL speed bits of its cells after stage 2.
-// ONE: every thread has at most one midpoint and one position.
-// PAIR (with ONE, Euler): two threads a midpoint, one side each, for lines that
+// THREADS (0: any): every thread of so many has at most one midpoint and one
+// position.
+// PAIR (with THREADS, Euler): two threads a midpoint, one side each, for lines that
 // leave most SIMDs a wavefront at most: a midpoint's chain (4400 cycles of a
 // stage's 6200) loses three of its six interpolations, for half as many
 // midpoints to a wavefront.
-template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, int DIFF, bool ONE, bool PAIR>
+template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, int DIFF, int THREADS, bool PAIR>
 __device__ __forceinline__ void line_stage(const Tile1D<DIFF>& T, const LineLds<SYS, NV, DIFF>& lds, int stage,
                                            double dt, long long step, const Params& P, double* __restrict__ out,
                                            unsigned long long& bad, unsigned long long& speed)
 {
     constexpr int G = Tile1D<DIFF>::G;
-    const int tid = (int)threadIdx.x, nt = ONE ? TILE_THREADS : (int)blockDim.x, cap = lds.cap;
+    const int tid = (int)threadIdx.x, nt = THREADS ? THREADS : (int)blockDim.x, cap = lds.cap;
     const int a = T.A(stage), base = T.base();
     const double* S = lds.state(stage);
     double* F = lds.flux();
@@ -164,7 +175,7 @@ __device__ __forceinline__ void line_stage(const Tile1D<DIFF>& T, const LineLds<
         }
 #pragma unroll
         for (int v = 0; v < NV; ++v) F[v * cap + i] = f[v];
-        if constexpr (ONE) break;
+        if constexpr (THREADS != 0) break;
     }
     if constexpr (DIFF == DIFF_HW) {
         // node fluxes a-2 .. b+1
@@ -236,14 +247,14 @@ __device__ __forceinline__ void line_stage(const Tile1D<DIFF>& T, const LineLds<
                 speed = bits > speed ? bits : speed;
             }
         }
-        if constexpr (ONE) break;
+        if constexpr (THREADS != 0) break;
     }
 }
 
 // Loads the tile's positions (cells, ghosts) from U and forms their Roe
-// quantities.  (No barrier.)  ONE: at most two positions per thread, both
+// quantities.  (No barrier.)  THREADS: at most two positions per thread, both
 // loads in flight, then the caller's (read) and the weight table.
-template <int SYS, int NV, int DIFF, bool ONE, class READ>
+template <int SYS, int NV, int DIFF, int THREADS, class READ>
 __device__ __forceinline__ void line_load(const Tile1D<DIFF>& T, const LineLds<SYS, NV, DIFF>& lds,
                                           const double* __restrict__ U, const Params& P, const READ& read)
 {
@@ -266,20 +277,20 @@ __device__ __forceinline__ void line_load(const Tile1D<DIFF>& T, const LineLds<S
 #pragma unroll
         for (int v = 0; v < NV; ++v) u[v] = U[(size_t)v * P.nx + c];
     };
-    if constexpr (ONE) {
-        const int i = (int)threadIdx.x, k = i + TILE_THREADS;
+    if constexpr (THREADS != 0) {
+        const int i = (int)threadIdx.x, k = i + THREADS;
         double u[2][NV];
         if (i < n) fetch(i, u[0]);
         if (k < n) fetch(k, u[1]);
         read();
-        put_weight_table(TILE_THREADS - WAVE);
+        put_weight_table(THREADS - WAVE);
 #pragma unroll 1
         for (int m = 0; m < 2; ++m) {
-            if (m * TILE_THREADS + i >= n) break;
+            if (m * THREADS + i >= n) break;
             double t[NV];
 #pragma unroll
             for (int v = 0; v < NV; ++v) t[v] = m ? u[1][v] : u[0][v];
-            store(m * TILE_THREADS + i, t);
+            store(m * THREADS + i, t);
         }
     } else {
         for (int i = (int)threadIdx.x; i < n; i += (int)blockDim.x) {
@@ -324,13 +335,14 @@ __device__ __forceinline__ bool line_dt(const LineStep& A, double t, unsigned lo
 }
 
 // One SSP-RK3 step of tile t of a line cut every w cells: in -> out.
-template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, int DIFF, bool AHEAD, bool PAIR>
+template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, int DIFF, bool AHEAD, LineTiles TILES>
 __device__ __forceinline__ void line_tile_step(const double* __restrict__ in, double* __restrict__ out,
                                                Ctrl* __restrict__ ctrl, const Params& P, const LineStep& A, int t,
                                                int w, double* mem)
 {
     const Tile1D<DIFF> T(t, w, P.nx, P.bc_x);
-    const LineLds<SYS, NV, DIFF> lds{mem, PAIR ? PAIR_CAP : LINE_CAP};
+    const LineLds<SYS, NV, DIFF> lds{mem, tile_cap(TILES)};
+    constexpr int THREADS = tile_threads(TILES);
     // Every workgroup takes the same decision from the record: an earlier
     // step's failure and the final time are fixed when the launch starts
     // (a failure in this launch has a key of this step; the status follows
@@ -353,9 +365,9 @@ __device__ __forceinline__ void line_tile_step(const double* __restrict__ in, do
         status = ctrl->status;
     };
     if constexpr (AHEAD) {
-        line_load<SYS, NV, DIFF, true>(T, lds, in, P, record);
+        line_load<SYS, NV, DIFF, THREADS>(T, lds, in, P, record);
     } else {
-        line_load<SYS, NV, DIFF, true>(T, lds, in, P, [] {});
+        line_load<SYS, NV, DIFF, THREADS>(T, lds, in, P, [] {});
         record();
     }
     const bool lead = t == 0 && threadIdx.x == 0;
@@ -383,8 +395,8 @@ __device__ __forceinline__ void line_tile_step(const double* __restrict__ in, do
     unsigned long long bad = ~0ull, speed = 0ull;
 #pragma unroll
     for (int stage = 0; stage < 3; ++stage) {
-        line_stage<SYS, NV, FLUX, SCHEME, CHAR, DIFF, true, PAIR>(T, lds, stage, dt, step, P, stage == 2 ? out : nullptr,
-                                                            bad, speed);
+        line_stage<SYS, NV, FLUX, SCHEME, CHAR, DIFF, THREADS, TILES == LineTiles::PAIR>(
+            T, lds, stage, dt, step, P, stage == 2 ? out : nullptr, bad, speed);
         __syncthreads();
     }
     if (bad != ~0ull) atomicMin(&ctrl->bad_key, bad);
@@ -396,7 +408,7 @@ __device__ __forceinline__ void line_tile_step(const double* __restrict__ in, do
     __syncthreads();
     if (threadIdx.x == 0) {
         speed = red[0];
-        for (int w = 1; w < TILE_THREADS / WAVE; ++w) speed = red[w] > speed ? red[w] : speed;
+        for (int w = 1; w < THREADS / WAVE; ++w) speed = red[w] > speed ? red[w] : speed;
         unsigned long long* dst = &ctrl->speed[next];
         // the record only grows during the launch: a workgroup whose
         // maximum it already holds skips the atomic
@@ -404,22 +416,32 @@ __device__ __forceinline__ void line_tile_step(const double* __restrict__ in, do
     }
 }
 
-template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, int DIFF, bool PAIR>
+template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, int DIFF, LineTiles TILES>
 __global__ void __launch_bounds__(TILE_THREADS, LINE_WAVES<SYS>)
 line_step(const double* __restrict__ in, double* __restrict__ out, Ctrl* __restrict__ ctrl, Params P, LineStep A,
           int width)
 {
-    __shared__ double mem[LineLds<SYS, NV, DIFF>::PER * (PAIR ? PAIR_CAP : LINE_CAP)];
-    line_tile_step<SYS, NV, FLUX, SCHEME, CHAR, DIFF, true, PAIR>(in, out, ctrl, P, A, (int)blockIdx.x, width, mem);
+    __shared__ double mem[LineLds<SYS, NV, DIFF>::PER * tile_cap(TILES)];
+    line_tile_step<SYS, NV, FLUX, SCHEME, CHAR, DIFF, true, TILES>(in, out, ctrl, P, A, (int)blockIdx.x, width, mem);
+}
+
+// A uniform pointer known to point to device memory (the statement keeps the
+// two casts from cancelling).
+template <class T>
+__device__ __forceinline__ T* in_global(T* p)
+{
+    auto g = (__attribute__((address_space(1))) T*)p;
+    asm("" : "+s"(g));
+    return (T*)g;
 }
 
 // One step of many independent 1D Euler lines: block b takes a tile of the
 // grid map[b] of the table (a search over the table without a map).
-template <int FLUX, int SCHEME, bool CHAR, bool PAIR>
-__global__ void __launch_bounds__(TILE_THREADS, LINE_WAVES<SYS_EULER>)
+template <int FLUX, int SCHEME, bool CHAR, LineTiles TILES>
+__global__ void __launch_bounds__(tile_threads(TILES), LINE_WAVES<SYS_EULER>)
 line_step_multi(const ReqGrid* __restrict__ reqs, const int* __restrict__ map, int nreq, int tick_step)
 {
-    __shared__ double mem[LineLds<SYS_EULER, 3, DIFF_MND>::PER * (PAIR ? PAIR_CAP : LINE_CAP)];
+    __shared__ double mem[LineLds<SYS_EULER, 3, DIFF_MND>::PER * tile_cap(TILES)];
     // the tiles of one XCD are one contiguous run of the table's tiles
     const int b = xcd_order((int)blockIdx.x, 0, (int)gridDim.x);
     int row = 0;
@@ -443,8 +465,11 @@ line_step_multi(const ReqGrid* __restrict__ reqs, const int* __restrict__ map, i
     A.fixed_dt = 0.0;
     A.parity = (R.parity0 + tick_step) & 1;
     const bool at_home = A.parity == R.home;
-    line_tile_step<SYS_EULER, 3, FLUX, SCHEME, CHAR, DIFF_MND, false, PAIR>(at_home ? R.U : R.U1, at_home ? R.U1 : R.U,
-                                                                     R.ctrl, R.P, A, b - R.blk0, R.width, mem);
+    // (pointers read from a table are generic; an access through one counts
+    // with the LDS accesses too, and each of these would wait for all)
+    double *U = in_global(R.U), *U1 = in_global(R.U1);
+    line_tile_step<SYS_EULER, 3, FLUX, SCHEME, CHAR, DIFF_MND, false, TILES>(
+        at_home ? U : U1, at_home ? U1 : U, in_global(R.ctrl), R.P, A, b - R.blk0, R.width, mem);
 }
 
 // Many steps of a short line in one launch: one workgroup holds the whole
@@ -465,7 +490,7 @@ line_solo(double* __restrict__ U, Ctrl* __restrict__ ctrl, Params P, LineStep A,
     const int tid = (int)threadIdx.x;
     const Tile1D<DIFF> T(0, P.nx, P.nx, P.bc_x);
     LineLds<SYS, NV, DIFF> lds{mem, cap};
-    line_load<SYS, NV, DIFF, false>(T, lds, U, P, [] {});
+    line_load<SYS, NV, DIFF, 0>(T, lds, U, P, [] {});
     int p = A.parity;
     const long long step0 = ctrl->rec[p].step;
     double time = ctrl->rec[p].t, before = time, dt = 0.0;
@@ -515,7 +540,7 @@ line_solo(double* __restrict__ U, Ctrl* __restrict__ ctrl, Params P, LineStep A,
                 whole = false;
                 break;
             }
-            line_stage<SYS, NV, FLUX, SCHEME, CHAR, DIFF, false, false>(T, lds, stage, dt, step0 + n, P, nullptr, bad, speed);
+            line_stage<SYS, NV, FLUX, SCHEME, CHAR, DIFF, 0, false>(T, lds, stage, dt, step0 + n, P, nullptr, bad, speed);
             if (bad != ~0ull) atomicMin(&first_bad, bad);
             if (stage == 0 && tid == 0) red[next] = 0ull;
             if (stage < 2) __syncthreads();
@@ -615,6 +640,21 @@ int wcnst_line_tiles(int diff, int nx, bool pair)
 // 14.9 -> 19.2.
 bool wcnst_line_pair(long long tiles) { return tiles <= WCNST_PAIR_TILES; }
 
+// A launch of more lines than a CU's four full tiles hold at once, all of
+// which fit a workgroup of one or two wavefronts whole, takes such workgroups:
+// of the four wavefronts of a full tile those lines leave two or three idle in
+// their places on the CU.  Us a step, full tiles -> these: 4096 lines of 16
+// cells 68.1 -> 42.8, of 56 68.7 -> 45.3, of 57 69.7 -> 57.8, of 120 84.2 ->
+// 69.8; 2000 of 32 37.1 -> 26.9; 1000 lines gain nothing (18.8; 5 cells 20.2
+// -> 22.5).
+LineTiles wcnst_line_shape(int lines, long long pair_tiles, int longest)
+{
+    if (wcnst_line_pair(pair_tiles)) return LineTiles::PAIR;
+    const int positions = longest + 2 * Tile1D<DIFF_MND>::REACH;
+    if (lines <= 4 * WCNST_PAIR_TILES || positions > 2 * WAVE) return LineTiles::WIDE;
+    return positions <= WAVE ? LineTiles::WAVES_1 : LineTiles::WAVES_2;
+}
+
 namespace {
 
 struct LineLaunch {
@@ -655,9 +695,10 @@ struct LineLaunch {
     template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, int DIFF, bool PAIR>
     void tiles() const
     {
-        hipLaunchKernelGGL((line_step<SYS, NV, FLUX, SCHEME, CHAR, DIFF, PAIR>),
-                           dim3((unsigned)wcnst_line_tiles(d->diff, d->nx, PAIR)), dim3(TILE_THREADS), 0, st, in, out,
-                           ctrl, *P, A, wcnst_line_width(d->diff, d->nx, PAIR));
+        constexpr LineTiles TILES = PAIR ? LineTiles::PAIR : LineTiles::WIDE;
+        hipLaunchKernelGGL((line_step<SYS, NV, FLUX, SCHEME, CHAR, DIFF, TILES>),
+                           dim3((unsigned)wcnst_line_tiles(d->diff, d->nx, PAIR)), dim3(tile_threads(TILES)), 0, st, in,
+                           out, ctrl, *P, A, wcnst_line_width(d->diff, d->nx, PAIR));
     }
     template <int SYS, int NV, int FLUX, bool CHAR>
     void scheme() const
@@ -695,18 +736,22 @@ struct MultiLaunch {
     const ReqGrid* reqs;
     const int* map;
     int nreq, nblocks, tick_step;
-    bool pair;
+    LineTiles shape;
     hipStream_t st;
 
     template <int FLUX, int SCHEME, bool CHAR>
     void go() const
     {
-        if (pair)
-            hipLaunchKernelGGL((line_step_multi<FLUX, SCHEME, CHAR, true>), dim3((unsigned)nblocks),
-                               dim3(TILE_THREADS), 0, st, reqs, map, nreq, tick_step);
-        else
-            hipLaunchKernelGGL((line_step_multi<FLUX, SCHEME, CHAR, false>), dim3((unsigned)nblocks),
-                               dim3(TILE_THREADS), 0, st, reqs, map, nreq, tick_step);
+        if (shape == LineTiles::PAIR) run<FLUX, SCHEME, CHAR, LineTiles::PAIR>();
+        else if (shape == LineTiles::WAVES_1) run<FLUX, SCHEME, CHAR, LineTiles::WAVES_1>();
+        else if (shape == LineTiles::WAVES_2) run<FLUX, SCHEME, CHAR, LineTiles::WAVES_2>();
+        else run<FLUX, SCHEME, CHAR, LineTiles::WIDE>();
+    }
+    template <int FLUX, int SCHEME, bool CHAR, LineTiles TILES>
+    void run() const
+    {
+        hipLaunchKernelGGL((line_step_multi<FLUX, SCHEME, CHAR, TILES>), dim3((unsigned)nblocks),
+                           dim3(tile_threads(TILES)), 0, st, reqs, map, nreq, tick_step);
     }
     template <int FLUX, bool CHAR>
     void scheme() const
@@ -761,9 +806,9 @@ hipError_t wcnst_launch_line_solo(const wcnst_desc* d, const Params& P, Ctrl* ct
 }
 
 hipError_t wcnst_launch_line_multi(const wcnst_desc* d, const void* reqs, const int* map, int nreq, int nblocks,
-                                   int tick_step, bool pair, hipStream_t st)
+                                   int tick_step, LineTiles shape, hipStream_t st)
 {
-    const MultiLaunch L{d, (const ReqGrid*)reqs, map, nreq, nblocks, tick_step, pair, st};
+    const MultiLaunch L{d, (const ReqGrid*)reqs, map, nreq, nblocks, tick_step, shape, st};
     if (d->flux == WCNST_LF) L.chars<FLUX_LF>();
     else if (d->flux == WCNST_VANLEER) L.chars<FLUX_VL>();
     else L.chars<FLUX_ROE>();

@@ -205,12 +205,18 @@ static wcnst_status issue_dim(wcnst_pool* p, int ndim, const std::vector<int>& a
         ty = wcnst_auto_rows(strips.data(), rows.data(), (int)act.size(), p->slots);
     }
     if (ty == 0) ty = 35;  // (unused in 1D)
-    bool pair = false;
+    LineTiles lines = LineTiles::WIDE;
     if (ndim == 1) {
         long long tiles = 0;
-        for (int i : act) tiles += wcnst_line_tiles(p->reqs[(size_t)i].d.diff, p->reqs[(size_t)i].d.nx, true);
-        pair = wcnst_line_pair(tiles);
+        int longest = 0;
+        for (int i : act) {
+            const wcnst_desc& d = p->reqs[(size_t)i].d;
+            tiles += wcnst_line_tiles(d.diff, d.nx, true);
+            longest = std::max(longest, d.nx);
+        }
+        lines = wcnst_line_shape((int)act.size(), tiles, longest);
     }
+    const bool pair = lines == LineTiles::PAIR;
     int blocks = 0;
     int n = 0;
     bool general = false;
@@ -249,7 +255,7 @@ static wcnst_status issue_dim(wcnst_pool* p, int ndim, const std::vector<int>& a
     }
     if (ndim == 1) {
         for (int64_t s = 0; s < steps; ++s)
-            WCNST_HIP_TRY(wcnst_launch_line_multi(&p->scheme, p->d_req[0], map, n, blocks, (int)(s & 1), pair, st));
+            WCNST_HIP_TRY(wcnst_launch_line_multi(&p->scheme, p->d_req[0], map, n, blocks, (int)(s & 1), lines, st));
         WCNST_HIP_TRY(wcnst_launch_line_settle_multi(p->d_req[0], n, st));
         return WCNST_OK;
     }

@@ -33,4 +33,11 @@ int tt_most(int nx, int bc, int diff, int pair)
     return most<DIFF_MND>(nx, bc, line_tile_width<DIFF_MND>(nx));
 }
 
+// Positions of a line that is one tile (0 where it is several).
+int tt_whole(int nx, int bc)
+{
+    const int w = line_tile_width<DIFF_MND>(nx);
+    return w < nx ? 0 : Tile1D<DIFF_MND>(0, w, nx, bc).positions();
+}
+
 }  // extern "C"

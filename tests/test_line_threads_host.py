@@ -27,3 +27,12 @@ def test_every_formed_position_has_a_thread(tt, bc, diff, pair):
     threads = tt.tt_threads()
     for nx in list(range(5, 60000)) + [100003, 1000001]:
         assert tt.tt_most(nx, bc, diff, pair) <= threads, nx
+
+
+@pytest.mark.parametrize("bc", [0, 1, 2, 3])
+def test_lines_of_one_and_two_wavefronts_fit_them(tt, bc):
+    """Up to 56 and 120 cells: every position and midpoint has a thread, and
+    every position its place."""
+    for nx in range(5, 121):
+        room = 64 if nx <= 56 else 128
+        assert 0 < tt.tt_whole(nx, bc) <= room and tt.tt_most(nx, bc, 0, 0) <= room, nx
