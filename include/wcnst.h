@@ -189,7 +189,8 @@ wcnst_status wcnst_reset(wcnst_solver* s, double t, int64_t steps);
  * segments of rows_per_segment rows (>= 1).  A segment of up to 12 rows is
  * worked whole by a workgroup of twelve wavefronts where that is the faster
  * (grids too small to fill the CUs), any other by four wavefronts, four rows
- * at a time.  The default, chosen at wcnst_create from the grid and the
+ * at a time; a workgroup takes several adjoining segments of 1, 2, 3, 5 or 6
+ * rows where they are too many to fill one each.  The default, chosen at wcnst_create from the grid and the
  * device's CU count, is the height of least estimated time: 1 to 12, or a
  * multiple of four up to 64.  0 restores it.  Changes only the work
  * decomposition, never the results.  Negative values: WCNST_E_INVALID_ARG. */

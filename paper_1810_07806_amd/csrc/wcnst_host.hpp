@@ -89,6 +89,10 @@ int wcnst_wave_slots();
 // on a device of `slots` wavefronts (2 per SIMD): the height minimising a
 // cost fitted to measured stage times.  Never changes results.
 int wcnst_auto_rows(const int* strips, const int* rows, int n, int slots);
+// Rows that a workgroup takes where the caller asks for segments of ty rows:
+// ty, or, of heights too low for the wavefronts of a workgroup, several
+// adjoining segments where the same fit has that faster.
+int wcnst_joined_rows(int ty, const int* strips, const int* rows, int n, int slots);
 // Whether a launch of `groups` segments of ty rows works them whole (twelve
 // wavefronts each) or by turns of four rows: the cheaper by the same fit.
 bool wcnst_short_segments(long long groups, int ty, int slots);

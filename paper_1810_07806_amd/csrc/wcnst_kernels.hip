@@ -1343,7 +1343,8 @@ struct wcnst_solver {
     Ctrl* host_ctrl[2];  // pinned snapshots for polling
     hipEvent_t snap_ev[2];
     int parity;
-    int ty;  // rows per 2D segment
+    int ty;      // rows per 2D segment
+    int ty_run;  // rows that a workgroup takes (whole segments; wcnst_joined_rows)
     bool ty_user;  // set by wcnst_set_tuning (else chosen at creation)
     int home;      // 1D: step parity at which the state is in U (else in U1)
     int slots;     // wavefront slots of the device
@@ -1589,7 +1590,7 @@ extern "C" wcnst_status wcnst_create(const wcnst_desc* d, void* hip_stream, void
     s->ty_user = false;
     {
         const int strips = (d->nx + TX - 1) / TX, rows = d->ny;
-        s->ty = d->ndim == 2 ? wcnst_auto_rows(&strips, &rows, 1, s->slots) : 35;
+        s->ty = s->ty_run = d->ndim == 2 ? wcnst_auto_rows(&strips, &rows, 1, s->slots) : 35;
     }
     s->home = 0;
     s->prof = false;
@@ -1697,7 +1698,7 @@ static void launch_sweep_t(const wcnst_solver* s, const double* U, const double*
     if constexpr (SYS == SYS_EULER && NV == 4) {
         const int nstrips = (s->d.nx + TX - 1) / TX;
         // cut flags (right-hand-side launches) need one segment height
-        const SegMap m = stage_segments(nstrips, s->d.ny, s->ty, s->slots, MODE == MODE_STAGE && !s->ty_user);
+        const SegMap m = stage_segments(nstrips, s->d.ny, s->ty_run, s->slots, MODE == MODE_STAGE && !s->ty_user);
         int seg_par = 0;
         if (MODE == MODE_STAGE && s->seg_on && m.nseg1 < m.nseg) {
             seg_par = (int)(s->seg_launch & 1);
@@ -2088,7 +2089,7 @@ extern "C" wcnst_status wcnst_solve_noalloc(const wcnst_desc* d, void* hip_strea
     s.slots = wcnst_wave_slots();
     {
         const int strips = (d->nx + TX - 1) / TX, rows = d->ny;
-        s.ty = d->ndim == 2 ? wcnst_auto_rows(&strips, &rows, 1, s.slots) : 35;
+        s.ty = s.ty_run = d->ndim == 2 ? wcnst_auto_rows(&strips, &rows, 1, s.slots) : 35;
     }
     wcnst_make_params(d, &s.P);
     const bool timed = std::isfinite(t_final);
@@ -2192,6 +2193,21 @@ bool wcnst_short_segments(long long groups, int ty, int slots)
     return ty <= ON_ROWS && short_cost(groups, ty, cus) < turns_cost(groups, ty, cus);
 }
 
+// Segments of ty rows of n grids, and the estimated stage time of a launch.
+static long long rows_groups(int ty, const int* strips, const int* rows, int n)
+{
+    long long groups = 0;
+    for (int i = 0; i < n; ++i) groups += (long long)strips[i] * ((rows[i] + ty - 1) / ty);
+    return groups;
+}
+
+static double rows_cost(int ty, const int* strips, const int* rows, int n, int cus)
+{
+    const long long groups = rows_groups(ty, strips, rows, n);
+    const double turns = turns_cost(groups, ty, cus);
+    return ty <= ON_ROWS ? std::min(turns, short_cost(groups, ty, cus)) : turns;
+}
+
 int wcnst_auto_rows(const int* strips, const int* rows, int n, int slots)
 {
     const int cus = slots / 8 > 0 ? slots / 8 : 1;
@@ -2200,8 +2216,7 @@ int wcnst_auto_rows(const int* strips, const int* rows, int n, int slots)
     // ties to the taller
     for (int ty = 64; ty >= 1; --ty) {
         if (ty > ON_ROWS && ty % WG_ROWS) continue;
-        long long groups = 0;
-        for (int i = 0; i < n; ++i) groups += (long long)strips[i] * ((rows[i] + ty - 1) / ty);
+        const long long groups = rows_groups(ty, strips, rows, n);
         double cost = ty <= ON_ROWS ? short_cost(groups, ty, cus) : 1e300;
         if (ty % WG_ROWS == 0) cost = std::min(cost, turns_cost(groups, ty, cus));
         if (cost < best) {
@@ -2212,19 +2227,40 @@ int wcnst_auto_rows(const int* strips, const int* rows, int n, int slots)
     return best_ty;
 }
 
+int wcnst_joined_rows(int ty, const int* strips, const int* rows, int n, int slots)
+{
+    const int cus = slots / 8 > 0 ? slots / 8 : 1;
+    // Of 1, 2, 3, 5 or 6 rows a turn's four (or a whole segment's twelve)
+    // wavefronts find too few; nearly as many more rows of midpoints are formed
+    // as cells.  With a few workgroups per CU that is hidden.  Us a step at
+    // 2048^2 alone -> joined: 1 row 4905 -> 886, 2 2553 -> 887, 3 1492 -> 904, 5
+    // 1374 -> 916, 6 1197 -> 905 (7: 1049, 8: 967).
+    if (ty >= 7 || ty % WG_ROWS == 0 || rows_groups(ty, strips, rows, n) <= 2 * cus) return ty;
+    int best_ty = ty;
+    double best = rows_cost(ty, strips, rows, n, cus);
+    for (int h = 2 * ty; h <= 16; h += ty) {
+        const double cost = rows_cost(h, strips, rows, n, cus);
+        if (cost < best) {
+            best = cost;
+            best_ty = h;
+        }
+    }
+    return best_ty;
+}
+
 extern "C" wcnst_status wcnst_set_tuning(wcnst_solver* s, int32_t rows_per_segment)
 {
     if (!s) return fail(WCNST_E_INVALID_ARG, "null handle");
     if (rows_per_segment < 0) return fail(WCNST_E_INVALID_ARG, "rows_per_segment must be >= 0");
-    if (rows_per_segment == 0) {
+    const int strips = (s->d.nx + TX - 1) / TX, rows = s->d.ny;
+    s->ty_user = rows_per_segment != 0;
+    if (!s->ty_user) {
         // the shape chosen at creation
-        const int strips = (s->d.nx + TX - 1) / TX, rows = s->d.ny;
-        s->ty = s->d.ndim == 2 ? wcnst_auto_rows(&strips, &rows, 1, s->slots) : 35;
-        s->ty_user = false;
-        return layout_reset(s);
+        s->ty = s->ty_run = s->d.ndim == 2 ? wcnst_auto_rows(&strips, &rows, 1, s->slots) : 35;
+    } else {
+        s->ty = rows_per_segment;
+        s->ty_run = wcnst_joined_rows(s->ty, &strips, &rows, 1, s->slots);
     }
-    s->ty = rows_per_segment;
-    s->ty_user = true;
     return layout_reset(s);
 }
 

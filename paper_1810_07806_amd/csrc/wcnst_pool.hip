@@ -196,13 +196,14 @@ static wcnst_status issue_dim(wcnst_pool* p, int ndim, const std::vector<int>& a
     if (act.empty()) return WCNST_OK;
     ReqGrid* tab = p->h_req[ndim - 1];
     int ty = p->ty;
-    if (ndim == 2 && ty == 0) {
+    if (ndim == 2) {
         std::vector<int> strips, rows;
         for (int i : act) {
             strips.push_back((p->reqs[(size_t)i].d.nx + TX - 1) / TX);
             rows.push_back(p->reqs[(size_t)i].d.ny);
         }
-        ty = wcnst_auto_rows(strips.data(), rows.data(), (int)act.size(), p->slots);
+        ty = ty == 0 ? wcnst_auto_rows(strips.data(), rows.data(), (int)act.size(), p->slots)
+                     : wcnst_joined_rows(ty, strips.data(), rows.data(), (int)act.size(), p->slots);
     }
     if (ty == 0) ty = 35;  // (unused in 1D)
     LineTiles lines = LineTiles::WIDE;
