@@ -995,7 +995,7 @@ WCNST_HD void midpoint_eigen(ST& st, const Params& P, Eigen<NV>& E)
 // Characteristic fields of the six stencil nodes, w[k][m] = l_k . U_m (sums
 // over the conserved variables in increasing order, structural zeros
 // skipped).
-template <int NV, class ST>
+template <int NV, bool PIN, class ST>
 WCNST_HD void project_nodes(ST& st, const Eigen<NV>& E, double (&w)[NV][6])
 {
 #pragma unroll
@@ -1009,7 +1009,7 @@ WCNST_HD void project_nodes(ST& st, const Eigen<NV>& E, double (&w)[NV][6])
                 acc = v == 0 ? E.L(k, v) * st(m, v) : fma(E.L(k, v), st(m, v), acc);
             }
             w[k][m] = acc;
-            keep_here(w[k][m]);
+            if constexpr (PIN) keep_here(w[k][m]);
         }
 }
 
@@ -1036,7 +1036,8 @@ WCNST_HD void back_project_field(const Eigen<NV>& E, int k, double wl, double wr
 // s: nodes j-2 .. j+3 around x_{j+1/2}.  basis(E): the characteristic basis
 // there.  F: flux at x_{j+1/2}.  fb: 6 flag bits per field (left mask |
 // right mask << 3).
-template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, class ST, class BASIS>
+// PIN: as below.
+template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, bool PIN = true, class ST, class BASIS>
 WCNST_HD void face_flux(ST& st, const Params& P, double (&F)[NV], unsigned& fb, const BASIS& basis)
 {
     fb = 0u;
@@ -1051,9 +1052,12 @@ WCNST_HD void face_flux(ST& st, const Params& P, double (&F)[NV], unsigned& fb, 
             // pinned where they stand: moved into the blocks after the
             // interpolation's branch, as the compiler would, they carry the
             // states, the basis and the candidates of every field along (2D
-            // stage 215 -> 145 registers, 1D step 145 -> 99).
+            // stage 215 -> 145 registers, 1D step 145 -> 99).  A kernel that a
+            // fixed workgroup holds to two wavefronts per SIMD has the
+            // registers and does not pin (persistent finish of 4096 tubes of
+            // 64 to 512 cells: 89.7 ms pinned, 86.9 not).
             double w[NV][6];
-            project_nodes<NV>(st, E, w);
+            project_nodes<NV, PIN>(st, E, w);
 #pragma unroll
             for (int k = 0; k < NV; ++k) {
                 unsigned mL, mR;
@@ -1064,8 +1068,8 @@ WCNST_HD void face_flux(ST& st, const Params& P, double (&F)[NV], unsigned& fb, 
 #pragma unroll
                 for (int v = 0; v < NV; ++v) {
                     if (Eigen<NV>::R_zero(v, k)) continue;
-                    keep_here(UL[v]);
-                    keep_here(UR[v]);
+                    if constexpr (PIN) keep_here(UL[v]);
+                    if constexpr (PIN) keep_here(UR[v]);
                 }
             }
         } else {
@@ -1097,10 +1101,10 @@ WCNST_HD void face_flux(ST& st, const Params& P, double (&F)[NV], unsigned& fb, 
 }
 
 // The same with the basis formed from the states of nodes j and j+1.
-template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, class ST>
+template <int SYS, int NV, int FLUX, int SCHEME, bool CHAR, bool PIN = true, class ST>
 WCNST_HD void face_flux(ST& st, const Params& P, double (&F)[NV], unsigned& fb)
 {
-    face_flux<SYS, NV, FLUX, SCHEME, CHAR>(st, P, F, fb, [&](auto& E) { midpoint_eigen<NV>(st, P, E); });
+    face_flux<SYS, NV, FLUX, SCHEME, CHAR, PIN>(st, P, F, fb, [&](auto& E) { midpoint_eigen<NV>(st, P, E); });
 }
 
 #if defined(__HIP_DEVICE_COMPILE__)

@@ -322,7 +322,7 @@ __device__ __forceinline__ void strip1d_stage(const double* __restrict__ U, cons
     double F[NV], fn[NV];
     unsigned fb;
     RegStencil<NV> st{s};
-    face_flux<SYS_EULER, NV, FLUX, SCHEME, CHAR>(st, P, F, fb);
+    face_flux<SYS_EULER, NV, FLUX, SCHEME, CHAR, false>(st, P, F, fb);
     node_flux<SYS_EULER, NV>(s[3], P, fn);
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
