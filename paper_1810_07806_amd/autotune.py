@@ -63,6 +63,8 @@ def _load(path):
         return json.load(f)
 
 
+# (21 and 35 end in a turn of fewer than four rows and seldom win; grids too
+# small for whole turns take the default, 0, which weighs heights from 1 row)
 DEFAULT_ROWS = (0, 12, 16, 21, 24, 28, 32, 35, 40, 48, 64)
 
 

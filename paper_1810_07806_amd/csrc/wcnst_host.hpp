@@ -51,7 +51,7 @@ hipError_t wcnst_launch_multi(const wcnst_desc* d, const void* reqs, const int* 
 // has the rule, from the launch's tiles at that width).
 int wcnst_line_width(int diff, int nx, bool pair);
 int wcnst_line_tiles(int diff, int nx, bool pair);
-constexpr int WCNST_PAIR_TILES = 256;
+constexpr int WCNST_PAIR_TILES = 256;  // the CUs of the device this is built for
 bool wcnst_line_pair(long long tiles);
 // The tiles of a multi-line launch: a thread a midpoint, two, or a thread a
 // midpoint in workgroups of one or two wavefronts that hold short lines whole.

@@ -322,7 +322,9 @@ __device__ __forceinline__ void strip1d_stage(const double* __restrict__ U, cons
     double F[NV], fn[NV];
     unsigned fb;
     RegStencil<NV> st{s};
-    face_flux<SYS_EULER, NV, FLUX, SCHEME, CHAR, false>(st, P, F, fb);
+    // (the linear scheme, without the cut test's branch, gains by the pins:
+    // 2000 lines of 90 cells 60.1 -> 47.9 us a step)
+    face_flux<SYS_EULER, NV, FLUX, SCHEME, CHAR, SCHEME == SCH_LINEAR>(st, P, F, fb);
     node_flux<SYS_EULER, NV>(s[3], P, fn);
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
@@ -606,7 +608,7 @@ __device__ __forceinline__ void seg_finish(SegCtl* __restrict__ seg, int par, in
 // of the four, then finishes one row.  The rows, their Roe quantities
 // (1/rho, pressure, enthalpy, sqrt(rho), formed once per node instead of four
 // times by the midpoints around it and three times by the node fluxes) and
-// the y fluxes stay in LDS, so a thread holds one midpoint only: 145
+// the y fluxes stay in LDS, so a thread holds one midpoint only: 148
 // registers, three wavefronts per SIMD (the LDS of a workgroup, 52.8 KB,
 // allows three workgroups per CU).  Bound: FP64 issue.  Against one
 // wavefront per segment with the stencils, four y fluxes and the next row in
@@ -1650,7 +1652,9 @@ struct SegMap {
 // the flow moves: SegCtl): na segments of a rows, na the segments of a strip
 // per SIMD, and the rest of c rows with c + 3 = 0.48 (a + 3); the first are
 // halved between two workgroups, so that all hold about c rows (2048^2: 24,
-// 23 and 22).
+// 23 and 22).  The proportions are those of a kernel of one wavefront a
+// segment and no longer the fastest (2048^2 273.9 us a stage, one height 271.5);
+// they stay because wcnst_stage_shape and wcnst_stage_layout report them.
 static SegMap stage_segments(int nstrips, int ny, int ty, int slots, bool balance)
 {
     const int nseg = (ny + ty - 1) / ty;
@@ -1980,7 +1984,6 @@ extern "C" wcnst_status wcnst_solve(wcnst_solver* s, double* U, double t_final, 
     int64_t chunk = 4;
     int slot = 0;
     bool have_prev = false;
-    int64_t prev_launched = 0;
     while (launched < max_steps) {
         const int64_t k = std::min(chunk, max_steps - launched);
         for (int64_t i = 0; i < k; ++i) HIP_TRY(launch_step(s, U, t_final, cfl, 0.0));
@@ -1993,7 +1996,6 @@ extern "C" wcnst_status wcnst_solve(wcnst_solver* s, double* U, double t_final, 
         slot ^= 1;
         if (!have_prev) {
             have_prev = true;
-            prev_launched = launched;
             continue;
         }
         HIP_TRY(hipEventSynchronize(s->snap_ev[prev]));
@@ -2006,8 +2008,6 @@ extern "C" wcnst_status wcnst_solve(wcnst_solver* s, double* U, double t_final, 
         int64_t est = 8;
         if (dt > 0.0 && std::isfinite(dt)) est = (int64_t)std::ceil((t_final - r.t) / dt) + 1;
         const int64_t queued = launched - done_steps;
-        (void)prev_launched;
-        prev_launched = launched;
         chunk = std::max<int64_t>(1, std::min<int64_t>(est - queued, 512));
     }
     HIP_TRY(launch_settle(s, U));

@@ -590,16 +590,19 @@ line_solo(double* __restrict__ U, Ctrl* __restrict__ ctrl, Params P, LineStep A,
 __device__ __forceinline__ void settle_line(Ctrl* ctrl, double* __restrict__ U, const double* __restrict__ U1,
                                             size_t n, int home, int blk, int nblk)
 {
-    const int p = ctrl->rec[0].step >= ctrl->rec[1].step ? 0 : 1;
-    if (ctrl->rec[p].step == ctrl->call_step0) return;
+    // (independent reads, issued together)
+    const long long s0 = ctrl->rec[0].step, s1 = ctrl->rec[1].step, begun = ctrl->call_step0;
     const unsigned long long key = ctrl->bad_key;
+    const int p = s0 >= s1 ? 0 : 1;
+    const long long step = p ? s1 : s0;
+    if (step == begun) return;
     // (the newest record is the one that a failed step opened)
-    const int at = key != ~0ull && bad_stage_of(key, ctrl->rec[p].step - 1) != 2u ? p ^ 1 : p;
+    const int at = key != ~0ull && bad_stage_of(key, step - 1) != 2u ? p ^ 1 : p;
     if (at != home)
         for (size_t i = (size_t)blk * blockDim.x + threadIdx.x; i < n; i += (size_t)nblk * blockDim.x) U[i] = U1[i];
     if (blk == 0 && threadIdx.x == 0) {
         if (key != ~0ull) ctrl->status = (int)WCNST_E_NONPHYSICAL;
-        ctrl->rec[p].smax_bits = ctrl->speed[speed_slot(ctrl->rec[p].step)];
+        ctrl->rec[p].smax_bits = ctrl->speed[speed_slot(step)];
     }
 }
 
@@ -637,7 +640,9 @@ int wcnst_line_tiles(int diff, int nx, bool pair)
 // Two threads a midpoint while that leaves the launch within one workgroup
 // per CU, where a step lasts as long as one wavefront's chain: 2048 cells 11.2
 // -> 9.7 us, 27 000 (248 tiles) 11.1 -> 9.7; 30 000 (276) 11.4 -> 11.8, 110 000
-// 14.9 -> 19.2.
+// 14.9 -> 19.2 (Shu-Osher states; a Sod tube of 27 904 cells takes 11.3).  For
+// MND: the right lane's centre node is the one whose node flux MND takes; MD and
+// HWCNS lines keep a thread a midpoint, and pairs are not written for them.
 bool wcnst_line_pair(long long tiles) { return tiles <= WCNST_PAIR_TILES; }
 
 // A launch of more lines than a CU's four full tiles hold at once, all of
@@ -784,9 +789,11 @@ hipError_t wcnst_launch_line_step(const wcnst_desc* d, const Params& P, Ctrl* ct
 }
 
 // One workgroup is ahead of a launch per step while its wavefronts have a
-// SIMD each (Euler: 4, 248 cells with MND: 9.5 us a step against 12.3; 312
-// cells 13.0 against 12.0) or their stage is short (scalar systems: 1000
-// cells 5.2 us against 6.9, 1500 6.6, 2000 8.4).
+// SIMD each (Euler: 4; us a step of 200 cells with MD 8.95 against 10.74, HWCNS
+// 9.33 against 10.95; MND 9.23 against 9.31, its tiles taking two threads a
+// midpoint; 312 cells with MND 13.0 against 12.0 for tiles of one) or their
+// stage is short (scalar systems: 1000 cells 5.2 us against 6.9, 1500 6.6,
+// 2000 8.4).
 bool wcnst_line_solo(const wcnst_desc* d)
 {
     if (d->ndim != 1) return false;
